@@ -1,0 +1,238 @@
+// Line transforms in LDS: X(k) = sum_j x(j) exp(-+ 2 pi i j k / n) of NL lines
+// at once for any n <= 1024 (sign - forward, + inverse), by mixed-radix
+// self-sorting stages (Stockham): a stage of radix r reads the r elements
+// j + u n / r of a group, multiplies by the twiddles and stores their r-point
+// transform at (j / Ns) Ns r + j mod Ns + u Ns, Ns the product of the earlier
+// radices, so input and output are both in natural order.  n is split into
+// radices 8, 4, 2, 3 and 5 (in registers); a prime factor p >= 7 takes a stage
+// of direct p-term sums, so a prime n is one direct sum per output.
+// A line of n costs about n sum(r) complex multiply-adds instead of n^2.
+//
+// Two LDS buffers per line are alternated, one barrier per stage.  Element i
+// of a line lies at i + i / 16: the stride-8 stores of a first radix-8 stage
+// then fall into different banks.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace flb {
+
+constexpr int FFT_MAX_STAGES = 12;   // 1024 = 8 8 4 4; worst case below 2^10: 7 or fewer
+
+struct FftPlan {
+    int n, stages;
+    int radix[FFT_MAX_STAGES];
+};
+
+inline FftPlan fft_plan(int n) {
+    FftPlan p{};
+    p.n = n;
+    int e = 0, m = n;
+    while (m % 2 == 0) {
+        m /= 2;
+        ++e;
+    }
+    // radices 8 with fours for the rest of the power of two (a two only for
+    // e = 1)
+    while (e > 0) {
+        const int r = (e == 1) ? 1 : (e % 3 == 0 ? 3 : 2);
+        p.radix[p.stages++] = 1 << r;
+        e -= r;
+    }
+    for (int f = 3; m > 1; f += 2)
+        while (m % f == 0) {
+            p.radix[p.stages++] = f;
+            m /= f;
+        }
+    return p;
+}
+
+// Complex values of precision R in LDS and in work buffers.
+template <typename R> struct Cx;
+template <> struct Cx<double> {
+    using T = double2;
+    static __device__ __forceinline__ T make(double re, double im) { return make_double2(re, im); }
+};
+template <> struct Cx<float> {
+    using T = float2;
+    static __device__ __forceinline__ T make(float re, float im) { return make_float2(re, im); }
+};
+template <typename R> using cx_t = typename Cx<R>::T;
+
+// Position of element i of a line, and the elements a line of n takes.
+__host__ __device__ __forceinline__ int fft_pos(int i) { return i + (i >> 4); }
+__host__ __device__ __forceinline__ int fft_ld(int n) { return n + (n >> 4) + 1; }
+
+// a / b for 0 <= a < 2^16, 1 <= b, with rb = 1.0f / b: (a + 1/2) / b is at
+// least 1 / (2 b) from an integer, beyond the rounding of the two FP32
+// operations for quotients below 2^11.
+__device__ __forceinline__ int fft_div(int a, float rb) { return (int)(((float)a + 0.5f) * rb); }
+
+// tw[j] = exp(-2 pi i j / n), evaluated in FP64 and rounded to R.
+template <typename R>
+__device__ __forceinline__ void twiddles(cx_t<R>* tw, int n) {
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+        double s, c;
+        sincospi(2.0 * (double)j / (double)n, &s, &c);
+        tw[j] = Cx<R>::make((R)c, (R)-s);
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ cx_t<R> cx_mul(cx_t<R> a, cx_t<R> w) {
+    return Cx<R>::make(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
+}
+template <typename R>
+__device__ __forceinline__ cx_t<R> cx_add(cx_t<R> a, cx_t<R> b) {
+    return Cx<R>::make(a.x + b.x, a.y + b.y);
+}
+template <typename R>
+__device__ __forceinline__ cx_t<R> cx_sub(cx_t<R> a, cx_t<R> b) {
+    return Cx<R>::make(a.x - b.x, a.y - b.y);
+}
+// -i a (forward) or +i a (inverse)
+template <typename R, bool INV>
+__device__ __forceinline__ cx_t<R> cx_rot(cx_t<R> a) {
+    return INV ? Cx<R>::make(-a.y, a.x) : Cx<R>::make(a.y, -a.x);
+}
+
+template <typename R, bool INV, int RAD>
+__device__ __forceinline__ void fft_small(cx_t<R> (&x)[RAD]) {
+    using C = cx_t<R>;
+    if constexpr (RAD == 2) {
+        const C a = x[0];
+        x[0] = cx_add<R>(a, x[1]);
+        x[1] = cx_sub<R>(a, x[1]);
+    } else if constexpr (RAD == 3) {
+        const R s3 = R(0.86602540378443864676);
+        const C t = cx_add<R>(x[1], x[2]), d = cx_sub<R>(x[1], x[2]);
+        const C m = Cx<R>::make(x[0].x - R(0.5) * t.x, x[0].y - R(0.5) * t.y);
+        const C r = cx_rot<R, INV>(Cx<R>::make(s3 * d.x, s3 * d.y));
+        x[0] = cx_add<R>(x[0], t);
+        x[1] = cx_add<R>(m, r);
+        x[2] = cx_sub<R>(m, r);
+    } else if constexpr (RAD == 4) {
+        const C a = cx_add<R>(x[0], x[2]), b = cx_sub<R>(x[0], x[2]);
+        const C c = cx_add<R>(x[1], x[3]), d = cx_rot<R, INV>(cx_sub<R>(x[1], x[3]));
+        x[0] = cx_add<R>(a, c);
+        x[1] = cx_add<R>(b, d);
+        x[2] = cx_sub<R>(a, c);
+        x[3] = cx_sub<R>(b, d);
+    } else if constexpr (RAD == 5) {
+        const R c1 = R(0.30901699437494742410), c2 = R(-0.80901699437494742410);
+        const R s1 = R(0.95105651629515357212), s2 = R(0.58778525229247312917);
+        const C t1 = cx_add<R>(x[1], x[4]), t2 = cx_add<R>(x[2], x[3]);
+        const C d1 = cx_sub<R>(x[1], x[4]), d2 = cx_sub<R>(x[2], x[3]);
+        const C m1 = Cx<R>::make(x[0].x + c1 * t1.x + c2 * t2.x, x[0].y + c1 * t1.y + c2 * t2.y);
+        const C m2 = Cx<R>::make(x[0].x + c2 * t1.x + c1 * t2.x, x[0].y + c2 * t1.y + c1 * t2.y);
+        const C r1 = cx_rot<R, INV>(Cx<R>::make(s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y));
+        const C r2 = cx_rot<R, INV>(Cx<R>::make(s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y));
+        x[0] = cx_add<R>(x[0], cx_add<R>(t1, t2));
+        x[1] = cx_add<R>(m1, r1);
+        x[4] = cx_sub<R>(m1, r1);
+        x[2] = cx_add<R>(m2, r2);
+        x[3] = cx_sub<R>(m2, r2);
+    } else {
+        static_assert(RAD == 8, "radices in registers: 2, 3, 4, 5, 8");
+        const R h = R(0.70710678118654752440);
+        C e[4] = {x[0], x[2], x[4], x[6]}, o[4] = {x[1], x[3], x[5], x[7]};
+        fft_small<R, INV, 4>(e);
+        fft_small<R, INV, 4>(o);
+        const C q = cx_rot<R, INV>(o[1]), q3 = cx_rot<R, INV>(o[3]);
+        o[1] = Cx<R>::make(h * (o[1].x + q.x), h * (o[1].y + q.y));
+        o[2] = cx_rot<R, INV>(o[2]);
+        o[3] = Cx<R>::make(h * (q3.x - o[3].x), h * (q3.y - o[3].y));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = cx_add<R>(e[u], o[u]);
+            x[u + 4] = cx_sub<R>(e[u], o[u]);
+        }
+    }
+}
+
+template <typename R, bool INV, int RAD>
+__device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>* __restrict__ b,
+                                          const cx_t<R>* __restrict__ tw, int NL, int n, int Ns) {
+    using C = cx_t<R>;
+    const int m = n / RAD, ld = fft_ld(n), ts = m / Ns;
+    const float rm = 1.0f / (float)m, rN = 1.0f / (float)Ns;
+    for (int t = threadIdx.x; t < NL * m; t += blockDim.x) {
+        const int L = fft_div(t, rm), j = t - L * m;
+        const int q = fft_div(j, rN), k = j - q * Ns;
+        const C* src = a + L * ld;
+        C x[RAD];
+#pragma unroll
+        for (int u = 0; u < RAD; ++u) x[u] = src[fft_pos(j + u * m)];
+        if (Ns > 1) {
+#pragma unroll
+            for (int u = 1; u < RAD; ++u) {
+                C w = tw[u * k * ts];
+                if (INV) w.y = -w.y;
+                x[u] = cx_mul<R>(x[u], w);
+            }
+        }
+        fft_small<R, INV, RAD>(x);
+        C* dst = b + L * ld;
+        const int o = q * Ns * RAD + k;
+#pragma unroll
+        for (int u = 0; u < RAD; ++u) dst[fft_pos(o + u * Ns)] = x[u];
+    }
+}
+
+// Any radix: every output as a direct sum over its group.
+template <typename R, bool INV>
+__device__ __forceinline__ void fft_stage_any(const cx_t<R>* __restrict__ a,
+                                              cx_t<R>* __restrict__ b,
+                                              const cx_t<R>* __restrict__ tw, int NL, int n, int Ns,
+                                              int rad) {
+    using C = cx_t<R>;
+    const int m = n / rad, ld = fft_ld(n), ts = m / Ns;
+    const float rn = 1.0f / (float)n, rm = 1.0f / (float)m, rN = 1.0f / (float)Ns;
+    for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
+        const int L = fft_div(t, rn), i = t - L * n;
+        const int u = fft_div(i, rm), j = i - u * m;     // output u of group j
+        const int q = fft_div(j, rN), k = j - q * Ns;
+        const C* src = a + L * ld;
+        const int inc = k * ts + u * m;                  // < n
+        R re = R(0), im = R(0);
+        int idx = 0;
+        for (int v = 0; v < rad; ++v) {
+            const C x = src[fft_pos(j + v * m)];
+            const C w = tw[idx];
+            const R wi = INV ? -w.y : w.y;
+            re = fma(x.x, w.x, fma(-x.y, wi, re));
+            im = fma(x.x, wi, fma(x.y, w.x, im));
+            idx += inc;
+            if (idx >= n) idx -= n;
+        }
+        b[L * ld + fft_pos(q * Ns * rad + k + u * Ns)] = Cx<R>::make(re, im);
+    }
+}
+
+// The NL lines of `a` (line L at a + L fft_ld(n)), already visible to the
+// block, are transformed through `b` and back; returns the buffer that holds
+// the result.  Ends with a barrier.  tw: the forward twiddles of n.
+template <typename R, bool INV>
+__device__ __forceinline__ cx_t<R>* fft_lines(cx_t<R>* a, cx_t<R>* b, const cx_t<R>* tw, int NL,
+                                              const FftPlan& p) {
+    int Ns = 1;
+    for (int s = 0; s < p.stages; ++s) {
+        const int r = p.radix[s];
+        switch (r) {
+            case 2: fft_stage<R, INV, 2>(a, b, tw, NL, p.n, Ns); break;
+            case 3: fft_stage<R, INV, 3>(a, b, tw, NL, p.n, Ns); break;
+            case 4: fft_stage<R, INV, 4>(a, b, tw, NL, p.n, Ns); break;
+            case 5: fft_stage<R, INV, 5>(a, b, tw, NL, p.n, Ns); break;
+            case 8: fft_stage<R, INV, 8>(a, b, tw, NL, p.n, Ns); break;
+            default: fft_stage_any<R, INV>(a, b, tw, NL, p.n, Ns, r); break;
+        }
+        __syncthreads();
+        Ns *= r;
+        cx_t<R>* c = a;
+        a = b;
+        b = c;
+    }
+    return a;
+}
+
+}  // namespace flb
