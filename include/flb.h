@@ -204,7 +204,7 @@ flb_status flb_mode_spectrum(flb_handle* h, void* work, double* spec, void* stre
 
 /* Power spectra of real fields: for f = 0 .. nfields - 1,
  *   spec[f V + k] += |sum_x fields[f V + x] exp(-i k.x)|^2,
- * x and k laid out as sites (x fastest), V = nx ny nz, periodic, direct DFT
+ * x and k laid out as sites (x fastest), V = nx ny nz, periodic, a DFT
  * along each axis.  Used for interface-height spectra (Sec. VI capillary
  * fluctuations, eq. capill-static).  fields, spec: device doubles, 8-byte
  * aligned, caller-owned (spec caller-zeroed; calls add to it).  work: device,

@@ -9,8 +9,12 @@
 // A line of n costs about n sum(r) complex multiply-adds instead of n^2.
 //
 // Two LDS buffers per line are alternated, one barrier per stage.  Element i
-// of a line lies at i + i / 16: the stride-8 stores of a first radix-8 stage
-// then fall into different banks.
+// of a line lies at i + i / 8: the stride-8 and stride-64 stores of radix-8
+// stages then fall into different banks.  The twiddles of a stage lie in the
+// order its lanes read them, (u, j mod Ns), behind those of the earlier stages
+// ((r - 1) Ns each, n - 1 in all): reading every n / (Ns r)-th entry of one
+// table of n put a stage's reads into one to four banks.  Direct-sum stages
+// read the table of n roots kept behind them.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -21,6 +25,7 @@ constexpr int FFT_MAX_STAGES = 12;   // 1024 = 8 8 4 4; worst case below 2^10: 7
 
 struct FftPlan {
     int n, stages;
+    int any;                     // 1: some stage is a direct sum
     int radix[FFT_MAX_STAGES];
 };
 
@@ -42,6 +47,7 @@ inline FftPlan fft_plan(int n) {
     for (int f = 3; m > 1; f += 2)
         while (m % f == 0) {
             p.radix[p.stages++] = f;
+            if (f > 5) p.any = 1;
             m /= f;
         }
     return p;
@@ -60,21 +66,39 @@ template <> struct Cx<float> {
 template <typename R> using cx_t = typename Cx<R>::T;
 
 // Position of element i of a line, and the elements a line of n takes.
-__host__ __device__ __forceinline__ int fft_pos(int i) { return i + (i >> 4); }
-__host__ __device__ __forceinline__ int fft_ld(int n) { return n + (n >> 4) + 1; }
+__host__ __device__ __forceinline__ int fft_pos(int i) { return i + (i >> 3); }
+__host__ __device__ __forceinline__ int fft_ld(int n) { return n + (n >> 3) + 1; }
+// Twiddle entries of a plan.
+__host__ __device__ __forceinline__ int fft_twiddles(const FftPlan& p) {
+    return p.any ? 2 * p.n : p.n;
+}
 
 // a / b for 0 <= a < 2^16, 1 <= b, with rb = 1.0f / b: (a + 1/2) / b is at
 // least 1 / (2 b) from an integer, beyond the rounding of the two FP32
 // operations for quotients below 2^11.
 __device__ __forceinline__ int fft_div(int a, float rb) { return (int)(((float)a + 0.5f) * rb); }
 
-// tw[j] = exp(-2 pi i j / n), evaluated in FP64 and rounded to R.
+// The twiddles of a plan, evaluated in FP64 and rounded to R: entry
+// Ns - 1 + (u - 1) Ns + k = exp(-2 pi i u k / (Ns r)) of the stage after Ns,
+// then, for direct sums, entry n + j = exp(-2 pi i j / n).  No barrier.
 template <typename R>
-__device__ __forceinline__ void twiddles(cx_t<R>* tw, int n) {
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+__device__ __forceinline__ void twiddles(cx_t<R>* tw, const FftPlan& p) {
+    for (int e = threadIdx.x; e < fft_twiddles(p); e += blockDim.x) {
+        int num = e - p.n, den = p.n;   // exp(-2 pi i num / den)
+        if (num < 0) {
+            int Ns = 1, r = 1;
+            for (int s = 0; s < p.stages; ++s) {
+                r = p.radix[s];
+                if (e < Ns * r - 1) break;
+                Ns *= r;
+            }
+            const int o = e - (Ns - 1), u = o / Ns;
+            num = (u + 1) * (o - u * Ns);
+            den = Ns * r;
+        }
         double s, c;
-        sincospi(2.0 * (double)j / (double)n, &s, &c);
-        tw[j] = Cx<R>::make((R)c, (R)-s);
+        sincospi(2.0 * (double)num / (double)den, &s, &c);
+        tw[e] = Cx<R>::make((R)c, (R)-s);
     }
 }
 
@@ -154,8 +178,9 @@ template <typename R, bool INV, int RAD>
 __device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>* __restrict__ b,
                                           const cx_t<R>* __restrict__ tw, int NL, int n, int Ns) {
     using C = cx_t<R>;
-    const int m = n / RAD, ld = fft_ld(n), ts = m / Ns;
+    const int m = n / RAD, ld = fft_ld(n);
     const float rm = 1.0f / (float)m, rN = 1.0f / (float)Ns;
+    tw += Ns - 1;
     for (int t = threadIdx.x; t < NL * m; t += blockDim.x) {
         const int L = fft_div(t, rm), j = t - L * m;
         const int q = fft_div(j, rN), k = j - q * Ns;
@@ -166,7 +191,7 @@ __device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>
         if (Ns > 1) {
 #pragma unroll
             for (int u = 1; u < RAD; ++u) {
-                C w = tw[u * k * ts];
+                C w = tw[(u - 1) * Ns + k];
                 if (INV) w.y = -w.y;
                 x[u] = cx_mul<R>(x[u], w);
             }
@@ -179,7 +204,7 @@ __device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>
     }
 }
 
-// Any radix: every output as a direct sum over its group.
+// Any radix: every output as a direct sum over its group.  tw: the n roots.
 template <typename R, bool INV>
 __device__ __forceinline__ void fft_stage_any(const cx_t<R>* __restrict__ a,
                                               cx_t<R>* __restrict__ b,
@@ -211,7 +236,7 @@ __device__ __forceinline__ void fft_stage_any(const cx_t<R>* __restrict__ a,
 
 // The NL lines of `a` (line L at a + L fft_ld(n)), already visible to the
 // block, are transformed through `b` and back; returns the buffer that holds
-// the result.  Ends with a barrier.  tw: the forward twiddles of n.
+// the result.  Ends with a barrier.  tw: the plan's twiddles.
 template <typename R, bool INV>
 __device__ __forceinline__ cx_t<R>* fft_lines(cx_t<R>* a, cx_t<R>* b, const cx_t<R>* tw, int NL,
                                               const FftPlan& p) {
@@ -224,7 +249,7 @@ __device__ __forceinline__ cx_t<R>* fft_lines(cx_t<R>* a, cx_t<R>* b, const cx_t
             case 4: fft_stage<R, INV, 4>(a, b, tw, NL, p.n, Ns); break;
             case 5: fft_stage<R, INV, 5>(a, b, tw, NL, p.n, Ns); break;
             case 8: fft_stage<R, INV, 8>(a, b, tw, NL, p.n, Ns); break;
-            default: fft_stage_any<R, INV>(a, b, tw, NL, p.n, Ns, r); break;
+            default: fft_stage_any<R, INV>(a, b, tw + p.n, NL, p.n, Ns, r); break;
         }
         __syncthreads();
         Ns *= r;

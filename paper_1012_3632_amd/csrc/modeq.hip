@@ -24,27 +24,34 @@
 // equilibrium populations are non-negative).  That pair is drawn as white
 // normals z_e, z_eps (the site's Philox normals 0 and 5), transformed, mixed
 // by the lower Cholesky factor of the block at every k, and transformed back:
-//   k_meq_noise_x      normals of one row, DFT along x         (one block per row)
-//   k_meq_filter_cols  DFT along y, Cholesky mix, inverse DFT  (CB adjacent columns
-//     / k_meq_filter_y                                          per block; one column
-//                                                               when ny is not a power of 2)
-//   k_meq_noise_ix     inverse DFT along x, real part / V      (one block per row)
+//   k_meq_noise_x   normals of a row, DFT along x
+//   k_meq_filter    DFT along y, Cholesky mix, inverse DFT (adjacent columns)
+//   k_meq_noise_ix  inverse DFT along x
+// The two white fields are real, and so are the two filtered ones (the factor
+// is real and even in k): a row carries both as the real and imaginary part
+// of one complex line, and only the half spectra 0 <= kx <= nx / 2 of e and
+// eps are kept and transformed along y.  The filtered pair is scaled to unit
+// amplitude until the last pass, so that neither field is rounded at the
+// other's size.
 // The noise does not depend on the state, so a launch of these three
-// kernels draws and filters the noise of a batch of consecutive steps
-// (blockIdx.y = step within the batch): at small lattices a single step's
-// lines are far fewer blocks than the chip has CUs.
-// Each line sits in LDS with its twiddles.  Power-of-two extents use an
-// in-place radix-2 FFT, the butterfly stages taken three per pass through LDS
-// and shared by all lines of a block: decimation in time from bit-reversed
-// input for the rows, and for the columns decimation in frequency forward
-// (bit-reversed output), the mix in that order, then decimation in time back.
-// Other extents (at most 1024) use direct sums.  Then k_meq_step applies the
-// step.  The transforms and the filtered fields are in the state's precision
-// (R = float or double; twiddles and Cholesky factors formed in FP64 and
-// rounded once).
+// kernels draws and filters the noise of a batch of consecutive steps: at
+// small lattices a single step's lines are far fewer blocks than the chip has
+// CUs.
+// Lines sit in LDS and are transformed by the staged passes of fft.h (any
+// extent up to 1024).  The transforms and the filtered fields are in the
+// state's precision (R = float or double; twiddles and Cholesky factors formed
+// in FP64 and rounded once).  Then k_meq_step applies the step.
+//
+// 1024^2 FP32, per step of a 16-step launch: rows 7.4 us (mostly the Philox
+// normals), columns 10.6 us, rows back 6.0 us; 11.6, 20.3 and 11.6 us with two
+// full spectra.  200 x 150 FP64, whole step with its noise: 11.3 us, 31 us when
+// extents that are not powers of two took n^2 direct sums.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device.h"
+#include "fft.h"
 #include "internal.h"
 #include "philox.h"
 
@@ -52,45 +59,13 @@ namespace flb {
 
 namespace {
 
-constexpr int MQ_THREADS = 256;
-constexpr int MQ_MAXK = SPECTRUM_MAX_N / MQ_THREADS;   // outputs per thread and line
+constexpr int MQ_THREADS = 1024;     // of the staged line transforms, at most
+constexpr int MQ_P2_THREADS = 256;   // of the in-place power-of-two passes
 constexpr int MQ_TX = 64, MQ_TY = 4;
-
-// Complex values of precision R in LDS and in the work buffer.
-template <typename R> struct Cx;
-template <> struct Cx<double> {
-    using T = double2;
-    static __device__ __forceinline__ T make(double re, double im) { return make_double2(re, im); }
-};
-template <> struct Cx<float> {
-    using T = float2;
-    static __device__ __forceinline__ T make(float re, float im) { return make_float2(re, im); }
-};
-template <typename R> using cx_t = typename Cx<R>::T;
-
-// X(k) = sum_j x(j) exp(-+ 2 pi i j k / n) (sign - forward, + inverse), from a
-// line in LDS and the forward twiddles tw[j] = exp(-2 pi i j / n).
-template <typename R>
-__device__ __forceinline__ cx_t<R> dft_at(const cx_t<R>* __restrict__ buf,
-                                          const cx_t<R>* __restrict__ tw, int n, int k,
-                                          bool inverse) {
-    R re = R(0), im = R(0);
-    int idx = 0;   // j k mod n
-    for (int j = 0; j < n; ++j) {
-        const cx_t<R> x = buf[j];
-        const cx_t<R> w = tw[idx];
-        const R wi = inverse ? -w.y : w.y;
-        re = fma(x.x, w.x, fma(-x.y, wi, re));
-        im = fma(x.x, wi, fma(x.y, w.x, im));
-        idx += k;
-        if (idx >= n) idx -= n;
-    }
-    return Cx<R>::make(re, im);
-}
 
 // tw[j] = exp(-2 pi i j / n), evaluated in FP64 and rounded to R.
 template <typename R>
-__device__ __forceinline__ void twiddles(cx_t<R>* tw, int n) {
+__device__ __forceinline__ void roots(cx_t<R>* tw, int n) {
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
         double s, c;
         sincospi(2.0 * (double)j / (double)n, &s, &c);
@@ -197,12 +172,6 @@ __device__ __forceinline__ void fft_lines_dit(cx_t<R>* b, const cx_t<R>* __restr
     }
 }
 
-template <typename R>
-__device__ __forceinline__ void fft2_lines(cx_t<R>* b, const cx_t<R>* __restrict__ tw, int n,
-                                           int logn, bool inverse) {
-    fft_lines_dit<R>(b, tw, 2, n, logn, inverse);
-}
-
 // (u, v) -> (u + v, (u - v) w): the decimation-in-frequency butterfly
 template <typename R>
 __device__ __forceinline__ void bfly_dif(cx_t<R>& u, cx_t<R>& v, cx_t<R> w) {
@@ -301,194 +270,169 @@ __device__ __forceinline__ void meq_chol(const ModEqArgs& a, double cx, double c
     l22 = sqrt(fmax(spp - l21 * l21, 0.0));
 }
 
-// Dynamic LDS of the noise kernels (lines and twiddles of either precision).
+// Amplitudes of the filtered e and eps noise: the square roots of the largest
+// diagonal entries of the block (at k = 0, where c2 is smallest).
+__device__ __forceinline__ void meq_scales(const ModEqArgs& a, double& se, double& sp) {
+    const double pre = 12.0 * a.rho0 * a.kT;
+    const double le = a.rate_bulk, lg = a.rate_ghost;
+    se = sqrt(fmax(pre * le * (2.0 - le) * (2.0 - 3.0 * a.cs2_0), 0.0));
+    sp = sqrt(fmax(pre * lg * (2.0 - lg) * (5.0 - 3.0 * a.cs2_0), 0.0));
+    if (!(se > 0.0)) se = 1.0;
+    if (!(sp > 0.0)) sp = 1.0;
+}
+
+// Dynamic LDS of the noise kernels: two buffers of NL lines, then the
+// twiddles (either precision).
 extern __shared__ __align__(16) unsigned char lds_mq[];
 
+// Half spectra of step b: e at W + 2 V b, eps hx ny values behind it, each
+// (y, kx), kx = 0 .. nx / 2.  A turn is NL rows of one step.
 template <typename Real>
-__global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, uint32_t step0,
+__global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan p, int NL,
+                                                            uint32_t step0, int nb,
                                                             cx_t<Real>* __restrict__ W) {
     using C = cx_t<Real>;
-    const int n = a.nx, y = blockIdx.x;
-    const size_t V = (size_t)a.nx * a.ny;
-    const uint32_t step = step0 + blockIdx.y;
-    W += (size_t)blockIdx.y * 2 * V;
-    C* tw = (C*)lds_mq;
-    C* be = tw + n;
-    C* bp = tw + 2 * n;
-    const bool fft = pow2(n);
-    const int logn = log2i(n);
-    twiddles<Real>(tw, n);
-    for (int x = threadIdx.x; x < n; x += blockDim.x) {
-        Real z[6];
-        site_normals<3, Real>((uint32_t)(x + n * y), step, 0u, 0u, a.k0, a.k1, z);
-        const int j = fft ? brev(x, logn) : x;
-        be[j] = Cx<Real>::make(z[0], Real(0));
-        bp[j] = Cx<Real>::make(z[5], Real(0));
-    }
-    __syncthreads();
-    if (fft) {
-        fft2_lines<Real>(be, tw, n, logn, false);
-        for (int k = threadIdx.x; k < n; k += blockDim.x) {
-            W[(size_t)y * n + k] = be[k];
-            W[V + (size_t)y * n + k] = bp[k];
+    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n);
+    const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * a.ny;
+    C* buf = (C*)lds_mq;
+    C* alt = buf + NL * ld;
+    C* tw = alt + NL * ld;
+    twiddles<Real>(tw, p);
+    const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx;
+    const uint32_t groups = (uint32_t)((a.ny + NL - 1) / NL);
+    for (uint32_t g = blockIdx.x; g < groups * (uint32_t)nb; g += gridDim.x) {
+        const uint32_t b = g / groups;
+        const int y0 = (int)(g - b * groups) * NL, nl = min(NL, a.ny - y0);
+        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
+            const int L = fft_div(t, rn), x = t - L * n;
+            C v = Cx<Real>::make(Real(0), Real(0));
+            if (L < nl) {
+                Real z[6];
+                site_normals<3, Real>((uint32_t)(x + n * (y0 + L)), step0 + b, 0u, 0u, a.k0, a.k1, z);
+                v = Cx<Real>::make(z[0], z[5]);
+            }
+            buf[L * ld + fft_pos(x)] = v;
         }
-        return;
-    }
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        W[(size_t)y * n + k] = dft_at<Real>(be, tw, n, k, false);
-        W[V + (size_t)y * n + k] = dft_at<Real>(bp, tw, n, k, false);
+        __syncthreads();
+        const C* z = fft_lines<Real, false>(buf, alt, tw, NL, p);
+        C* out = W + (size_t)b * 2 * V + (size_t)y0 * hx;
+        for (int t = threadIdx.x; t < nl * hx; t += blockDim.x) {
+            const int L = fft_div(t, rh), k = t - L * hx;
+            const C u = z[L * ld + fft_pos(k)], v = z[L * ld + fft_pos(k == 0 ? 0 : n - k)];
+            out[t] = Cx<Real>::make(Real(0.5) * (u.x + v.x), Real(0.5) * (u.y - v.y));
+            out[H + t] = Cx<Real>::make(Real(0.5) * (u.y + v.y), Real(0.5) * (v.x - u.x));
+        }
+        __syncthreads();   // the result is read before the next turn's loads
     }
 }
 
-template <typename Real>
-__global__ __launch_bounds__(MQ_THREADS) void k_meq_filter_y(ModEqArgs a,
-                                                             cx_t<Real>* __restrict__ W) {
+// NC adjacent columns kx of one step per block.  LDS lines: e of the columns,
+// then eps.  P2 (ny a power of two): in-place radix-2 passes, decimation in
+// frequency forward and in time back, so that position j holds wavenumber
+// brev(j) in between and no line is permuted; at 1024 they take 168 us per
+// 16 steps where the staged passes, with two buffers and more index
+// arithmetic, take 311.
+template <typename Real, bool P2>
+__global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
+    ModEqArgs a, FftPlan p, int NC, cx_t<Real>* __restrict__ W) {
     using C = cx_t<Real>;
-    // blocks of neighbouring columns (which share cache lines) go to the same
-    // XCD, so one L2 serves the line to all of them
+    // neighbouring column groups share cache lines: same XCD, one L2
     const uint32_t lin = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
-    const int n = a.ny, nx = a.nx, kx = (int)(lin % gridDim.x);
-    const size_t V = (size_t)a.nx * a.ny;
-    W += (size_t)(lin / gridDim.x) * 2 * V;
-    C* tw = (C*)lds_mq;
-    C* be = tw + n;
-    C* bp = tw + 2 * n;
-    const bool fft = pow2(n);
-    const int logn = log2i(n);
-    twiddles<Real>(tw, n);
-    for (int y = threadIdx.x; y < n; y += blockDim.x) {
-        const int j = fft ? brev(y, logn) : y;
-        be[j] = W[(size_t)y * nx + kx];
-        bp[j] = W[V + (size_t)y * nx + kx];
+    const int n = a.ny, hx = a.nx / 2 + 1, ld = P2 ? n : fft_ld(n), logn = log2i(n);
+    const uint32_t step = lin / gridDim.x;
+    const int c0 = (int)(lin - step * gridDim.x) * NC, nc = min(NC, hx - c0);
+    const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * n;
+    C* base = W + (size_t)step * 2 * V + c0;
+    C* buf = (C*)lds_mq;
+    C* alt = buf + 2 * NC * ld;
+    C* tw = P2 ? alt : alt + 2 * NC * ld;
+    if constexpr (P2) roots<Real>(tw, n);
+    else twiddles<Real>(tw, p);
+    const float rc = 1.0f / (float)NC, rn = 1.0f / (float)nc;
+    auto pos = [](int i) { return P2 ? i : fft_pos(i); };
+    for (int t = threadIdx.x; t < NC * n; t += blockDim.x) {
+        const int j = fft_div(t, rc), c = t - j * NC;
+        C e = Cx<Real>::make(Real(0), Real(0)), q = e;
+        if (c < nc) {
+            e = base[(size_t)j * hx + c];
+            q = base[H + (size_t)j * hx + c];
+        }
+        buf[c * ld + pos(j)] = e;
+        buf[(NC + c) * ld + pos(j)] = q;
     }
     __syncthreads();
-    if (fft) fft2_lines<Real>(be, tw, n, logn, false);
-    double sx, cx;
-    sincospi(2.0 * (double)kx / (double)nx, &sx, &cx);
-    C oe[MQ_MAXK], op[MQ_MAXK];
-#pragma unroll
-    for (int r = 0; r < MQ_MAXK; ++r) {
-        const int ky = threadIdx.x + r * MQ_THREADS;
-        if (ky < n) {
-            const C ze = fft ? be[ky] : dft_at<Real>(be, tw, n, ky, false);
-            const C zp = fft ? bp[ky] : dft_at<Real>(bp, tw, n, ky, false);
-            double d11, d21, d22;
-            meq_chol(a, cx, (double)tw[ky].x, d11, d21, d22);
-            const Real l11 = (Real)d11, l21 = (Real)d21, l22 = (Real)d22;
-            oe[r] = Cx<Real>::make(l11 * ze.x, l11 * ze.y);
-            op[r] = Cx<Real>::make(l21 * ze.x + l22 * zp.x, l21 * ze.y + l22 * zp.y);
-        }
-    }
-    __syncthreads();   // every forward value has been read from be, bp
-#pragma unroll
-    for (int r = 0; r < MQ_MAXK; ++r) {
-        const int ky = threadIdx.x + r * MQ_THREADS;
-        if (ky < n) {
-            const int j = fft ? brev(ky, logn) : ky;
-            be[j] = oe[r];
-            bp[j] = op[r];
-        }
+    C* z = buf;
+    if constexpr (P2) fft_lines_dif<Real>(z, tw, 2 * NC, n, logn);
+    else z = fft_lines<Real, false>(buf, alt, tw, 2 * NC, p);
+    double se, sp;
+    meq_scales(a, se, sp);
+    for (int t = threadIdx.x; t < nc * n; t += blockDim.x) {
+        const int j = fft_div(t, rn), c = t - j * nc;
+        double sn, cx, cy, d11, d21, d22;
+        sincospi(2.0 * (double)(c0 + c) / (double)a.nx, &sn, &cx);
+        if constexpr (P2) cy = (double)tw[brev(j, logn)].x;
+        else sincospi(2.0 * (double)j / (double)n, &sn, &cy);
+        meq_chol(a, cx, cy, d11, d21, d22);
+        const Real l11 = (Real)(d11 / se), l21 = (Real)(d21 / sp), l22 = (Real)(d22 / sp);
+        C* pe = z + c * ld + pos(j);
+        C* pq = pe + NC * ld;
+        const C e = *pe, q = *pq;
+        *pe = Cx<Real>::make(l11 * e.x, l11 * e.y);
+        *pq = Cx<Real>::make(l21 * e.x + l22 * q.x, l21 * e.y + l22 * q.y);
     }
     __syncthreads();
-    if (fft) {
-        fft2_lines<Real>(be, tw, n, logn, true);
-        for (int y = threadIdx.x; y < n; y += blockDim.x) {
-            W[(size_t)y * nx + kx] = be[y];
-            W[V + (size_t)y * nx + kx] = bp[y];
-        }
-        return;
-    }
-    for (int y = threadIdx.x; y < n; y += blockDim.x) {
-        W[(size_t)y * nx + kx] = dft_at<Real>(be, tw, n, y, true);
-        W[V + (size_t)y * nx + kx] = dft_at<Real>(bp, tw, n, y, true);
+    if constexpr (P2) fft_lines_dit<Real>(z, tw, 2 * NC, n, logn, true);
+    else z = fft_lines<Real, true>(z, z == buf ? alt : buf, tw, 2 * NC, p);
+    for (int t = threadIdx.x; t < nc * n; t += blockDim.x) {
+        const int j = fft_div(t, rn), c = t - j * nc;
+        base[(size_t)j * hx + c] = z[c * ld + pos(j)];
+        base[H + (size_t)j * hx + c] = z[(NC + c) * ld + pos(j)];
     }
 }
 
-// Power-of-two ny: CB adjacent columns per block (loads and stores of a row
-// touch CB consecutive values).  The forward transforms leave the spectra in
-// bit-reversed order (decimation in frequency), the Cholesky mix is
-// pointwise there (position j holds wavenumber ky = brev(j)), and the inverse
-// transforms take that order back to natural order (decimation in time), so
-// no permutation step is needed.  Lines in LDS: e of columns 0 .. CB-1, then
-// eps.  nx must be a multiple of CB.
-template <typename Real, int CB>
-__global__ __launch_bounds__(MQ_THREADS) void k_meq_filter_cols(ModEqArgs a,
-                                                                cx_t<Real>* __restrict__ W) {
-    using C = cx_t<Real>;
-    // blocks of neighbouring column groups (which share cache lines) go to
-    // the same XCD, so one L2 serves the line to all of them
-    const uint32_t lin = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
-    const int n = a.ny, nx = a.nx, kx0 = (int)(lin % gridDim.x) * CB;
-    const int logn = log2i(n);
-    const size_t V = (size_t)a.nx * a.ny;
-    W += (size_t)(lin / gridDim.x) * 2 * V;
-    C* tw = (C*)lds_mq;
-    C* b = tw + n;
-    twiddles<Real>(tw, n);
-    for (int idx = threadIdx.x; idx < CB * n; idx += blockDim.x) {
-        const int y = idx / CB, c = idx - y * CB;
-        b[c * n + y] = W[(size_t)y * nx + kx0 + c];
-        b[(CB + c) * n + y] = W[V + (size_t)y * nx + kx0 + c];
-    }
-    __syncthreads();
-    fft_lines_dif<Real>(b, tw, 2 * CB, n, logn);
-    double cxs[CB];
-#pragma unroll
-    for (int c = 0; c < CB; ++c) {
-        double sx;
-        sincospi(2.0 * (double)(kx0 + c) / (double)nx, &sx, &cxs[c]);
-    }
-    for (int idx = threadIdx.x; idx < CB * n; idx += blockDim.x) {
-        const int c = idx >> logn, j = idx & (n - 1);
-        double d11, d21, d22;
-        meq_chol(a, cxs[c], (double)tw[brev(j, logn)].x, d11, d21, d22);
-        const Real l11 = (Real)d11, l21 = (Real)d21, l22 = (Real)d22;
-        const C ze = b[c * n + j], zp = b[(CB + c) * n + j];
-        b[c * n + j] = Cx<Real>::make(l11 * ze.x, l11 * ze.y);
-        b[(CB + c) * n + j] = Cx<Real>::make(l21 * ze.x + l22 * zp.x, l21 * ze.y + l22 * zp.y);
-    }
-    __syncthreads();
-    fft_lines_dit<Real>(b, tw, 2 * CB, n, logn, true);
-    for (int idx = threadIdx.x; idx < CB * n; idx += blockDim.x) {
-        const int y = idx / CB, c = idx - y * CB;
-        W[(size_t)y * nx + kx0 + c] = b[c * n + y];
-        W[V + (size_t)y * nx + kx0 + c] = b[(CB + c) * n + y];
-    }
-}
-
+// X(k) = E(k) + i P(k), k = 0 .. nx - 1, from the half spectra (E(n - k) =
+// conj E(k)); its inverse transform is xi_e + i xi_eps.
 template <typename Real>
-__global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_ix(ModEqArgs a,
+__global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_ix(ModEqArgs a, FftPlan p, int NL, int nb,
                                                              const cx_t<Real>* __restrict__ W,
                                                              Real* __restrict__ xi) {
     using C = cx_t<Real>;
-    const int n = a.nx, y = blockIdx.x;
-    const size_t V = (size_t)a.nx * a.ny;
-    const Real inv_v = (Real)(1.0 / (double)V);
-    W += (size_t)blockIdx.y * 2 * V;
-    xi += (size_t)blockIdx.y * 2 * V;
-    C* tw = (C*)lds_mq;
-    C* be = tw + n;
-    C* bp = tw + 2 * n;
-    const bool fft = pow2(n);
-    const int logn = log2i(n);
-    twiddles<Real>(tw, n);
-    for (int x = threadIdx.x; x < n; x += blockDim.x) {
-        const int j = fft ? brev(x, logn) : x;
-        be[j] = W[(size_t)y * n + x];
-        bp[j] = W[V + (size_t)y * n + x];
-    }
-    __syncthreads();
-    if (fft) {
-        fft2_lines<Real>(be, tw, n, logn, true);
-        for (int x = threadIdx.x; x < n; x += blockDim.x) {
-            xi[(size_t)y * n + x] = be[x].x * inv_v;
-            xi[V + (size_t)y * n + x] = bp[x].x * inv_v;
+    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n);
+    const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * a.ny;
+    C* buf = (C*)lds_mq;
+    C* alt = buf + NL * ld;
+    C* tw = alt + NL * ld;
+    twiddles<Real>(tw, p);
+    double se, sp;
+    meq_scales(a, se, sp);
+    const Real fe = (Real)(se / (double)V), fp = (Real)(sp / (double)V);
+    const float rn = 1.0f / (float)n;
+    const uint32_t groups = (uint32_t)((a.ny + NL - 1) / NL);
+    for (uint32_t g = blockIdx.x; g < groups * (uint32_t)nb; g += gridDim.x) {
+        const uint32_t b = g / groups;
+        const int y0 = (int)(g - b * groups) * NL, nl = min(NL, a.ny - y0);
+        const C* in = W + (size_t)b * 2 * V + (size_t)y0 * hx;
+        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
+            const int L = fft_div(t, rn), k = t - L * n;
+            C v = Cx<Real>::make(Real(0), Real(0));
+            if (L < nl) {
+                const int h = k < hx ? k : n - k;
+                const C e = in[L * hx + h], q = in[H + L * hx + h];
+                v = k < hx ? Cx<Real>::make(e.x - q.y, e.y + q.x)
+                           : Cx<Real>::make(e.x + q.y, q.x - e.y);
+            }
+            buf[L * ld + fft_pos(k)] = v;
         }
-        return;
-    }
-    for (int x = threadIdx.x; x < n; x += blockDim.x) {
-        xi[(size_t)y * n + x] = dft_at<Real>(be, tw, n, x, true).x * inv_v;
-        xi[V + (size_t)y * n + x] = dft_at<Real>(bp, tw, n, x, true).x * inv_v;
+        __syncthreads();
+        const C* z = fft_lines<Real, true>(buf, alt, tw, NL, p);
+        Real* out = xi + (size_t)b * 2 * V + (size_t)y0 * n;
+        for (int t = threadIdx.x; t < nl * n; t += blockDim.x) {
+            const int L = fft_div(t, rn), x = t - L * n;
+            const C v = z[L * ld + fft_pos(x)];
+            out[t] = v.x * fe;
+            out[V + t] = v.y * fp;
+        }
+        __syncthreads();
     }
 }
 
@@ -634,30 +578,20 @@ size_t modeq_work_bytes(int nx, int ny, int prec) {
 
 namespace {
 
-// Choice of CB for k_meq_filter_cols: the widest of 4, 2 that divides nx and
-// whose lines fit the block's LDS, else 1.
-int filter_cols_cb(const ModEqArgs& a, size_t csize) {
-    int dev = 0, lmax = 65536;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&lmax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    const size_t per = (size_t)a.ny * csize;
-    // two columns per block measured fastest at 1024^2 (323 us per 16-step
-    // launch against 385 for four and 337 for one): twice the resident
-    // blocks of four for half the LDS
-    for (int c : {2, 4})
-        if (a.nx % c == 0 && (1 + 2 * (size_t)c) * per <= (size_t)lmax) return c;
-    return 1;
+// Threads for `lines` lines of n: one per four elements.
+int mq_block(int lines, int n) {
+    return std::min(MQ_THREADS, std::max(64, (lines * n / 4 + 63) / 64 * 64));
 }
 
-template <typename Real, int CB>
-hipError_t launch_filter_cols(const ModEqArgs& a, int nb, cx_t<Real>* W, hipStream_t st) {
-    const size_t lc = (1 + 2 * (size_t)CB) * (size_t)a.ny * sizeof(cx_t<Real>);
-    hipError_t e = hipFuncSetAttribute((const void*)k_meq_filter_cols<Real, CB>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lc);
-    if (e != hipSuccess) return e;
-    const dim3 gc((unsigned)(a.nx / CB), (unsigned)nb);
-    hipLaunchKernelGGL((k_meq_filter_cols<Real, CB>), gc, dim3(MQ_THREADS), lc, st, a, W);
-    return hipSuccess;
+size_t mq_lds(int lines, const FftPlan& p, size_t csize) {
+    return (2 * (size_t)lines * fft_ld(p.n) + fft_twiddles(p)) * csize;
+}
+
+template <typename K>
+hipError_t mq_lds_limit(K kernel, size_t lds) {
+    if (lds <= 65536) return hipSuccess;
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds);
 }
 
 template <typename Real>
@@ -665,21 +599,39 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
                           hipStream_t st) {
     using C = cx_t<Real>;
     C* W = (C*)Wv;
-    const size_t lx = 3 * (size_t)a.nx * sizeof(C), ly = 3 * (size_t)a.ny * sizeof(C);
-    const dim3 gx((unsigned)a.ny, (unsigned)nb), gy((unsigned)a.nx, (unsigned)nb);
-    hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, dim3(MQ_THREADS), lx, st, a, step0, W);
-    if ((a.ny & (a.ny - 1)) == 0) {
-        hipError_t e = hipSuccess;
-        switch (filter_cols_cb(a, sizeof(C))) {
-            case 4: e = launch_filter_cols<Real, 4>(a, nb, W, st); break;
-            case 2: e = launch_filter_cols<Real, 2>(a, nb, W, st); break;
-            default: e = launch_filter_cols<Real, 1>(a, nb, W, st); break;
-        }
+    const FftPlan px = fft_plan(a.nx), py = fft_plan(a.ny);
+    // rows per block: up to 2048 elements (512 threads) and 48 KB, fewer
+    // where that leaves less than 1024 turns
+    int NL = 16;
+    while (NL > 1 && (NL * a.nx > 2048 || mq_lds(NL, px, sizeof(C)) > 49152 ||
+                      (size_t)a.ny * nb < 1024 * (size_t)NL))
+        NL /= 2;
+    const size_t lx = mq_lds(NL, px, sizeof(C));
+    const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
+    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, a.nx));
+    hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, bx, lx, st, a, px, NL, step0, nb, W);
+    // columns per block: two for the in-place passes (four columns halve the
+    // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
+    // for the staged ones; fewer where that leaves less than 512 blocks
+    const int hx = a.nx / 2 + 1;
+    const bool p2 = (a.ny & (a.ny - 1)) == 0;
+    int NC = p2 ? 2 : 4;
+    while (NC > 1 && ((!p2 && 2 * NC * a.ny > 4096) || hx * nb < 512 * NC)) NC /= 2;
+    const dim3 gy((unsigned)((hx + NC - 1) / NC), (unsigned)nb);
+    if (p2) {
+        const size_t ly = (2 * (size_t)NC + 1) * a.ny * sizeof(C);
+        hipError_t e = mq_lds_limit(k_meq_filter<Real, true>, ly);
         if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_meq_filter<Real, true>), gy, dim3(MQ_P2_THREADS), ly, st, a, py, NC,
+                           W);
     } else {
-        hipLaunchKernelGGL(k_meq_filter_y<Real>, gy, dim3(MQ_THREADS), ly, st, a, W);
+        const size_t ly = mq_lds(2 * NC, py, sizeof(C));
+        hipError_t e = mq_lds_limit(k_meq_filter<Real, false>, ly);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, a.ny)), ly, st, a,
+                           py, NC, W);
     }
-    hipLaunchKernelGGL(k_meq_noise_ix<Real>, gx, dim3(MQ_THREADS), lx, st, a, (const C*)W, xi);
+    hipLaunchKernelGGL(k_meq_noise_ix<Real>, gx, bx, lx, st, a, px, NL, nb, (const C*)W, xi);
     return hipGetLastError();
 }
 

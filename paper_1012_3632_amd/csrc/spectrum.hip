@@ -52,7 +52,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
-    twiddles<double>(tw, n);
+    twiddles<double>(tw, p);
     const uint32_t per = (rows + 1) / 2;   // lines per field
     const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx, rp = 1.0f / (float)per;
     for (size_t l0 = (size_t)blockIdx.x * NL; l0 < nlines; l0 += (size_t)gridDim.x * NL) {
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_cols(double2* __restrict__ 
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
-    twiddles<double>(tw, n);
+    twiddles<double>(tw, p);
     const float rl = 1.0f / (float)NL;
     for (size_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
         const size_t o = g / groups;
@@ -235,16 +235,16 @@ namespace {
 
 // Lines per block of n elements, of `lines` adjacent ones: at most 16 (256
 // consecutive bytes of a row) and as many as keep two buffers and the
-// twiddles within 80 KB, two blocks per CU, but at least four, so that
-// adjacent lines fill 64 bytes (n = 1024: 152 KB of the CU's 160 KB); then
-// the same number of groups with equal shares (65 lines: five groups of 13).
+// twiddles within 80 KB, two blocks per CU, but four, so that adjacent lines
+// fill 64 bytes, up to 128 KB (n above 800: two); then the same number of groups with equal shares (65 lines: five groups of 13).
 // At 128 x 96 x 80 the z pass took 83 us with this limit, 95-102 with 40 KB.
 // Where that would give fewer than 512 blocks (total lines), fewer lines, so
 // that a small lattice still spreads over the chip.
-int fft_lines_per_block(int n, size_t lines, size_t total, size_t* lds) {
-    const size_t per = 2 * (size_t)fft_ld(n) * sizeof(double2), tw = (size_t)n * sizeof(double2);
+int fft_lines_per_block(const FftPlan& p, size_t lines, size_t total, size_t* lds) {
+    const size_t per = 2 * (size_t)fft_ld(p.n) * sizeof(double2);
+    const size_t tw = fft_twiddles(p) * sizeof(double2);
     size_t NL = 16;
-    while (NL > 4 && NL * per + tw > 81920) NL /= 2;
+    while (NL > 2 && NL * per + tw > (NL > 4 ? 81920 : 131072)) NL /= 2;
     NL = std::min(NL, std::max<size_t>(2, total / 512));
     const size_t groups = (lines + NL - 1) / NL;
     NL = (lines + groups - 1) / groups;
@@ -278,7 +278,7 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         const FftPlan p = fft_plan(nx);
         const uint32_t rows = (uint32_t)((size_t)ny * nz);
         const size_t nlines = (size_t)q * ((rows + 1) / 2);
-        const int NL = fft_lines_per_block(nx, nlines, nlines, &lds);
+        const int NL = fft_lines_per_block(p, nlines, nlines, &lds);
         const size_t blocks = (nlines + NL - 1) / NL;
         hipError_t e = fft_lds((const void*)k_fft_rows, lds);
         if (e != hipSuccess) return e;
@@ -292,7 +292,7 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         const FftPlan p = fft_plan(n);
         const size_t inner = axis == 1 ? hx : hx * ny, outer = inner * n;
         const size_t sets = axis == 1 ? (size_t)q * nz : (size_t)q;
-        const int NL = fft_lines_per_block(n, inner, inner * sets, &lds);
+        const int NL = fft_lines_per_block(p, inner, inner * sets, &lds);
         const uint32_t groups = (uint32_t)((inner + NL - 1) / NL);
         const size_t ngroups = groups * sets;
         hipError_t e = fft_lds((const void*)k_fft_cols, lds);

@@ -37,3 +37,37 @@ def test_field_spectrum_every_radix(shape):
     terms = 2 + sum(_radix_sum(n) for n in shape[1:])
     tol = 12 * np.finfo(float).eps * terms * ref.max()
     assert np.abs(spec.cpu().numpy() - start - ref).max() <= tol
+
+
+# rows and columns that do not divide a block's share, every radix, primes, and
+# a power of two along one axis only (the columns' in-place passes)
+NOISE = [(17, 40, {}), (96, 101, {}), (60, 1024, {}), (1024, 77, {}), (7, 512, {}), (300, 210, {}),
+         # e noise 300 times weaker than eps
+         (64, 48, dict(cs2_0=1.0 / 3.0, kappa=0.0, rate_bulk=1.99999, rate_ghost=1.0)),
+         (45, 64, dict(cs2_0=1.0 / 3.0, kappa=0.0, rate_bulk=1.99999, rate_ghost=1.0))]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,ny,kw", NOISE)
+def test_modeq_noise_every_split(nx, ny, kw, prec):
+    from helpers import F32_TOL, F64_TOL, rel_err
+    from oracle import modeq as OM
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    d = dict(dict(rho0=1.0, kT=1e-5, cs2_0=0.265 ** 2, kappa=0.08, rate_bulk=1.2, rate_shear=1.6,
+                  rate_ghost=0.9, seed=21, nx=nx, ny=ny), **kw)
+    xi = ModEq(ModEqParams(precision=prec, **d)).noise(3).cpu().numpy()
+    ref = OM.noise(3, OM.ModEqParams(**d))
+    for got, want in ((xi[0], ref[0]), (xi[1], ref[5])):   # each against its own size
+        assert rel_err(got, want) < (F64_TOL if prec == "fp64" else F32_TOL)
+
+
+@pytest.mark.parametrize("nx,ny", [(101, 96), (256, 64), (33, 512)])
+def test_modeq_batches_same_bits(nx, ny):
+    """The rows and columns a block takes depend on the steps drawn together;
+    the noise does not."""
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    p = ModEqParams(nx=nx, ny=ny, precision="fp32", kT=1e-5, cs2_0=0.265 ** 2, kappa=0.08, seed=4)
+    a, b = ModEq(p, batch=1), ModEq(p, batch=16)
+    a.step(18)
+    b.step(18)
+    assert torch.equal(a.f, b.f)
