@@ -495,6 +495,12 @@ flb_status flb_batch_destroy(flb_batch* b);
  * before and restored after; the call synchronizes the stream.
  * Until then a handle uses shape 0, except D2Q9 force steps, which use
  * shape 4 (32 x 8, forming its own density tile).
+ * Small D2Q9 lattices (at most 2^18 sites in FP32, less in FP64 and with
+ * statistics) take two to four steps per launch, with the bits of as many
+ * ordinary steps in populations and noise (statistics are summed in another
+ * order); flb_autotune times that too and keeps it where it is the fastest,
+ * and the shapes above then serve the steps left over.  flb_set_launch turns
+ * it off.
  * flb_set_launch sets every shape to `config` (an in-place shape then serves
  * pairs and, as an ordinary kernel of its tile, lone steps);
  * flb_launch_configs writes the number of shapes and current[3] (plain, with

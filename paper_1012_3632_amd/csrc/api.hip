@@ -141,6 +141,8 @@ struct flb_handle {
     int cfg;                // launch shape of steps without statistics
     int cfg_stats;          // launch shape of steps that accumulate statistics
     int pair_cfg;           // in-place shape for pairs of steps, or -1
+    bool multi[2];          // several steps per launch where multi_steps says so, for
+                            // calls without and with statistics
     int64_t check_every;    // > 0: flb_step reads the non-finite flag every this many steps
     // captured steps, one graph per current buffer (index cur_a): kernel
     // arguments hold the buffer pointers, so a replay must start from the
@@ -212,7 +214,28 @@ flb_status run_steps(flb_handle* h, int64_t nsteps, int32_t stride, bool graph_m
     bool drho_ready = false;   // a call starts with a density pass
     const unsigned long long* dev = graph_mode ? h->step_dev : nullptr;
     const unsigned long long base = graph_mode ? 0ull : (unsigned long long)h->step;
+    // groups of T steps in one launch first; a captured graph must end in the
+    // buffer it began in, so its number of swaps (one per group or step) is even
+    const bool stats = stride > 0;
+    const int T = h->multi[stats] ? multi_steps(h->spec, stats, h->slots) : 0;
+    int64_t groups = T > 0 ? nsteps / T : 0;
+    if (graph_mode && groups > 0 && ((groups + nsteps - groups * T) & 1)) --groups;
     for (int64_t k = 0; k < nsteps;) {
+        if (groups > 0) {
+            MultiArgs a{};
+            a.out[T - 1] = h->other();
+            for (int j = 0; j < T; ++j) {
+                const bool on = stride > 0 && ((k0 + k + j + 1) % stride) == 0;
+                a.mask |= (uint32_t)on << j;
+                ns += on;
+            }
+            HIP_TRY(launch_multi(h->spec, stats, h->slots, h->cur(), a, dev,
+                                 base + (unsigned long long)k, h->stats, st));
+            h->cur_a = !h->cur_a;
+            k += T;
+            --groups;
+            continue;
+        }
         const bool sample = stride > 0 && ((k0 + k + 1) % stride) == 0;
         if (h->pair_cfg >= 0 && k + 1 < nsteps) {
             // two steps in place on the current buffer (no swap)
@@ -325,6 +348,7 @@ flb_status flb_init(const flb_params* p, void* f_a, void* f_b, void* scratch, vo
     // tile (no density pass); every other kind to shape 0
     h->cfg = h->cfg_stats = (h->spec.force && h->spec.lat == 0) ? 4 : 0;
     h->pair_cfg = -1;
+    h->multi[0] = h->multi[1] = true;
     h->graph[0] = h->graph[1] = nullptr;
     h->gexec[0] = h->gexec[1] = nullptr;
     size_t drho_off, part_off, adj_off, gp_off, total;
@@ -717,6 +741,21 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
                 best_pair = cands[i];
             }
     }
+    // several steps per launch against the fastest of the others
+    bool multi[2] = {false, false};
+    for (int mode = 0; mode < 2 && e == hipSuccess; ++mode) {
+        const int T = multi_steps(h->spec, mode == 1, h->slots);
+        if (T == 0) continue;
+        float ms = 0.f;
+        e = timed([&](int k) {
+            MultiArgs a{};
+            a.out[T - 1] = (k & 1) ? A : B;
+            a.mask = mode ? (1u << T) - 1u : 0u;
+            return launch_multi(h->spec, mode == 1, h->slots, (k & 1) ? B : A, a, nullptr, h->step,
+                                h->stats, st);
+        }, T, &ms);
+        multi[mode] = ms < std::min(bt[mode], pair_ms);
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     // restore the state and the sums even after a failed trial
@@ -728,6 +767,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     if (e != hipSuccess) return fail(FLB_ERR_HIP, "autotune: %s", hipGetErrorString(e));
     h->cfg = bi[0];
     h->cfg_stats = bi[1];
+    for (int m = 0; m < 2; ++m) h->multi[m] = multi[m];
     // pairs are used when they beat ordinary steps with statistics
     h->pair_cfg = (best_pair >= 0 && pair_ms < bt[1]) ? best_pair : -1;
     for (int m = 0; m < 2; ++m) {
@@ -744,6 +784,7 @@ flb_status flb_set_launch(flb_handle* h, int32_t config) {
     if (!h) return fail(FLB_ERR_INVALID_ARG, "handle is NULL");
     if (config < 0 || config >= n_configs(h->spec.lat, h->spec.force))
         return fail(FLB_ERR_INVALID_ARG, "launch config %d out of range", config);
+    h->multi[0] = h->multi[1] = false;   // an explicit shape: one launch per step
     if (config_in_place(h->spec, config)) {
         h->pair_cfg = config;
         h->cfg = h->cfg_stats = config;   // a lone step runs the ordinary kernel of this tile
@@ -842,6 +883,28 @@ struct SegWork {
 // Recompute S_{k0+1} .. S_{k0+k-1} (and every state's density) with the forward kernels.
 flb_status seg_recompute(const SegWork& sw, uint64_t k0, hipStream_t st) {
     flb_handle* h = sw.h;
+    const int T = h->multi[0] && h->spec.force ? multi_steps(h->spec, false, h->slots) : 0;
+    if (T > 0) {
+        // T recomputed steps per launch, each writing the state it ends in and
+        // the density it starts from; the last state's density is a pass
+        size_t j = 1;
+        for (; j + T - 1 < sw.k; j += T) {
+            MultiArgs a{};
+            for (int t = 0; t < T; ++t) {
+                a.out[t] = (void*)sw.state(j + t);
+                a.rho[t] = sw.density(j - 1 + t);
+            }
+            HIP_TRY(launch_multi(h->spec, false, h->slots, sw.state(j - 1), a, nullptr,
+                                 (unsigned long long)(k0 + j - 1), nullptr, st));
+        }
+        const int cfg = config_fused(h->spec, h->cfg) ? h->cfg : 4;
+        for (; j < sw.k; ++j)
+            HIP_TRY(launch_step(h->spec, cfg, sw.state(j - 1), (void*)sw.state(j), nullptr, nullptr,
+                                (unsigned long long)(k0 + j - 1), nullptr, st,
+                                (void*)sw.density(j - 1)));
+        HIP_TRY(launch_density(h->spec, sw.state(sw.k - 1), sw.density(sw.k - 1), st));
+        return FLB_OK;
+    }
     if (h->spec.force && config_fused(h->spec, h->cfg)) {
         // the step forms its input's density itself and writes it out, so a
         // recomputed step is one launch; the last state's density is a pass

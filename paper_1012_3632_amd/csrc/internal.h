@@ -91,6 +91,23 @@ bool config_fused(const StepSpec& s, int cfg);
 hipError_t launch_step_in_place(const StepSpec& s, int cfg, int phase, void* f,
                                 const unsigned long long* step_dev, unsigned long long step_host,
                                 double* partial, hipStream_t st);
+// Several D2Q9 steps in one launch (multistep.h).  multi_steps: how many, or
+// 0 where ordinary steps are the better choice; stats: some step may be
+// sampled, slots: the statistics slots the caller has.  launch_multi (the same
+// stats and slots) takes fin through that many steps: out[k] receives the
+// state after step k (null but for the last: not wanted), rho[k] the density
+// step k starts from (null: not wanted), bit k of mask samples step k into
+// partial.
+constexpr int MULTI_MAX = 4;
+struct MultiArgs {
+    void* out[MULTI_MAX];
+    void* rho[MULTI_MAX];
+    uint32_t mask;
+};
+int multi_steps(const StepSpec& s, bool stats, uint32_t slots);
+hipError_t launch_multi(const StepSpec& s, bool stats, uint32_t slots, const void* fin,
+                        const MultiArgs& a, const unsigned long long* step_dev,
+                        unsigned long long step_host, double* partial, hipStream_t st);
 hipError_t launch_fields(const StepSpec& s, const void* fin, const void* drho, void* out,
                          hipStream_t st);
 // All Q mode densities of fin after streaming (FP64, out[a V + s]); momentum

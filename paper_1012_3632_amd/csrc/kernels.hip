@@ -19,6 +19,7 @@
 
 #include "device.h"
 #include "internal.h"
+#include "multistep.h"
 
 namespace flb {
 
@@ -1127,6 +1128,79 @@ hipError_t launch_step(const StepSpec& s, int cfg, const void* fin, void* fout, 
     else if (s.prec == 0) step_dispatch<1, float>(s, cfg, fin, fout, drho, si, partial, st, rho_out, rho_part);
     else step_dispatch<1, double>(s, cfg, fin, fout, drho, si, partial, st, rho_out, rho_part);
     return hipGetLastError();
+}
+
+template <typename Real, bool FORCE, int T, int TX, int TY>
+static void multi_tile(const StepSpec& s, const void* fin, const MultiArgs& a, StepIndex si,
+                       double* partial, hipStream_t st) {
+    const Geom g = make_geom(s, TileShape{TX, TY, 1, 1, 0, 0, 0});
+    const dim3 grid(g.nblocks), block(MultiTile<FORCE, T, TX, TY>::NT);
+    const CollideParams<Real> P = collide_params<Real>(s);
+    const ForceParams<Real> fp = force_params<Real>(s);
+    MultiOut<Real> o{};
+    for (int k = 0; k < T; ++k) {
+        o.out[k] = (Real*)a.out[k];
+        o.rho[k] = (Real*)a.rho[k];
+    }
+    o.mask = a.mask;
+    if (a.mask)
+        hipLaunchKernelGGL((k_multi<Real, FORCE, true, T, TX, TY>), grid, block, 0, st,
+                           (const Real*)fin, g, P, fp, si, partial, o);
+    else
+        hipLaunchKernelGGL((k_multi<Real, FORCE, false, T, TX, TY>), grid, block, 0, st,
+                           (const Real*)fin, g, P, fp, si, partial, o);
+}
+
+// Tile edge (0: ordinary steps) and steps per launch.  Measured, us per step
+// in a captured graph, ordinary -> here: landau FP32 128^2 4.40 -> 2.78 (8, T
+// 3; 16, T 2: 3.22), 256^2 4.76 -> 3.39 (16; 8: 4.34), 512 x 256 5.54 -> 4.52,
+// 512^2 7.44 -> 6.80; with statistics 512 x 256 6.03 -> 5.22, 512^2 8.18 ->
+// 8.68; FP64 with statistics 256^2 6.89 -> 5.52, 512 x 256 8.50 -> 9.75.  Ideal
+// FP32 128^2 2.73 -> 1.82, 512^2 4.97 -> 4.59; FP64 with statistics 32^2 4.64
+// -> 2.67, 256^2 4.72 -> 3.52.  So small tiles while they leave a CU one
+// block, larger ones (less halo) up to 2^18 tiled sites, half of that for
+// each of FP64 and statistics, which add registers, LDS and operations.
+static int multi_shape(const StepSpec& s, bool stats, uint32_t slots, int* T) {
+    *T = 0;
+    if (s.lat != 0) return 0;
+    const size_t limit = (size_t)262144 >> ((s.prec ? 1 : 0) + (stats ? 1 : 0));
+    for (int t : {8, 16}) {
+        const size_t nb = (size_t)((s.nx + t - 1) / t) * ((s.ny + t - 1) / t);
+        if (nb * t * t > (t == 8 ? (size_t)16384 : limit)) continue;
+        if (stats && nb > slots) continue;   // a statistics slot per block
+        *T = !s.force ? 4 : (t == 8 && s.prec == 0 ? 3 : 2);
+        return t;
+    }
+    return 0;
+}
+
+int multi_steps(const StepSpec& s, bool stats, uint32_t slots) {
+    int T;
+    return multi_shape(s, stats, slots, &T) ? T : 0;
+}
+
+template <typename Real>
+static hipError_t multi_dispatch(const StepSpec& s, int tile, int T, const void* fin,
+                                 const MultiArgs& a, StepIndex si, double* partial,
+                                 hipStream_t st) {
+    constexpr int T8 = sizeof(Real) == 4 ? 3 : 2;   // force, small tiles
+    if (!s.force && T == 4 && tile == 8) multi_tile<Real, false, 4, 8, 8>(s, fin, a, si, partial, st);
+    else if (!s.force && T == 4) multi_tile<Real, false, 4, 16, 16>(s, fin, a, si, partial, st);
+    else if (s.force && T == T8 && tile == 8) multi_tile<Real, true, T8, 8, 8>(s, fin, a, si, partial, st);
+    else if (s.force && T == 2 && tile == 16) multi_tile<Real, true, 2, 16, 16>(s, fin, a, si, partial, st);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_multi(const StepSpec& s, bool stats, uint32_t slots, const void* fin,
+                        const MultiArgs& a, const unsigned long long* step_dev,
+                        unsigned long long step_host, double* partial, hipStream_t st) {
+    int T;
+    const int tile = multi_shape(s, stats, slots, &T);
+    if (!tile || (a.mask && !stats)) return hipErrorInvalidValue;
+    StepIndex si{step_dev, step_host};
+    if (s.prec == 0) return multi_dispatch<float>(s, tile, T, fin, a, si, partial, st);
+    return multi_dispatch<double>(s, tile, T, fin, a, si, partial, st);
 }
 
 // All Q mode densities of fin after streaming, in FP64: out[a V + s] =
