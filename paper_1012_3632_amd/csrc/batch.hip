@@ -203,8 +203,9 @@ __global__ __launch_bounds__(BT) void k_batch_step(const Real* __restrict__ fin,
         // chunk j + 1 orders the reads of chunk j before the writes of j + 2
         if constexpr (STATS) {
             double* lds = lds_stats + (it & 1) * LDS1;
+            const double old = threadIdx.x < 2 * Q ? partial[(size_t)threadIdx.x * nchunks + c] : 0.0;
             rows_to_lds<2 * Q>(v, lds);
-            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks);
+            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks, old);
         }
     }
 }
@@ -293,8 +294,9 @@ __global__ __launch_bounds__(BT) void k_batch_step_ip(Real* f, const RepInfo* __
         }
         if constexpr (STATS) {
             double* lds = lds_stats + (it & 1) * LDS1;
+            const double old = threadIdx.x < 2 * Q ? partial[(size_t)threadIdx.x * nchunks + c] : 0.0;
             rows_to_lds<2 * Q>(v, lds);
-            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks);
+            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks, old);
         }
     }
 }

@@ -190,16 +190,18 @@ __device__ __forceinline__ void rows_to_lds(Acc (&v)[NV], double* lds) {
     for (int p = 0; p < H4; ++p)
         if (p < len) lds[row * NV + base + p] = (double)a4[p];
 }
+// old: with ADD, thread k's out[k * stride], loaded by the caller before
+// (a load after the barrier would end the block with a round trip to memory).
 template <int NV, int NT, bool ADD>
 __device__ __forceinline__ void lds_rows_finish(const double* lds, double* __restrict__ out,
-                                                uint32_t stride) {
+                                                uint32_t stride, double old = 0.0) {
     constexpr int NR = 4 * ((NT + 63) / 64);   // 16-lane rows in the block
     __syncthreads();
     if (threadIdx.x < NV) {
         double acc = 0.0;
 #pragma unroll
         for (int r = 0; r < NR; ++r) acc += lds[r * NV + threadIdx.x];
-        if constexpr (ADD) out[(size_t)threadIdx.x * stride] += acc;
+        if constexpr (ADD) out[(size_t)threadIdx.x * stride] = old + acc;
         else out[(size_t)threadIdx.x * stride] = acc;
     }
 }
@@ -209,8 +211,9 @@ __device__ __forceinline__ void lds_rows_finish(const double* lds, double* __res
 template <int NV, int NT, typename Acc>
 __device__ __forceinline__ void block_accumulate(Acc (&v)[NV], double* __restrict__ slot,
                                                  double* lds) {
+    const double old = threadIdx.x < NV ? slot[threadIdx.x] : 0.0;
     rows_to_lds<NV, Acc>(v, lds);
-    lds_rows_finish<NV, NT, true>(lds, slot, 1);
+    lds_rows_finish<NV, NT, true>(lds, slot, 1, old);
 }
 
 template <int LAT, int TX, int TY, int TZ>
