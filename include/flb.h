@@ -493,8 +493,10 @@ flb_status flb_batch_destroy(flb_batch* b);
  * best_ms[3]: ms per step of the first three (either pointer may be NULL).
  * The statistics trials run on the handle's own slots, saved to host memory
  * before and restored after; the call synchronizes the stream.
- * Until then a handle uses shape 0, except D2Q9 force steps, which use
- * shape 4 (32 x 8, forming its own density tile).
+ * Until then a handle uses, for the ideal gas, the flat shapes (15, and 16 for
+ * pairs unless one population buffer exceeds 400 MiB; shape 0 where a box is
+ * past their 32-bit offsets), for D2Q9 force steps shape 4 (32 x 8, forming its
+ * own density tile) and for D3Q19 force steps shape 0.
  * Small D2Q9 lattices (at most 2^18 sites in FP32, less in FP64 and with
  * statistics) take two to four steps per launch, with the bits of as many
  * ordinary steps in populations and noise (statistics are summed in another
@@ -515,7 +517,8 @@ flb_status flb_launch_configs(const flb_handle* h, int32_t* count, int32_t* curr
  * shape, and 1 for a force step that forms its density tile from the
  * populations itself (no density pass before it; D2Q9), 2 for a z-marching
  * force step that forms the next step's density (D3Q19, FP32; in FP64 such a
- * shape runs the plain march of its tile). */
+ * shape runs the plain march of its tile), 3 for a flat shape (blocks of 256
+ * consecutive sites, ideal gas). */
 flb_status flb_launch_shape(const flb_handle* h, int32_t config, int32_t* shape);
 /* The same for a batch: the candidates are persistent grids of 8, 4, 16 or 2
  * blocks per compute unit; best[2] / best_ms[2] as for flb_autotune.  It then

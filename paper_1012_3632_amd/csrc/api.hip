@@ -345,9 +345,13 @@ flb_status flb_init(const flb_params* p, void* f_a, void* f_b, void* scratch, vo
     h->step = p->step0;
     h->nsamples = 0;
     // D2Q9 force steps default to the 32 x 8 tile that forms its own density
-    // tile (no density pass); every other kind to shape 0
-    h->cfg = h->cfg_stats = (h->spec.force && h->spec.lat == 0) ? 4 : 0;
-    h->pair_cfg = -1;
+    // tile (no density pass), D3Q19 ones to shape 0, the ideal gas to the flat
+    // shapes: pairs in place while one population buffer is not far above the
+    // 256 MB last-level cache (176 x 150 x 140: FP32, 281 MB, 121 us in pairs and
+    // 134 between two buffers; FP64, 562 MB, 268 and 250)
+    const bool flat = flat_fits(h->spec);
+    h->cfg = h->cfg_stats = h->spec.force ? (h->spec.lat == 0 ? 4 : 0) : (flat ? FLAT_CFG : 0);
+    h->pair_cfg = flat && (size_t)h->q * h->V * h->real_bytes <= (size_t)400 << 20 ? FLAT_PAIR_CFG : -1;
     h->multi[0] = h->multi[1] = true;
     h->graph[0] = h->graph[1] = nullptr;
     h->gexec[0] = h->gexec[1] = nullptr;
@@ -652,6 +656,15 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     const int ncfg = n_configs(h->spec.lat, h->spec.force);
+    // row tiles that a ragged box leaves more than a fifth empty lose to the
+    // flat shapes wherever those fit (101 x 77 x 53: 14.6 against 11.8 us) and
+    // are not timed
+    const bool flat = flat_fits(h->spec);
+    auto sparse = [&](int c) {
+        const TileShape t = config_shape(h->spec.lat, h->spec.force, c);
+        return flat && !t.fl &&
+               (double)config_blocks(h->spec, c) * t.tx * t.ty * t.tz * t.spt > 1.25 * (double)h->V;
+    };
     int bi[2] = {h->cfg, h->cfg_stats};
     float bt[2] = {1e30f, 1e30f};
     if (e == hipSuccess && h->spec.force) e = launch_density(h->spec, A, h->drho, st);
@@ -669,7 +682,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     for (int mode = 0; mode < 2 && e == hipSuccess; ++mode) {
         double* part = mode ? h->stats : nullptr;
         for (int c = 0; c < ncfg && e == hipSuccess; ++c) {
-            if (config_in_place(h->spec, c)) continue;   // timed as pairs below
+            if (config_in_place(h->spec, c) || sparse(c)) continue;   // pairs: timed below
             float ms = 0.f;
             // a force step that reads a density field pays for its pass; a
             // partial-density march for the completion of the next density
@@ -703,7 +716,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     float pair_ms = 1e30f;
     std::vector<int> cands;
     for (int c = 0; c < ncfg; ++c)
-        if (config_in_place(h->spec, c)) cands.push_back(c);
+        if (config_in_place(h->spec, c) && !sparse(c)) cands.push_back(c);
     auto pair = [&](int c) {
         hipError_t r = launch_step_in_place(h->spec, c, 0, A, nullptr, h->step, h->stats, st);
         if (r == hipSuccess)
@@ -818,7 +831,7 @@ flb_status flb_launch_shape(const flb_handle* h, int32_t config, int32_t* shape)
     shape[4] = t.nt;
     shape[5] = t.zc;
     shape[6] = t.ip;
-    shape[7] = t.fd ? 1 : (t.pd ? 2 : 0);
+    shape[7] = t.fd ? 1 : (t.pd ? 2 : (t.fl ? 3 : 0));
     return FLB_OK;
 }
 

@@ -38,6 +38,7 @@
 
 #include "../../include/flb.h"
 #include "device.h"
+#include "flat.h"
 #include "internal.h"
 
 namespace flb {
@@ -53,92 +54,6 @@ struct RepInfo {
     uint32_t chunk0, nchunks;
     uint32_t inv_nx, inv_ny;   // ceil(2^32 / n): exact division for n < 256, s < 2^24
 };
-
-__device__ __forceinline__ uint32_t div_small(uint32_t s, uint32_t inv) { return __umulhi(s, inv); }
-
-// Periodic neighbourhood of site s = x + nx (y + ny z) of one replica, in
-// bytes: s4 = s sizeof(Real) and the wrapped byte steps to x -+ 1, y -+ 1 and
-// z -+ 1 (modulo 2^32), each a selection between two uniform values, so that
-// the byte offset of x + c is s4 plus up to three of them (no multiplies;
-// the partial sums are shared between directions).
-template <typename Real>
-struct Nbr {
-    uint32_t s4, dx[2], dy[2], dz[2];
-    __device__ __forceinline__ Nbr(uint32_t s, int x, int y, int z, const struct RepInfo& R);
-    __device__ __forceinline__ uint32_t at(int cx, int cy, int cz) const {
-        uint32_t o = s4;
-        if (cz) o += dz[cz > 0];
-        if (cy) o += dy[cy > 0];
-        if (cx) o += dx[cx > 0];
-        return o;
-    }
-};
-template <typename Real>
-__device__ __forceinline__ Nbr<Real>::Nbr(uint32_t s, int x, int y, int z, const RepInfo& R) {
-    constexpr uint32_t E = sizeof(Real);
-    const uint32_t ex = E, ey = E * (uint32_t)R.nx, ez = ey * (uint32_t)R.ny;
-    const uint32_t wx = ey - ex, wy = ez - ey, wz = E * R.V - ez;   // a wrap: period minus a step
-    s4 = s * E;
-    dx[0] = x == 0 ? wx : 0u - ex;
-    dx[1] = x == R.nx - 1 ? 0u - wx : ex;
-    dy[0] = y == 0 ? wy : 0u - ey;
-    dy[1] = y == R.ny - 1 ? 0u - wy : ey;
-    dz[0] = z == 0 ? wz : 0u - ez;
-    dz[1] = z == R.nz - 1 ? 0u - wz : ez;
-}
-
-// The populations of one replica (Q planes of V sites from rep) as a buffer
-// resource: an access is the resource plus a uniform byte offset (plane i:
-// i V sizeof(Real), an SGPR) plus the lane's 32-bit byte offset, so no lane
-// forms a 64-bit address.  The record count is the replica's population
-// bytes (a replica has V < 2^24 sites).  V is made opaque to the compiler by
-// the caller once per tile (an empty asm on an SGPR), so that the plane
-// offsets are formed next to their accesses instead of being hoisted out of
-// the tile loop and held.  Word 3 of the resource is the CDNA raw-buffer
-// format (32-bit data format, no swizzle, no stride).
-// The record count and the scalar offsets are unsigned 32-bit fields of the
-// hardware (V < 2^24 sites, so Q V sizeof(Real) < 2^32); the builtins take
-// them as int, so values above 2^31 pass through the cast bit for bit.
-template <int LAT, typename Real>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rep_rsrc(const Real* rep, uint32_t V) {
-    const uint32_t bytes = (uint32_t)Lattice<LAT>::Q * V * (uint32_t)sizeof(Real);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<Real*>(rep), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ uint32_t plane_soff(uint32_t Vr, int i, uint32_t esize) {
-    return (uint32_t)i * Vr * esize;
-}
-__device__ __forceinline__ float rep_ld(__amdgpu_buffer_rsrc_t r, uint32_t Vr, int i, uint32_t boff,
-                                        float) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, (int)plane_soff(Vr, i, 4), 0));
-}
-__device__ __forceinline__ double rep_ld(__amdgpu_buffer_rsrc_t r, uint32_t Vr, int i,
-                                         uint32_t boff, double) {
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-    const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, (int)boff, (int)plane_soff(Vr, i, 8), 0);
-    return __longlong_as_double((long long)(((unsigned long long)w.y << 32) | w.x));
-}
-__device__ __forceinline__ void rep_st(__amdgpu_buffer_rsrc_t r, uint32_t Vr, int i, uint32_t boff,
-                                       float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)boff, (int)plane_soff(Vr, i, 4), 0);
-}
-__device__ __forceinline__ void rep_st(__amdgpu_buffer_rsrc_t r, uint32_t Vr, int i, uint32_t boff,
-                                       double v) {
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    u2 w;
-    w.x = (unsigned int)b;
-    w.y = (unsigned int)(b >> 32);
-    __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)boff, (int)plane_soff(Vr, i, 8), 0);
-}
-
-template <int LAT, typename Real>
-__device__ __forceinline__ void rep_pull(__amdgpu_buffer_rsrc_t rep, uint32_t Vr,
-                                         const Nbr<Real>& nb, Real (&f)[Lattice<LAT>::Q]) {
-    using L = Lattice<LAT>;
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i)
-        f[i] = rep_ld(rep, Vr, i, nb.at(-L::cx[i], -L::cy[i], -L::cz[i]), Real(0));
-}
 
 template <int LAT, typename Real, bool STATS>
 __global__ __launch_bounds__(BT) void k_batch_step(const Real* __restrict__ fin,
@@ -177,7 +92,7 @@ __global__ __launch_bounds__(BT) void k_batch_step(const Real* __restrict__ fin,
                 const int y = (int)(yz - z * (uint32_t)R.ny);
                 Real f[Q], m[Q];
                 rep_pull<LAT, Real>(rep_rsrc<LAT, Real>(fin + R.off, R.V), Vr,
-                                    Nbr<Real>(s, x, y, (int)z, R), f);
+                                    Nbr<Real>(s, x, y, (int)z, R.nx, R.ny, R.nz, R.V), f);
                 M::forward(f, m);
                 if constexpr (STATS) {
 #pragma unroll
@@ -252,7 +167,7 @@ __global__ __launch_bounds__(BT) void k_batch_step_ip(Real* f, const RepInfo* __
                 const int y = (int)(yz - z * (uint32_t)R.ny);
                 Real fl[Q], m[Q];
                 if constexpr (PH == 0) {
-                    rep_pull<LAT, Real>(rb, Vr, Nbr<Real>(s, x, y, (int)z, R), fl);
+                    rep_pull<LAT, Real>(rb, Vr, Nbr<Real>(s, x, y, (int)z, R.nx, R.ny, R.nz, R.V), fl);
                 } else {
                     // local accesses: one lane offset for every plane
                     const uint32_t s4 = s * (uint32_t)sizeof(Real);
@@ -277,7 +192,7 @@ __global__ __launch_bounds__(BT) void k_batch_step_ip(Real* f, const RepInfo* __
                     // in registers through it)
                     int xs = x;
                     asm volatile("" : "+v"(xs));
-                    const Nbr<Real> nb(s, xs, y, (int)z, R);
+                    const Nbr<Real> nb(s, xs, y, (int)z, R.nx, R.ny, R.nz, R.V);
                     uint32_t Vs = Vr;   // the store offsets are not those of the loads
                     asm volatile("" : "+s"(Vs));
 #pragma unroll

@@ -18,15 +18,20 @@ struct TileShape {
     int pd;           // 1: the z-marching force step also forms the next step's
                       //    density from its own sources (FP32), completed by
                       //    launch_density_fix (no density pass between steps)
+    int fl;           // 1: a block takes 256 consecutive sites in storage order (ideal
+                      //    gas; flat.h), so ragged rows leave no lane idle; boxes
+                      //    past its 32-bit offsets run the 256 x 1 tile
 };
 
 // Candidate tiles (the autotuner picks one per handle).
-constexpr int N_IDEAL_CFG = 15;
+constexpr int N_IDEAL_CFG = 17;
+constexpr int FLAT_CFG = 15, FLAT_PAIR_CFG = 16;
 constexpr TileShape IDEAL_CFG[N_IDEAL_CFG] = {
     {64, 4, 1, 1, 0},  {128, 2, 1, 1, 0}, {256, 1, 1, 1, 0}, {32, 8, 1, 1, 0},
     {128, 2, 1, 2, 0}, {64, 4, 1, 2, 0},  {128, 2, 1, 4, 0}, {256, 1, 1, 2, 0},
     {128, 2, 1, 1, 1}, {256, 1, 1, 1, 1}, {128, 2, 1, 1, 0, 0, 1}, {64, 4, 1, 1, 0, 0, 1},
-    {256, 1, 1, 1, 0, 0, 1}, {128, 2, 1, 2, 0, 0, 1}, {64, 4, 1, 2, 0, 0, 1}};
+    {256, 1, 1, 1, 0, 0, 1}, {128, 2, 1, 2, 0, 0, 1}, {64, 4, 1, 2, 0, 0, 1},
+    {256, 1, 1, 1, 0, 0, 0, 0, 0, 1}, {256, 1, 1, 1, 0, 0, 1, 0, 0, 1}};
 constexpr int N_FORCE3_CFG = 12;
 constexpr TileShape FORCE3_CFG[N_FORCE3_CFG] = {
     {32, 4, 2, 1, 0},     {16, 4, 4, 1, 0},     {64, 2, 2, 1, 0},
@@ -91,6 +96,8 @@ bool config_fused(const StepSpec& s, int cfg);
 hipError_t launch_step_in_place(const StepSpec& s, int cfg, int phase, void* f,
                                 const unsigned long long* step_dev, unsigned long long step_host,
                                 double* partial, hipStream_t st);
+// Whether the flat shapes' 32-bit offsets and divisions cover the box.
+bool flat_fits(const StepSpec& s);
 // Several D2Q9 steps in one launch (multistep.h).  multi_steps: how many, or
 // 0 where ordinary steps are the better choice; stats: some step may be
 // sampled, slots: the statistics slots the caller has.  launch_multi (the same

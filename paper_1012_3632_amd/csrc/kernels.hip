@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "device.h"
+#include "flat.h"
 #include "internal.h"
 #include "multistep.h"
 
@@ -303,6 +304,83 @@ __global__ __launch_bounds__(TX* TY) void k_step_ip(Real* f, Geom g, CollidePara
         const uint32_t b = xcd_remap(blockIdx.x, g.nblocks);
         block_accumulate<2 * Q, NT>(v, partial + (size_t)b * 2 * Q, lds_stats);
     }
+}
+
+// One ideal-gas step with 256 consecutive sites per block (flat.h): KIND 0
+// between two buffers, 1 and 2 the phases of an in-place pair (fin == fout).
+// The collision, noise counters and statistics are those of k_step.
+// Bound: memory and the last-level cache together with instruction issue, as
+// for the row tiles, which it replaces as the default: no lane idles on a
+// ragged row, offsets are wrapped steps from the site's own (a buffer resource
+// with scalar plane offsets) where a row tile forms 19 row bases, and 64-73
+// VGPRs with FP32 statistics keep 6-8 wavefronts per SIMD.  us per step with
+// statistics, best row tile -> here (pairs): 128^3 FP32 53.1 -> 49.8, FP64 130
+// -> 122 (plain 126 -> 110), 120 x 100 x 90 FP64 70.5 -> 58.1, 101 x 77 x 53
+// FP32 14.6 -> 11.8, 17 x 120 x 90 FP32 10.9 -> 7.5.
+constexpr int FLAT_NT = 256;
+template <int LAT, typename Real, bool STATS, int KIND>
+__global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fout, Geom g,
+                                                       uint32_t inv_nx, uint32_t inv_ny,
+                                                       CollideParams<Real> P, StepIndex st,
+                                                       double* __restrict__ partial) {
+    using L = Lattice<LAT>;
+    using M = Moments<LAT, Real>;
+    constexpr int Q = L::Q, D = L::D;
+    __shared__ double lds_stats[STATS ? 4 * (FLAT_NT / 64) * 2 * Q : 1];
+    const double2* tab = noise_table<Real, FLAT_NT>();
+    const uint32_t b = xcd_remap(blockIdx.x, g.nblocks);
+    const uint32_t s = b * (uint32_t)FLAT_NT + threadIdx.x;
+    const uint32_t step = st.get();
+    Real v[STATS ? 2 * Q : 1];
+    if constexpr (STATS) {
+#pragma unroll
+        for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
+    }
+    if (s < g.V) {
+        const uint32_t yz = div_small(s, inv_nx);
+        const int x = (int)(s - yz * (uint32_t)g.nx);
+        const uint32_t z = div_small(yz, inv_ny);
+        const int y = (int)(yz - z * (uint32_t)g.ny);
+        const __amdgpu_buffer_rsrc_t in = rep_rsrc<LAT, Real>(fin, g.V);
+        const __amdgpu_buffer_rsrc_t out = rep_rsrc<LAT, Real>(fout, g.V);
+        const uint32_t se = s * (uint32_t)sizeof(Real);
+        uint32_t Vr = g.V;
+        asm volatile("" : "+s"(Vr));
+        Real f[Q], m[Q];
+        if constexpr (KIND < 2) {
+            rep_pull<LAT, Real>(in, Vr, Nbr<Real>(s, x, y, (int)z, g.nx, g.ny, g.nz, g.V), f);
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) f[i] = rep_ld(in, Vr, L::opp[i], se, Real(0));
+        }
+        M::forward(f, m);
+        if constexpr (STATS) {
+#pragma unroll
+            for (int a = 0; a < Q; ++a) {
+                v[a] += m[a];
+                v[Q + a] += m[a] * m[a];
+            }
+        }
+        Real zn[2 * L::NPAIR];
+        if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, P.replica, P.key0, P.key1, zn, tab);
+        const Real F[D] = {};
+        collide_moments<LAT, Real, false>(m, F, zn, P);
+        M::inverse(m, f);
+        uint32_t Vs = Vr;   // the store offsets are not those of the loads
+        asm volatile("" : "+s"(Vs));
+        if constexpr (KIND == 1) {
+            int xs = x;     // nor is the neighbourhood held through the collision
+            asm volatile("" : "+v"(xs));
+            const Nbr<Real> nb(s, xs, y, (int)z, g.nx, g.ny, g.nz, g.V);
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                rep_st(out, Vs, L::opp[i], nb.at(L::cx[i], L::cy[i], L::cz[i]), f[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) rep_st(out, Vs, i, se, f[i]);
+        }
+    }
+    if constexpr (STATS) block_accumulate<2 * Q, FLAT_NT>(v, partial + (size_t)b * 2 * Q, lds_stats);
 }
 
 // The next step's density formed inside the z-march.  After streaming, the
@@ -881,7 +959,9 @@ static Geom make_geom(const StepSpec& s, TileShape t) {
 }
 
 uint32_t config_blocks(const StepSpec& s, int cfg) {
-    return make_geom(s, config_shape(s.lat, s.force, cfg)).nblocks;
+    const TileShape t = config_shape(s.lat, s.force, cfg);
+    if (t.fl && flat_fits(s)) return (uint32_t)(((size_t)s.nx * s.ny * s.nz + 255) / 256);
+    return make_geom(s, t).nblocks;
 }
 
 template <typename Real>
@@ -987,6 +1067,31 @@ static void step_march(const StepSpec& s, int zc, const void* fin, void* fout, c
     }
 }
 
+bool flat_fits(const StepSpec& s) {
+    const uint64_t V = (uint64_t)s.nx * s.ny * s.nz;
+    const uint64_t Q = s.lat == 0 ? 9 : 19, lim = 1ull << 32;
+    // the populations as one buffer resource; s / nx and (s / nx) / ny exact
+    return !s.force && Q * V * (s.prec ? 8 : 4) < lim && (V - 1) * (uint64_t)s.nx < lim &&
+           (V / s.nx - 1) * (uint64_t)s.ny < lim;
+}
+
+template <int LAT, typename Real>
+static void flat_launch(const StepSpec& s, int kind, const void* fin, void* fout, StepIndex si,
+                        double* partial, hipStream_t st) {
+    Geom g = make_geom(s, TileShape{1, 1, 1, 1, 0, 0, 0});
+    g.nblocks = (g.V + FLAT_NT - 1) / FLAT_NT;
+    const dim3 grid(g.nblocks), block(FLAT_NT);
+    const CollideParams<Real> P = collide_params<Real>(s);
+    const uint32_t ix = (uint32_t)(((1ull << 32) + s.nx - 1) / s.nx);
+    const uint32_t iy = (uint32_t)(((1ull << 32) + s.ny - 1) / s.ny);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, 0, st, (const Real*)fin, (Real*)fout, g, ix, iy, P, si, partial);
+    };
+    if (kind == 0) partial ? go(k_step_flat<LAT, Real, true, 0>) : go(k_step_flat<LAT, Real, false, 0>);
+    else if (kind == 1) partial ? go(k_step_flat<LAT, Real, true, 1>) : go(k_step_flat<LAT, Real, false, 1>);
+    else partial ? go(k_step_flat<LAT, Real, true, 2>) : go(k_step_flat<LAT, Real, false, 2>);
+}
+
 template <int LAT, typename Real>
 static void step_dispatch(const StepSpec& s, int cfg, const void* fin, void* fout,
                           const void* drho, StepIndex si, double* partial, hipStream_t st,
@@ -1008,6 +1113,11 @@ static void step_dispatch(const StepSpec& s, int cfg, const void* fin, void* fou
             case 11: step_tile<LAT, Real, false, 64, 4, 1, 1>(s, fin, fout, drho, si, partial, st); break;
             case 12: step_tile<LAT, Real, false, 256, 1, 1, 1>(s, fin, fout, drho, si, partial, st); break;
             case 13: step_tile<LAT, Real, false, 128, 2, 1, 2>(s, fin, fout, drho, si, partial, st); break;
+            case FLAT_CFG:
+            case FLAT_PAIR_CFG:
+                if (flat_fits(s)) flat_launch<LAT, Real>(s, 0, fin, fout, si, partial, st);
+                else step_tile<LAT, Real, false, 256, 1, 1, 1>(s, fin, fout, drho, si, partial, st);
+                break;
             default: step_tile<LAT, Real, false, 64, 4, 1, 2>(s, fin, fout, drho, si, partial, st); break;
         }
     } else if constexpr (LAT == 1) {
@@ -1061,6 +1171,12 @@ static void ip_dispatch(const StepSpec& s, int cfg, int phase, void* f, StepInde
         case 11: step_ip<LAT, Real, 64, 4>(s, phase, f, si, partial, st); break;
         case 13: step_ip<LAT, Real, 128, 2, 2>(s, phase, f, si, partial, st); break;
         case 14: step_ip<LAT, Real, 64, 4, 2>(s, phase, f, si, partial, st); break;
+        case FLAT_PAIR_CFG:
+            if (flat_fits(s)) {
+                flat_launch<LAT, Real>(s, 1 + phase, f, f, si, partial, st);
+                break;
+            }
+            [[fallthrough]];
         default: step_ip<LAT, Real, 256, 1>(s, phase, f, si, partial, st); break;
     }
 }
