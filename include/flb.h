@@ -426,15 +426,15 @@ flb_status flb_destroy(flb_handle* h);
 /* ---------------------------------------------------------------------------
  * Batched replicas: R independent lattices (same lattice type, precision and
  * physical parameters, each with its own box and seed) advanced by one
- * persistent launch per step over a flattened tile table.  Replica r uses
+ * launch per step over a flattened tile table.  Replica r uses
  * Philox key seeds[r] and counter word 3 = r; its populations occupy
  * Q V_r consecutive reals starting at element offset Q * sum_{s<r} V_s of
  * each population buffer (replica-major, then SoA within the replica).
- * Statistics buffer: a table of per-chunk sums (2Q x chunks FP64, a chunk
- * being up to 8 tiles of 256 sites of one replica; each sampled step of a
+ * Statistics buffer: a table of per-tile sums (tiles x 2Q FP64, a tile
+ * being up to 256 sites of one replica; each sampled step of a
  * call adds to it) followed by the per-replica FP64 accumulators (R x 2Q), to
  * which the end of each call (flb_batch_step, a graph replay) adds the sums
- * over the replica's chunks, clearing the table.
+ * over the replica's tiles, clearing the table.
  * -------------------------------------------------------------------------*/
 typedef struct flb_batch flb_batch;
 
@@ -520,13 +520,13 @@ flb_status flb_launch_configs(const flb_handle* h, int32_t* count, int32_t* curr
  * shape runs the plain march of its tile), 3 for a flat shape (blocks of 256
  * consecutive sites, ideal gas). */
 flb_status flb_launch_shape(const flb_handle* h, int32_t config, int32_t* shape);
-/* The same for a batch: the candidates are persistent grids of 8, 4, 16 or 2
- * blocks per compute unit; best[2] / best_ms[2] as for flb_autotune.  It then
+/* The same for a batch: there is one grid, a block per tile, so best[2] is 0;
+ * best_ms[2] as for flb_autotune.  It then
  * times in-place pairs group by group (flb_batch_set_pairs) with groups of up
- * to 64, 128, 160, 192, 224, 256 and 320 MiB on each of the four grids, with statistics, and keeps
- * the fastest (budget and grid) if it beats
+ * to 64, 128, 160, 192, 224, 256 and 320 MiB, with statistics, and keeps
+ * the fastest budget if it beats
  * the ordinary step with statistics (else turns pairs off).  The statistics
- * trials add only to the per-chunk table, which is clear between calls and
+ * trials add only to the per-tile table, which is clear between calls and
  * cleared again afterwards, so the accumulated statistics are unchanged;
  * the pair trials run on a copy
  * of the state in the other buffer, so the state is unchanged.

@@ -1,15 +1,11 @@
 // Batched replicas: many independent ideal-gas lattices of uneven size
-// advanced by one persistent launch per step.
+// advanced by one launch per step.
 //
 // Every replica's sites are cut into tiles of BT = 256 consecutive sites
-// (x fastest), and its n tiles are dealt to c = ceil(n / CH) chunks (CH = 8):
-// chunk j holds tiles j, j + c, j + 2c, ... (at most CH, all of one
-// replica).  The chunks of all replicas form one flat table.  Blocks working
-// on neighbouring chunks at the same time therefore touch neighbouring tiles.  A grid of (compute units x blocks per CU) workgroups walks the
-// table with a grid stride, one chunk at a time, so uneven replica sizes cost
-// nothing beyond the last partial wave.  Replica r has its own box, Philox
-// key seeds[r] and counter word 3 = r, and its populations start at element
-// Q * sum_{s<r} V_s of each buffer.
+// (x fastest; the last tile of a replica may be partly empty), the tiles of
+// all replicas form one flat table, and a block takes one tile, the flat step
+// of flat.h.  Replica r has its own box, Philox key seeds[r] and counter word
+// 3 = r, and its populations start at element Q * sum_{s<r} V_s of each buffer.
 // In-place pairs (optional, flb_batch_set_pairs): consecutive replicas are
 // grouped up to a byte budget and each group is taken through all the steps of
 // a call before the next, pairs of steps in one buffer (the first step of a
@@ -18,13 +14,16 @@
 // only it reads, just before), so that a group's working set can stay in the
 // last-level cache.  The noise counters hold the global step, so the result
 // is the same bits in either schedule.
-// Statistics: a thread sums the moments of its CH sites in registers; a
-// sampled step adds each chunk's 2Q FP64 block sums to a value-major table
-// partial[k][chunk] (one block reduction per chunk, the chunk's own slots),
-// and at the end of a call k_batch_fold adds, per replica and value, the sum
-// over the replica's chunks (fixed order) to an FP64 accumulator and clears
-// the slots.  Either schedule adds the same chunk sums in the same step
+// Statistics: a sampled step adds each tile's 2Q FP64 block sums to the tile's
+// own slots, and at the end of a call k_batch_fold adds, per replica and value,
+// the sum over the replica's tiles (fixed order) to an FP64 accumulator and
+// clears the slots.  Either schedule adds the same tile sums in the same step
 // order, so the statistics are bitwise the same.
+//
+// A block per tile rather than a persistent grid over chunks of eight tiles
+// with sums kept across them: a group near the cache size has about 1200
+// chunks, barely more than fit the chip at once, so its last wave of blocks
+// left it nearly idle, and the kept sums cost a third of the wavefronts.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,191 +42,58 @@
 
 namespace flb {
 
-constexpr int BT = 256;   // sites per tile (one per thread)
-constexpr int CH = 8;     // tiles per chunk
+constexpr int BT = FLAT_NT;   // sites per tile (one per thread)
 
 struct RepInfo {
     int32_t nx, ny, nz;
     uint32_t V;
     uint64_t off;          // element offset of the replica in a population buffer
     uint32_t key0, key1;
-    uint32_t chunk0, nchunks;
+    uint32_t tile0, ntiles;
     uint32_t inv_nx, inv_ny;   // ceil(2^32 / n): exact division for n < 256, s < 2^24
 };
 
-template <int LAT, typename Real, bool STATS>
-__global__ __launch_bounds__(BT) void k_batch_step(const Real* __restrict__ fin,
-                                                   Real* __restrict__ fout,
+// The tiles from t0 on: KIND 0 from fin to fout, 1 and 2 the phases of an
+// in-place pair (fin == fout, not restrict: a thread's stores alias its own
+// earlier loads).
+template <int LAT, typename Real, bool STATS, int KIND>
+__global__ __launch_bounds__(BT) void k_batch_step(const Real* fin, Real* fout,
                                                    const RepInfo* __restrict__ reps,
-                                                   const uint32_t* __restrict__ chunk_rep,
-                                                   uint32_t nchunks, CollideParams<Real> P,
-                                                   StepIndex st, double* __restrict__ partial) {
-    using L = Lattice<LAT>;
-    using M = Moments<LAT, Real>;
-    constexpr int Q = L::Q, D = L::D;
-    constexpr int LDS1 = 4 * (BT / 64) * 2 * Q;
-    __shared__ double lds_stats[STATS ? 2 * LDS1 : 1];
+                                                   const uint32_t* __restrict__ tile_rep,
+                                                   uint32_t t0, CollideParams<Real> P, StepIndex st,
+                                                   double* __restrict__ partial) {
+    constexpr int Q = Lattice<LAT>::Q;
+    __shared__ double lds_stats[STATS ? 4 * (BT / 64) * 2 * Q : 1];
+    const double2* tab = noise_table<Real, BT>();
+    const uint32_t t = t0 + xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t r = tile_rep[t];
+    const RepInfo R = reps[r];
+    const uint32_t s = (t - R.tile0) * (uint32_t)BT + threadIdx.x;
     const uint32_t step = st.get();
-    uint32_t it = 0;
-    for (uint32_t c = blockIdx.x; c < nchunks; c += gridDim.x, ++it) {
-        const uint32_t r = chunk_rep[c];
-        const RepInfo R = reps[r];
-        const uint32_t s0 = (c - R.chunk0) * (uint32_t)BT;
-        const uint32_t ds = R.nchunks * (uint32_t)BT;
-        Real v[STATS ? 2 * Q : 1];
-        if constexpr (STATS) {
+    Real v[STATS ? 2 * Q : 1];
+    if constexpr (STATS) {
 #pragma unroll
-            for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
-        }
-#pragma unroll 1
-        for (int tt = 0; tt < CH; ++tt) {
-            if (s0 + (uint32_t)tt * ds >= R.V) break;   // chunk with fewer tiles (uniform)
-            uint32_t Vr = R.V;
-            asm volatile("" : "+s"(Vr));
-            const uint32_t s = s0 + (uint32_t)tt * ds + threadIdx.x;
-            if (s < R.V) {
-                const uint32_t yz = div_small(s, R.inv_nx);
-                const int x = (int)(s - yz * (uint32_t)R.nx);
-                const uint32_t z = div_small(yz, R.inv_ny);
-                const int y = (int)(yz - z * (uint32_t)R.ny);
-                Real f[Q], m[Q];
-                rep_pull<LAT, Real>(rep_rsrc<LAT, Real>(fin + R.off, R.V), Vr,
-                                    Nbr<Real>(s, x, y, (int)z, R.nx, R.ny, R.nz, R.V), f);
-                M::forward(f, m);
-                if constexpr (STATS) {
-#pragma unroll
-                    for (int a = 0; a < Q; ++a) {
-                        v[a] += m[a];
-                        v[Q + a] += m[a] * m[a];
-                    }
-                }
-                Real zn[2 * L::NPAIR];
-                if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, r, R.key0, R.key1, zn);
-                const Real F[D] = {};
-                collide_moments<LAT, Real, false>(m, F, zn, P);
-                M::inverse(m, f);
-                const __amdgpu_buffer_rsrc_t out = rep_rsrc<LAT, Real>(fout + R.off, R.V);
-                const uint32_t s4 = s * (uint32_t)sizeof(Real);
-                uint32_t Vs = Vr;   // the store offsets are not those of the loads
-                asm volatile("" : "+s"(Vs));
-#pragma unroll
-                for (int i = 0; i < Q; ++i) rep_st(out, Vs, i, s4, f[i]);
-            }
-        }
-        // the two LDS buffers alternate: the barrier inside the finish of
-        // chunk j + 1 orders the reads of chunk j before the writes of j + 2
-        if constexpr (STATS) {
-            double* lds = lds_stats + (it & 1) * LDS1;
-            const double old = threadIdx.x < 2 * Q ? partial[(size_t)threadIdx.x * nchunks + c] : 0.0;
-            rows_to_lds<2 * Q>(v, lds);
-            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks, old);
-        }
+        for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
     }
+    if (s < R.V)
+        flat_site<LAT, Real, STATS, KIND>(fin + R.off, fout + R.off, s,
+                                          FlatBox{R.nx, R.ny, R.nz, R.V, R.inv_nx, R.inv_ny}, P, r,
+                                          R.key0, R.key1, step, tab, v);
+    if constexpr (STATS) block_accumulate<2 * Q, BT>(v, partial + (size_t)t * 2 * Q, lds_stats);
 }
 
-// One step of an in-place pair on the chunks [c0, c1) of the single buffer f
-// (not restrict: a thread's stores alias its own earlier loads).  PH 0 pulls
-// from the ordinary layout and stores S*_i(x) in plane opp(i) at x + c_i; PH 1
-// reads plane opp(i) at x and stores plane i at x.  The per-site arithmetic
-// and the statistics are those of k_batch_step.
-template <int LAT, typename Real, bool STATS, int PH>
-__global__ __launch_bounds__(BT) void k_batch_step_ip(Real* f, const RepInfo* __restrict__ reps,
-                                                      const uint32_t* __restrict__ chunk_rep,
-                                                      uint32_t c0, uint32_t c1, uint32_t nchunks,
-                                                      CollideParams<Real> P, StepIndex st,
-                                                      double* __restrict__ partial) {
-    using L = Lattice<LAT>;
-    using M = Moments<LAT, Real>;
-    constexpr int Q = L::Q, D = L::D;
-    constexpr int LDS1 = 4 * (BT / 64) * 2 * Q;
-    __shared__ double lds_stats[STATS ? 2 * LDS1 : 1];
-    const uint32_t step = st.get();
-    uint32_t it = 0;
-    for (uint32_t c = c0 + blockIdx.x; c < c1; c += gridDim.x, ++it) {
-        const uint32_t r = chunk_rep[c];
-        const RepInfo R = reps[r];
-        const uint32_t s0 = (c - R.chunk0) * (uint32_t)BT;
-        const uint32_t ds = R.nchunks * (uint32_t)BT;
-        const __amdgpu_buffer_rsrc_t rb = rep_rsrc<LAT, Real>(f + R.off, R.V);
-        Real v[STATS ? 2 * Q : 1];
-        if constexpr (STATS) {
-#pragma unroll
-            for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
-        }
-#pragma unroll 1
-        for (int tt = 0; tt < CH; ++tt) {
-            if (s0 + (uint32_t)tt * ds >= R.V) break;   // chunk with fewer tiles (uniform)
-            uint32_t Vr = R.V;
-            asm volatile("" : "+s"(Vr));
-            const uint32_t s = s0 + (uint32_t)tt * ds + threadIdx.x;
-            if (s < R.V) {
-                const uint32_t yz = div_small(s, R.inv_nx);
-                const int x = (int)(s - yz * (uint32_t)R.nx);
-                const uint32_t z = div_small(yz, R.inv_ny);
-                const int y = (int)(yz - z * (uint32_t)R.ny);
-                Real fl[Q], m[Q];
-                if constexpr (PH == 0) {
-                    rep_pull<LAT, Real>(rb, Vr, Nbr<Real>(s, x, y, (int)z, R.nx, R.ny, R.nz, R.V), fl);
-                } else {
-                    // local accesses: one lane offset for every plane
-                    const uint32_t s4 = s * (uint32_t)sizeof(Real);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) fl[i] = rep_ld(rb, Vr, L::opp[i], s4, Real(0));
-                }
-                M::forward(fl, m);
-                if constexpr (STATS) {
-#pragma unroll
-                    for (int a = 0; a < Q; ++a) {
-                        v[a] += m[a];
-                        v[Q + a] += m[a] * m[a];
-                    }
-                }
-                Real zn[2 * L::NPAIR];
-                if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, r, R.key0, R.key1, zn);
-                const Real F[D] = {};
-                collide_moments<LAT, Real, false>(m, F, zn, P);
-                M::inverse(m, fl);
-                if constexpr (PH == 0) {
-                    // neighbourhood formed again after the collision (not held
-                    // in registers through it)
-                    int xs = x;
-                    asm volatile("" : "+v"(xs));
-                    const Nbr<Real> nb(s, xs, y, (int)z, R.nx, R.ny, R.nz, R.V);
-                    uint32_t Vs = Vr;   // the store offsets are not those of the loads
-                    asm volatile("" : "+s"(Vs));
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-                        rep_st(rb, Vs, L::opp[i], nb.at(L::cx[i], L::cy[i], L::cz[i]), fl[i]);
-                } else {
-                    const uint32_t s4 = s * (uint32_t)sizeof(Real);
-                    uint32_t Vs = Vr;
-                    asm volatile("" : "+s"(Vs));
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) rep_st(rb, Vs, i, s4, fl[i]);
-                }
-            }
-        }
-        if constexpr (STATS) {
-            double* lds = lds_stats + (it & 1) * LDS1;
-            const double old = threadIdx.x < 2 * Q ? partial[(size_t)threadIdx.x * nchunks + c] : 0.0;
-            rows_to_lds<2 * Q>(v, lds);
-            lds_rows_finish<2 * Q, BT, true>(lds, partial + c, nchunks, old);
-        }
-    }
-}
-
-// acc[r][k] += sum over replica r's chunks (fixed order) of partial[k][chunk],
+// acc[r][k] += sum over replica r's tiles (fixed order) of partial[tile][k],
 // then those slots are cleared.  One block per (value k, replica r).
 __global__ void k_batch_fold(double* __restrict__ partial, const RepInfo* __restrict__ reps,
-                             uint32_t nchunks, int nvals, double* __restrict__ acc_out) {
+                             int nvals, double* __restrict__ acc_out) {
     __shared__ double red[256];
     const int k = blockIdx.x, r = blockIdx.y;
     const RepInfo R = reps[r];
-    double* col = partial + (size_t)k * nchunks + R.chunk0;
+    double* col = partial + (size_t)R.tile0 * nvals + k;
     double acc = 0.0;
-    for (uint32_t t = threadIdx.x; t < R.nchunks; t += 256) {
-        acc += col[t];
-        col[t] = 0.0;
+    for (uint32_t t = threadIdx.x; t < R.ntiles; t += 256) {
+        acc += col[(size_t)t * nvals];
+        col[(size_t)t * nvals] = 0.0;
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -236,23 +102,6 @@ __global__ void k_batch_fold(double* __restrict__ partial, const RepInfo* __rest
         __syncthreads();
     }
     if (threadIdx.x == 0) acc_out[(size_t)r * nvals + k] += red[0];
-}
-
-template <int LAT, typename Real>
-__global__ void k_batch_init(Real* __restrict__ f, const RepInfo* __restrict__ reps,
-                             const uint32_t* __restrict__ chunk_rep, uint32_t nchunks) {
-    using L = Lattice<LAT>;
-    for (uint32_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        const RepInfo R = reps[chunk_rep[c]];
-        const uint32_t s0 = (c - R.chunk0) * (uint32_t)BT;
-        for (int tt = 0; tt < CH; ++tt) {
-            const uint32_t s = s0 + (uint32_t)tt * R.nchunks * (uint32_t)BT + threadIdx.x;
-            if (s < R.V) {
-#pragma unroll
-                for (int i = 0; i < L::Q; ++i) f[R.off + (size_t)i * R.V + s] = Real(0);
-            }
-        }
-    }
 }
 
 }  // namespace flb
@@ -284,7 +133,7 @@ constexpr double CS2 = 1.0 / 3.0;
 
 struct Layout {
     std::vector<RepInfo> reps;
-    std::vector<uint32_t> chunk_rep;
+    std::vector<uint32_t> tile_rep;
     size_t elems;          // reals per population buffer
     size_t reps_off, tiles_off, ctr_off, scratch_bytes, stats_bytes;
 };
@@ -298,9 +147,9 @@ flb_status batch_layout(const flb_params* p, int32_t nrep, const int32_t* dims,
     flb_params q = *p;
     const int Q = p->lattice == FLB_D2Q9 ? 9 : 19;
     L->reps.clear();
-    L->chunk_rep.clear();
+    L->tile_rep.clear();
     size_t off = 0;
-    uint32_t chunk = 0;
+    uint32_t tile = 0;
     for (int r = 0; r < nrep; ++r) {
         q.nx = dims[3 * r];
         q.ny = dims[3 * r + 1];
@@ -323,12 +172,12 @@ flb_status batch_layout(const flb_params* p, int32_t nrep, const int32_t* dims,
         const uint64_t seed = seeds ? seeds[r] : (uint64_t)r;
         R.key0 = (uint32_t)(seed & 0xffffffffu);
         R.key1 = (uint32_t)(seed >> 32);
-        R.chunk0 = chunk;
-        R.nchunks = (R.V + CH * BT - 1) / (CH * BT);
+        R.tile0 = tile;
+        R.ntiles = (R.V + BT - 1) / BT;
         R.inv_nx = (uint32_t)(((1ull << 32) + R.nx - 1) / R.nx);
         R.inv_ny = (uint32_t)(((1ull << 32) + R.ny - 1) / R.ny);
-        for (uint32_t c = 0; c < R.nchunks; ++c) L->chunk_rep.push_back((uint32_t)r);
-        chunk += R.nchunks;
+        L->tile_rep.insert(L->tile_rep.end(), R.ntiles, (uint32_t)r);
+        tile += R.ntiles;
         off += (size_t)Q * R.V;
         L->reps.push_back(R);
     }
@@ -339,17 +188,17 @@ flb_status batch_layout(const flb_params* p, int32_t nrep, const int32_t* dims,
     L->reps_off = s;
     s += align_up(L->reps.size() * sizeof(RepInfo));
     L->tiles_off = s;
-    s += align_up(L->chunk_rep.size() * sizeof(uint32_t));
+    s += align_up(L->tile_rep.size() * sizeof(uint32_t));
     L->scratch_bytes = s;
-    L->stats_bytes = align_up(((size_t)chunk * 2 * Q + (size_t)nrep * 2 * Q) * sizeof(double));
+    L->stats_bytes = align_up(((size_t)tile * 2 * Q + (size_t)nrep * 2 * Q) * sizeof(double));
     return FLB_OK;
 }
 
 }  // namespace
 
-// Consecutive replicas [r0, r1), whose chunks are [c0, c1).
+// Consecutive replicas [r0, r1), whose tiles are [t0, t1).
 struct BatchGroup {
-    uint32_t r0, r1, c0, c1;
+    uint32_t r0, r1, t0, t1;
 };
 
 struct flb_batch {
@@ -365,14 +214,10 @@ struct flb_batch {
     RepInfo* reps_dev;
     uint32_t* tiles_dev;
     unsigned long long* ctr_dev;
-    uint32_t nchunks;
+    uint32_t ntiles;
     uint64_t step;
     int64_t nsamples;
-    int grid_cfg;          // persistent grid of plain steps
-    int grid_cfg_stats;    // persistent grid of steps with statistics
-    int ncu;
     uint64_t pair_bytes;   // > 0: in-place pairs, groups of replicas up to this many bytes
-    int pair_cfg;          // persistent grid of the in-place steps
     std::vector<BatchGroup> groups;
     // captured steps, one graph per current buffer (index cur_a): kernel
     // arguments hold the buffer pointers
@@ -394,9 +239,6 @@ void release_batch_graphs(flb_batch* b) {
     }
 }
 
-constexpr int N_GRID_CFG = 4;
-constexpr int GRID_PER_CU[N_GRID_CFG] = {8, 4, 16, 2};
-
 template <int LAT, typename Real>
 CollideParams<Real> batch_collide_params(const flb_batch* b) {
     CollideParams<Real> P;
@@ -416,55 +258,35 @@ CollideParams<Real> batch_collide_params(const flb_batch* b) {
     return P;
 }
 
+// kind 0: all replicas from fin to fout; 1, 2: a phase of an in-place pair on
+// the tiles of G (fin == fout).
 template <int LAT, typename Real>
-void batch_launch(flb_batch* b, int cfg, const void* fin, void* fout,
+void batch_launch(flb_batch* b, int kind, const BatchGroup& G, const void* fin, void* fout,
                   const unsigned long long* step_dev, unsigned long long step_host,
                   double* partial, hipStream_t st) {
     const CollideParams<Real> P = batch_collide_params<LAT, Real>(b);
     StepIndex si{step_dev, step_host};
-    const uint32_t grid = std::min<uint32_t>(b->nchunks, (uint32_t)(b->ncu * GRID_PER_CU[cfg]));
-    if (partial)
-        hipLaunchKernelGGL((k_batch_step<LAT, Real, true>), dim3(grid), dim3(BT), 0, st,
-                           (const Real*)fin, (Real*)fout, b->reps_dev, b->tiles_dev, b->nchunks, P,
-                           si, partial);
-    else
-        hipLaunchKernelGGL((k_batch_step<LAT, Real, false>), dim3(grid), dim3(BT), 0, st,
-                           (const Real*)fin, (Real*)fout, b->reps_dev, b->tiles_dev, b->nchunks, P,
-                           si, partial);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(G.t1 - G.t0), dim3(BT), 0, st, (const Real*)fin, (Real*)fout,
+                           b->reps_dev, b->tiles_dev, G.t0, P, si, partial);
+    };
+    if (kind == 0) partial ? go(k_batch_step<LAT, Real, true, 0>) : go(k_batch_step<LAT, Real, false, 0>);
+    else if (kind == 1) partial ? go(k_batch_step<LAT, Real, true, 1>) : go(k_batch_step<LAT, Real, false, 1>);
+    else partial ? go(k_batch_step<LAT, Real, true, 2>) : go(k_batch_step<LAT, Real, false, 2>);
 }
 
-template <int LAT, typename Real>
-void batch_ip_launch(flb_batch* b, int cfg, int phase, const BatchGroup& G, void* f,
+hipError_t batch_one(flb_batch* b, int kind, const BatchGroup& G, const void* fin, void* fout,
                      const unsigned long long* step_dev, unsigned long long step_host,
                      double* partial, hipStream_t st) {
-    const CollideParams<Real> P = batch_collide_params<LAT, Real>(b);
-    StepIndex si{step_dev, step_host};
-    const uint32_t n = G.c1 - G.c0;
-    const uint32_t grid = std::min<uint32_t>(n, (uint32_t)(b->ncu * GRID_PER_CU[cfg]));
-    Real* fr = (Real*)f;
-#define FLB_BATCH_IP(S, PH)                                                                   \
-    hipLaunchKernelGGL((k_batch_step_ip<LAT, Real, S, PH>), dim3(grid), dim3(BT), 0, st, fr,  \
-                       b->reps_dev, b->tiles_dev, G.c0, G.c1, b->nchunks, P, si, partial)
-    if (partial) {
-        if (phase == 0) FLB_BATCH_IP(true, 0);
-        else FLB_BATCH_IP(true, 1);
-    } else {
-        if (phase == 0) FLB_BATCH_IP(false, 0);
-        else FLB_BATCH_IP(false, 1);
-    }
-#undef FLB_BATCH_IP
-}
-
-hipError_t batch_ip_one(flb_batch* b, int cfg, int phase, const BatchGroup& G, void* f,
-                        const unsigned long long* step_dev, unsigned long long step_host,
-                        double* partial, hipStream_t st) {
     const int lat = b->p.lattice, prec = b->p.precision;
-    if (lat == 0 && prec == 0) batch_ip_launch<0, float>(b, cfg, phase, G, f, step_dev, step_host, partial, st);
-    else if (lat == 0) batch_ip_launch<0, double>(b, cfg, phase, G, f, step_dev, step_host, partial, st);
-    else if (prec == 0) batch_ip_launch<1, float>(b, cfg, phase, G, f, step_dev, step_host, partial, st);
-    else batch_ip_launch<1, double>(b, cfg, phase, G, f, step_dev, step_host, partial, st);
+    if (lat == 0 && prec == 0) batch_launch<0, float>(b, kind, G, fin, fout, step_dev, step_host, partial, st);
+    else if (lat == 0) batch_launch<0, double>(b, kind, G, fin, fout, step_dev, step_host, partial, st);
+    else if (prec == 0) batch_launch<1, float>(b, kind, G, fin, fout, step_dev, step_host, partial, st);
+    else batch_launch<1, double>(b, kind, G, fin, fout, step_dev, step_host, partial, st);
     return hipGetLastError();
 }
+
+BatchGroup batch_all(const flb_batch* b) { return BatchGroup{0, (uint32_t)b->nrep, 0, b->ntiles}; }
 
 // Consecutive replicas up to `bytes` of populations per group (a replica
 // larger than that forms a group of its own).
@@ -476,28 +298,17 @@ std::vector<BatchGroup> batch_groups(const flb_batch* b, uint64_t bytes) {
     for (uint32_t r = 0; r < (uint32_t)R.size(); ++r) {
         const uint64_t rb = (uint64_t)b->q * R[r].V * b->rb;
         if (r > r0 && acc + rb > bytes) {
-            out.push_back({r0, r, R[r0].chunk0, R[r].chunk0});
+            out.push_back({r0, r, R[r0].tile0, R[r].tile0});
             r0 = r;
             acc = 0;
         }
         acc += rb;
     }
-    out.push_back({r0, (uint32_t)R.size(), R[r0].chunk0, b->nchunks});
+    out.push_back({r0, (uint32_t)R.size(), R[r0].tile0, b->ntiles});
     return out;
 }
 
-hipError_t batch_one(flb_batch* b, int cfg, const void* fin, void* fout,
-                     const unsigned long long* step_dev, unsigned long long step_host,
-                     double* partial, hipStream_t st) {
-    const int lat = b->p.lattice, prec = b->p.precision;
-    if (lat == 0 && prec == 0) batch_launch<0, float>(b, cfg, fin, fout, step_dev, step_host, partial, st);
-    else if (lat == 0) batch_launch<0, double>(b, cfg, fin, fout, step_dev, step_host, partial, st);
-    else if (prec == 0) batch_launch<1, float>(b, cfg, fin, fout, step_dev, step_host, partial, st);
-    else batch_launch<1, double>(b, cfg, fin, fout, step_dev, step_host, partial, st);
-    return hipGetLastError();
-}
-
-double* batch_acc(flb_batch* b) { return b->stats + (size_t)b->nchunks * 2 * b->q; }
+double* batch_acc(flb_batch* b) { return b->stats + (size_t)b->ntiles * 2 * b->q; }
 
 flb_status batch_run(flb_batch* b, int64_t nsteps, int32_t stride, bool graph_mode,
                      hipStream_t st, int64_t* samples) {
@@ -515,8 +326,8 @@ flb_status batch_run(flb_batch* b, int64_t nsteps, int32_t stride, bool graph_mo
         for (const BatchGroup& G : b->groups) {
             for (int64_t j = 0; j < np; ++j) {
                 const bool sample = sampled(j);
-                BHIP(batch_ip_one(b, b->pair_cfg, (int)(j & 1), G, b->cur(), sd, index(j),
-                                  sample ? b->stats : nullptr, st));
+                BHIP(batch_one(b, 1 + (int)(j & 1), G, b->cur(), b->cur(), sd, index(j),
+                               sample ? b->stats : nullptr, st));
             }
         }
         for (int64_t j = 0; j < np; ++j) ns += sampled(j);
@@ -524,14 +335,14 @@ flb_status batch_run(flb_batch* b, int64_t nsteps, int32_t stride, bool graph_mo
     }
     for (; k < nsteps; ++k) {
         const bool sample = sampled(k);
-        BHIP(batch_one(b, sample ? b->grid_cfg_stats : b->grid_cfg, b->cur(), b->other(), sd,
-                       index(k), sample ? b->stats : nullptr, st));
+        BHIP(batch_one(b, 0, batch_all(b), b->cur(), b->other(), sd, index(k),
+                       sample ? b->stats : nullptr, st));
         b->cur_a = !b->cur_a;
         ns += sample;
     }
     if (ns > 0) {
         hipLaunchKernelGGL(k_batch_fold, dim3(nv, b->nrep), dim3(256), 0, st, b->stats,
-                           b->reps_dev, b->nchunks, nv, batch_acc(b));
+                           b->reps_dev, nv, batch_acc(b));
         BHIP(hipGetLastError());
     }
     if (graph_mode) BHIP(launch_add_u64(b->ctr_dev, (unsigned long long)nsteps, st));
@@ -583,38 +394,23 @@ flb_status flb_batch_init(const flb_params* base, int32_t nrep, const int32_t* d
     b->reps_dev = (RepInfo*)(b->scratch + b->L.reps_off);
     b->tiles_dev = (uint32_t*)(b->scratch + b->L.tiles_off);
     b->ctr_dev = (unsigned long long*)(b->scratch + b->L.ctr_off);
-    b->nchunks = (uint32_t)b->L.chunk_rep.size();
+    b->ntiles = (uint32_t)b->L.tile_rep.size();
     b->step = base->step0;
     b->nsamples = 0;
-    b->grid_cfg = 0;
-    b->grid_cfg_stats = 0;
     b->pair_bytes = 0;
-    b->pair_cfg = 2;
     b->graph[0] = b->graph[1] = nullptr;
     b->gexec[0] = b->gexec[1] = nullptr;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&b->ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    hipError_t e = hipSuccess;
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->reps_dev, b->L.reps.data(), b->L.reps.size() * sizeof(RepInfo),
                            hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(b->tiles_dev, b->L.chunk_rep.data(), b->nchunks * sizeof(uint32_t),
+        e = hipMemcpyAsync(b->tiles_dev, b->L.tile_rep.data(), b->ntiles * sizeof(uint32_t),
                            hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = launch_set_u64(b->ctr_dev, b->step, st);
     if (e == hipSuccess) e = launch_fill_zero(stats, b->L.stats_bytes, st);
-    if (e == hipSuccess) {
-        const uint32_t grid = std::min<uint32_t>(b->nchunks, 2048);
-        if (b->p.lattice == 0 && b->p.precision == 0)
-            hipLaunchKernelGGL((k_batch_init<0, float>), dim3(grid), dim3(BT), 0, st, (float*)f_a, b->reps_dev, b->tiles_dev, b->nchunks);
-        else if (b->p.lattice == 0)
-            hipLaunchKernelGGL((k_batch_init<0, double>), dim3(grid), dim3(BT), 0, st, (double*)f_a, b->reps_dev, b->tiles_dev, b->nchunks);
-        else if (b->p.precision == 0)
-            hipLaunchKernelGGL((k_batch_init<1, float>), dim3(grid), dim3(BT), 0, st, (float*)f_a, b->reps_dev, b->tiles_dev, b->nchunks);
-        else
-            hipLaunchKernelGGL((k_batch_init<1, double>), dim3(grid), dim3(BT), 0, st, (double*)f_a, b->reps_dev, b->tiles_dev, b->nchunks);
-        e = hipGetLastError();
-    }
+    // the uniform rest state: every deviation from w_i rho0 is zero
+    if (e == hipSuccess) e = launch_fill_zero(f_a, b->L.elems * b->rb, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         delete b;
@@ -658,7 +454,7 @@ flb_status flb_batch_moments(flb_batch* b, double* mode_sum, double* mode_sumsq,
 
 flb_status flb_batch_reset_stats(flb_batch* b, void* stream) {
     if (!b) return bfail(FLB_ERR_INVALID_ARG, "batch is NULL");
-    // the per-chunk table is clear between calls; the accumulators follow it
+    // the per-tile table is clear between calls; the accumulators follow it
     BHIP(launch_fill_zero(batch_acc(b), (size_t)b->nrep * 2 * b->q * sizeof(double),
                           (hipStream_t)stream));
     b->nsamples = 0;
@@ -733,30 +529,21 @@ flb_status flb_batch_autotune(flb_batch* b, int32_t repeats, int32_t* best, doub
     hipEvent_t e0, e1;
     BHIP(hipEventCreate(&e0));
     BHIP(hipEventCreate(&e1));
-    int bi[2] = {b->grid_cfg, b->grid_cfg_stats};
-    float bt[2] = {1e30f, 1e30f};
-    // statistics trials only add to the per-chunk table, cleared below; the
+    float bt[2] = {0.f, 0.f};
+    // statistics trials only add to the per-tile table, cleared below; the
     // accumulators are not touched
     for (int mode = 0; mode < 2; ++mode) {
         double* part = mode ? b->stats : nullptr;
-        for (int c = 0; c < N_GRID_CFG; ++c) {
-            BHIP(batch_one(b, c, b->cur(), b->other(), nullptr, b->step, part, st));
-            BHIP(hipEventRecord(e0, st));
-            for (int r = 0; r < repeats; ++r)
-                BHIP(batch_one(b, c, b->cur(), b->other(), nullptr, b->step, part, st));
-            BHIP(hipEventRecord(e1, st));
-            BHIP(hipEventSynchronize(e1));
-            float ms = 0.f;
-            BHIP(hipEventElapsedTime(&ms, e0, e1));
-            ms /= repeats;
-            if (ms < bt[mode]) {
-                bt[mode] = ms;
-                bi[mode] = c;
-            }
-        }
+        const BatchGroup all = batch_all(b);
+        BHIP(batch_one(b, 0, all, b->cur(), b->other(), nullptr, b->step, part, st));
+        BHIP(hipEventRecord(e0, st));
+        for (int r = 0; r < repeats; ++r)
+            BHIP(batch_one(b, 0, all, b->cur(), b->other(), nullptr, b->step, part, st));
+        BHIP(hipEventRecord(e1, st));
+        BHIP(hipEventSynchronize(e1));
+        BHIP(hipEventElapsedTime(&bt[mode], e0, e1));
+        bt[mode] /= repeats;
     }
-    b->grid_cfg = bi[0];
-    b->grid_cfg_stats = bi[1];
     // in-place pairs group by group, with statistics: the trials run in place
     // on a copy of the state in the other buffer (the next ordinary step
     // overwrites it), so the state is untouched
@@ -764,40 +551,35 @@ flb_status flb_batch_autotune(flb_batch* b, int32_t repeats, int32_t* best, doub
         BHIP(hipMemcpyAsync(b->other(), b->cur(), b->L.elems * b->rb, hipMemcpyDeviceToDevice,
                             st));
         uint64_t best_bytes = 0;
-        int best_cfg = b->pair_cfg;
         float best_pair = bt[1];
         for (uint64_t mib : {64ull, 128ull, 160ull, 192ull, 224ull, 256ull, 320ull}) {
             const std::vector<BatchGroup> groups = batch_groups(b, mib << 20);
-            for (int c = 0; c < N_GRID_CFG; ++c) {
-                BHIP(hipEventRecord(e0, st));
-                for (const BatchGroup& G : groups)
-                    for (int j = 0; j < 2 * repeats; ++j)
-                        BHIP(batch_ip_one(b, c, j & 1, G, b->other(), nullptr, b->step + j,
-                                          b->stats, st));
-                BHIP(hipEventRecord(e1, st));
-                BHIP(hipEventSynchronize(e1));
-                float ms = 0.f;
-                BHIP(hipEventElapsedTime(&ms, e0, e1));
-                ms /= 2 * repeats;
-                if (ms < best_pair) {
-                    best_pair = ms;
-                    best_bytes = mib << 20;
-                    best_cfg = c;
-                }
+            BHIP(hipEventRecord(e0, st));
+            for (const BatchGroup& G : groups)
+                for (int j = 0; j < 2 * repeats; ++j)
+                    BHIP(batch_one(b, 1 + (j & 1), G, b->other(), b->other(), nullptr, b->step + j,
+                                   b->stats, st));
+            BHIP(hipEventRecord(e1, st));
+            BHIP(hipEventSynchronize(e1));
+            float ms = 0.f;
+            BHIP(hipEventElapsedTime(&ms, e0, e1));
+            ms /= 2 * repeats;
+            if (ms < best_pair) {
+                best_pair = ms;
+                best_bytes = mib << 20;
             }
         }
         b->pair_bytes = best_bytes;
-        b->pair_cfg = best_cfg;
-        // the statistics trials added to the per-chunk slots, which are clear
+        // the statistics trials added to the per-tile slots, which are clear
         // between calls: clear them again
-        BHIP(launch_fill_zero(b->stats, (size_t)b->nchunks * 2 * b->q * sizeof(double), st));
+        BHIP(launch_fill_zero(b->stats, (size_t)b->ntiles * 2 * b->q * sizeof(double), st));
         BHIP(hipStreamSynchronize(st));
         b->groups = best_bytes ? batch_groups(b, best_bytes) : std::vector<BatchGroup>();
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     for (int m = 0; m < 2; ++m) {
-        if (best) best[m] = bi[m];
+        if (best) best[m] = 0;   // one grid: a block per tile
         if (best_ms) best_ms[m] = bt[m];
     }
     return FLB_OK;

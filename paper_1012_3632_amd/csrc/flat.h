@@ -101,4 +101,67 @@ __device__ __forceinline__ void rep_pull(__amdgpu_buffer_rsrc_t rep, uint32_t Vr
         f[i] = rep_ld(rep, Vr, i, nb.at(-L::cx[i], -L::cy[i], -L::cz[i]), Real(0));
 }
 
+constexpr int FLAT_NT = 256;   // sites per block
+
+struct FlatBox {
+    int32_t nx, ny, nz;
+    uint32_t V, inv_nx, inv_ny;   // the inverses of div_small
+};
+
+// One ideal-gas step of site s: KIND 0 from fin to fout, 1 and 2 the phases of
+// an in-place pair (fin == fout).  With STATS the site's moments and their
+// squares are added to v.
+template <int LAT, typename Real, bool STATS, int KIND>
+__device__ __forceinline__ void flat_site(const Real* fin, Real* fout, uint32_t s, const FlatBox& B,
+                                          const CollideParams<Real>& P, uint32_t replica,
+                                          uint32_t key0, uint32_t key1, uint32_t step,
+                                          const double2* tab, Real* v) {
+    using L = Lattice<LAT>;
+    using M = Moments<LAT, Real>;
+    constexpr int Q = L::Q, D = L::D;
+    const uint32_t yz = div_small(s, B.inv_nx);
+    const int x = (int)(s - yz * (uint32_t)B.nx);
+    const uint32_t z = div_small(yz, B.inv_ny);
+    const int y = (int)(yz - z * (uint32_t)B.ny);
+    const __amdgpu_buffer_rsrc_t in = rep_rsrc<LAT, Real>(fin, B.V);
+    const __amdgpu_buffer_rsrc_t out = rep_rsrc<LAT, Real>(fout, B.V);
+    const uint32_t se = s * (uint32_t)sizeof(Real);
+    uint32_t Vr = B.V;
+    asm volatile("" : "+s"(Vr));
+    Real f[Q], m[Q];
+    if constexpr (KIND < 2) {
+        rep_pull<LAT, Real>(in, Vr, Nbr<Real>(s, x, y, (int)z, B.nx, B.ny, B.nz, B.V), f);
+    } else {
+        // local accesses: one lane offset for every plane
+#pragma unroll
+        for (int i = 0; i < Q; ++i) f[i] = rep_ld(in, Vr, L::opp[i], se, Real(0));
+    }
+    M::forward(f, m);
+    if constexpr (STATS) {
+#pragma unroll
+        for (int a = 0; a < Q; ++a) {
+            v[a] += m[a];
+            v[Q + a] += m[a] * m[a];
+        }
+    }
+    Real zn[2 * L::NPAIR];
+    if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, replica, key0, key1, zn, tab);
+    const Real F[D] = {};
+    collide_moments<LAT, Real, false>(m, F, zn, P);
+    M::inverse(m, f);
+    uint32_t Vs = Vr;   // the store offsets are not those of the loads
+    asm volatile("" : "+s"(Vs));
+    if constexpr (KIND == 1) {
+        int xs = x;     // nor is the neighbourhood held through the collision
+        asm volatile("" : "+v"(xs));
+        const Nbr<Real> nb(s, xs, y, (int)z, B.nx, B.ny, B.nz, B.V);
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            rep_st(out, Vs, L::opp[i], nb.at(L::cx[i], L::cy[i], L::cz[i]), f[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) rep_st(out, Vs, i, se, f[i]);
+    }
+}
+
 }  // namespace flb

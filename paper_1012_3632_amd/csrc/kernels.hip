@@ -317,15 +317,12 @@ __global__ __launch_bounds__(TX* TY) void k_step_ip(Real* f, Geom g, CollidePara
 // statistics, best row tile -> here (pairs): 128^3 FP32 53.1 -> 49.8, FP64 130
 // -> 122 (plain 126 -> 110), 120 x 100 x 90 FP64 70.5 -> 58.1, 101 x 77 x 53
 // FP32 14.6 -> 11.8, 17 x 120 x 90 FP32 10.9 -> 7.5.
-constexpr int FLAT_NT = 256;
 template <int LAT, typename Real, bool STATS, int KIND>
 __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fout, Geom g,
                                                        uint32_t inv_nx, uint32_t inv_ny,
                                                        CollideParams<Real> P, StepIndex st,
                                                        double* __restrict__ partial) {
-    using L = Lattice<LAT>;
-    using M = Moments<LAT, Real>;
-    constexpr int Q = L::Q, D = L::D;
+    constexpr int Q = Lattice<LAT>::Q;
     __shared__ double lds_stats[STATS ? 4 * (FLAT_NT / 64) * 2 * Q : 1];
     const double2* tab = noise_table<Real, FLAT_NT>();
     const uint32_t b = xcd_remap(blockIdx.x, g.nblocks);
@@ -336,50 +333,9 @@ __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fo
 #pragma unroll
         for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
     }
-    if (s < g.V) {
-        const uint32_t yz = div_small(s, inv_nx);
-        const int x = (int)(s - yz * (uint32_t)g.nx);
-        const uint32_t z = div_small(yz, inv_ny);
-        const int y = (int)(yz - z * (uint32_t)g.ny);
-        const __amdgpu_buffer_rsrc_t in = rep_rsrc<LAT, Real>(fin, g.V);
-        const __amdgpu_buffer_rsrc_t out = rep_rsrc<LAT, Real>(fout, g.V);
-        const uint32_t se = s * (uint32_t)sizeof(Real);
-        uint32_t Vr = g.V;
-        asm volatile("" : "+s"(Vr));
-        Real f[Q], m[Q];
-        if constexpr (KIND < 2) {
-            rep_pull<LAT, Real>(in, Vr, Nbr<Real>(s, x, y, (int)z, g.nx, g.ny, g.nz, g.V), f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) f[i] = rep_ld(in, Vr, L::opp[i], se, Real(0));
-        }
-        M::forward(f, m);
-        if constexpr (STATS) {
-#pragma unroll
-            for (int a = 0; a < Q; ++a) {
-                v[a] += m[a];
-                v[Q + a] += m[a] * m[a];
-            }
-        }
-        Real zn[2 * L::NPAIR];
-        if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, P.replica, P.key0, P.key1, zn, tab);
-        const Real F[D] = {};
-        collide_moments<LAT, Real, false>(m, F, zn, P);
-        M::inverse(m, f);
-        uint32_t Vs = Vr;   // the store offsets are not those of the loads
-        asm volatile("" : "+s"(Vs));
-        if constexpr (KIND == 1) {
-            int xs = x;     // nor is the neighbourhood held through the collision
-            asm volatile("" : "+v"(xs));
-            const Nbr<Real> nb(s, xs, y, (int)z, g.nx, g.ny, g.nz, g.V);
-#pragma unroll
-            for (int i = 0; i < Q; ++i)
-                rep_st(out, Vs, L::opp[i], nb.at(L::cx[i], L::cy[i], L::cz[i]), f[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) rep_st(out, Vs, i, se, f[i]);
-        }
-    }
+    if (s < g.V)
+        flat_site<LAT, Real, STATS, KIND>(fin, fout, s, FlatBox{g.nx, g.ny, g.nz, g.V, inv_nx, inv_ny},
+                                          P, P.replica, P.key0, P.key1, step, tab, v);
     if constexpr (STATS) block_accumulate<2 * Q, FLAT_NT>(v, partial + (size_t)b * 2 * Q, lds_stats);
 }
 
