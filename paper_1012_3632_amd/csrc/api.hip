@@ -1197,7 +1197,7 @@ flb_status flb_modeq_step(const flb_modeq_params* p, const void* fin, void* fout
         xi = modeq_fields(a, work, 1);
         HIP_TRY(launch_modeq_noise(a, p->precision, (uint32_t)step, 1, work, xi, st));
     }
-    HIP_TRY(launch_modeq_step(a, p->precision, fin, fout, (uint32_t)step, xi, st));
+    HIP_TRY(launch_modeq_step(a, p->precision, 1, fin, fout, (uint32_t)step, xi, st));
     return FLB_OK;
 }
 
@@ -1278,7 +1278,7 @@ flb_status flb_modeq_step_noalloc(const flb_modeq_params* p, const void* fin, vo
         xi = modeq_fields(a, work, 1);
         HIP_TRY(launch_modeq_noise(a, p->precision, (uint32_t)step, 1, work, xi, st));
     }
-    HIP_TRY(launch_modeq_step(a, p->precision, fin, fout, (uint32_t)step, xi, st));
+    HIP_TRY(launch_modeq_step(a, p->precision, 1, fin, fout, (uint32_t)step, xi, st));
     return FLB_OK;
 }
 
@@ -1296,8 +1296,12 @@ flb_status flb_modeq_run(const flb_modeq_params* p, void* f, void* tmp, uint64_t
     const size_t V = (size_t)a.nx * a.ny;
     const size_t rsize = a.prec == 0 ? sizeof(float) : sizeof(double);
     // noise batches of up to MODEQ_MAX_BATCH steps, as many as work holds
-    size_t fit = a.kT > 0.0 ? work_bytes / modeq_work_bytes(a.nx, a.ny, a.prec) : 1;
+    const size_t fit = a.kT > 0.0 ? work_bytes / modeq_work_bytes(a.nx, a.ny, a.prec)
+                                  : (size_t)MODEQ_MAX_BATCH;
     const int nb_max = (int)(fit < (size_t)MODEQ_MAX_BATCH ? fit : MODEQ_MAX_BATCH);
+    const int T = modeq_steps(a);
+    void* in = f;
+    void* out = tmp;
     for (int32_t k0 = 0; k0 < nsteps; k0 += nb_max) {
         const int nb = nsteps - k0 < nb_max ? nsteps - k0 : nb_max;
         char* xi = nullptr;
@@ -1305,18 +1309,15 @@ flb_status flb_modeq_run(const flb_modeq_params* p, void* f, void* tmp, uint64_t
             xi = (char*)modeq_fields(a, work, nb);
             HIP_TRY(launch_modeq_noise(a, p->precision, (uint32_t)(step0 + k0), nb, work, xi, st));
         }
-        for (int b = 0; b < nb; ++b) {
-            const int32_t k = k0 + b;
-            const void* in = (k % 2 == 0) ? f : tmp;
-            void* out = (k % 2 == 0) ? tmp : f;
-            HIP_TRY(launch_modeq_step(a, p->precision, in, out, (uint32_t)(step0 + k),
+        for (int b = 0, n; b < nb; b += n) {
+            n = b + T <= nb ? T : 1;
+            HIP_TRY(launch_modeq_step(a, p->precision, n, in, out, (uint32_t)(step0 + k0 + b),
                                       xi ? xi + (size_t)b * 2 * V * rsize : nullptr, st));
+            std::swap(in, out);
         }
     }
-    if (nsteps % 2) {
-        const size_t bytes = (size_t)9 * a.nx * a.ny * (p->precision == FLB_FP64 ? 8 : 4);
-        HIP_TRY(hipMemcpyAsync(f, tmp, bytes, hipMemcpyDeviceToDevice, st));
-    }
+    if (in != f)
+        HIP_TRY(hipMemcpyAsync(f, tmp, (size_t)9 * V * rsize, hipMemcpyDeviceToDevice, st));
     return FLB_OK;
 }
 

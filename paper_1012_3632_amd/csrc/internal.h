@@ -173,8 +173,10 @@ hipError_t launch_modeq_noise(const ModEqArgs& a, int prec, uint32_t step0, int 
 // Moment fields of the pulled populations, FP64, m[a * V + site].
 hipError_t launch_modeq_moments(const ModEqArgs& a, int prec, const void* fin, double* m,
                                 hipStream_t st);
-// One step; xi = that step's filtered fields, or null for kT = 0.
-hipError_t launch_modeq_step(const ModEqArgs& a, int prec, const void* fin, void* fout,
+// T steps in one launch (T = 1 or modeq_steps(a)); xi: the filtered fields of
+// the first, those of step s at xi + 2 V s, or null for kT = 0.
+int modeq_steps(const ModEqArgs& a);
+hipError_t launch_modeq_step(const ModEqArgs& a, int prec, int T, const void* fin, void* fout,
                              uint32_t step, const void* xi, hipStream_t st);
 
 // Adjoint launchers (adjoint.hip).

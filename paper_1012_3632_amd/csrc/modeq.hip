@@ -42,10 +42,11 @@
 // state's precision (R = float or double; twiddles and Cholesky factors formed
 // in FP64 and rounded once).  Then k_meq_step applies the step.
 //
-// 1024^2 FP32, per step of a 16-step launch: rows 7.4 us (mostly the Philox
+// 1024^2 FP32, noise per step of a 16-step launch: rows 7.4 us (mostly the Philox
 // normals), columns 10.6 us, rows back 6.0 us; 11.6, 20.3 and 11.6 us with two
-// full spectra.  200 x 150 FP64, whole step with its noise: 11.3 us, 31 us when
-// extents that are not powers of two took n^2 direct sums.
+// full spectra.  200 x 150 FP64, noise and one step per launch: 11.3 us, 31 us
+// when extents that are not powers of two took n^2 direct sums; 7.0 us with
+// several steps per launch (modeq_steps).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -61,7 +62,6 @@ namespace {
 
 constexpr int MQ_THREADS = 1024;     // of the staged line transforms, at most
 constexpr int MQ_P2_THREADS = 256;   // of the in-place power-of-two passes
-constexpr int MQ_TX = 64, MQ_TY = 4;
 
 // tw[j] = exp(-2 pi i j / n), evaluated in FP64 and rounded to R.
 template <typename R>
@@ -436,99 +436,178 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_ix(ModEqArgs a, FftPla
     }
 }
 
-__device__ __forceinline__ int wrap(int v, int n) {
-    v %= n;
-    return v < 0 ? v + n : v;
-}
+// T steps in one launch on tiles of TX x TY sites (as multistep.h does for the
+// force-based fluid): step s is computed on the tile plus a halo of 2 (T - 1 -
+// s) sites, two being the reach of a step (a pull and the density's
+// neighbours), and its populations stay in LDS for step s + 1.
+template <int T, int TX, int TY>
+struct MeqTile {
+    static constexpr int w(int s) { return TX + 4 * (T - 1 - s); }
+    static constexpr int h(int s) { return TY + 4 * (T - 1 - s); }
+    static constexpr int NT = (w(0) * h(0) + 63) / 64 * 64;
+    static constexpr int NR = (w(0) + 2) * (h(0) + 2);
+    static constexpr int NS0 = T > 1 ? 9 * w(0) * h(0) : 1;
+    static constexpr int NS1 = T > 2 ? 9 * w(1) * h(1) : 1;
+};
 
-template <typename Real>
-__global__ __launch_bounds__(MQ_TX * MQ_TY) void k_meq_step(ModEqArgs a, Geom g,
-                                                            const Real* __restrict__ fin,
-                                                            Real* __restrict__ fout,
-                                                            uint32_t step,
-                                                            const Real* __restrict__ xi) {
+template <typename Real, int T, int TX, int TY, int S>
+struct MeqStep {
     using L = Lattice<0>;
-    constexpr int SX = MQ_TX + 2, NS = SX * (MQ_TY + 2);
-    constexpr int NRING = NS - MQ_TX * MQ_TY;   // halo sites: two rows of SX, two columns of TY
-    static_assert(NRING <= MQ_TX * MQ_TY, "one halo site per thread at most");
-    __shared__ Real rs[NS];
-    const int x0 = blockIdx.x * MQ_TX, y0 = blockIdx.y * MQ_TY;
-    const int tx = threadIdx.x % MQ_TX, ty = threadIdx.x / MQ_TX;
-    const int x = x0 + tx, y = y0 + ty;
-    // density of the pulled populations on the tile and a one-site halo: each
-    // thread pulls its own site (periodic image for a ragged edge) and keeps
-    // the populations, the first NRING threads pull the halo ring
-    Real f[L::Q];
-    pull<0, Real>(fin, wrap(x, g.nx), wrap(y, g.ny), 0, g, f);
-    {
-        Real s = Real(0);
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) s += f[i];
-        rs[(ty + 1) * SX + tx + 1] = s;
+    using MT = MeqTile<T, TX, TY>;
+    using M = Moments<0, Real>;
+    static constexpr int W = MT::w(S), HH = MT::h(S), N = W * HH, Q = L::Q, NT = MT::NT;
+    static constexpr int B = 2 * (T - 1 - S), SX = W + 2;
+
+    static __device__ __forceinline__ bool place(const Geom& g, int x0, int y0, int& lx, int& ly,
+                                                 int& x, int& y) {
+        const int l = (int)threadIdx.x;
+        ly = l / W;
+        lx = l - ly * W;
+        x = wrap_any(x0 - B + lx, g.nx);
+        y = wrap_any(y0 - B + ly, g.ny);
+        return l < N;
     }
-    if (threadIdx.x < NRING) {
-        const int r = threadIdx.x;
-        int lx, ly;
-        if (r < SX) {
-            lx = r;
-            ly = 0;
-        } else if (r < 2 * SX) {
-            lx = r - SX;
-            ly = MQ_TY + 1;
-        } else {
-            const int c = r - 2 * SX;   // 0 .. 2 TY - 1
-            lx = c < MQ_TY ? 0 : SX - 1;
-            ly = 1 + (c < MQ_TY ? c : c - MQ_TY);
+    // the site's normals z_1 .. z_4 and its filtered noise
+    static __device__ __forceinline__ void draw(const ModEqArgs& a, const Geom& g, int x0, int y0,
+                                                uint32_t step, const Real* __restrict__ xi,
+                                                const double2* tab, Real (&z)[6]) {
+        int lx, ly, x, y;
+        if (!xi || !place(g, x0, y0, lx, ly, x, y)) return;
+        const uint32_t site = (uint32_t)(x + g.nx * y);
+        const Real* f = xi + (size_t)S * 2 * g.V;
+        const Real e = f[site], p = f[g.V + site];
+        site_normals<3, Real>(site, step + S, 0u, 0u, a.k0, a.k1, z, tab);
+        z[0] = e;
+        z[5] = p;
+    }
+    // f: the site's streamed populations; rs: with S = 0, the density on the
+    // region and a one-site ring; src (S > 0): the populations of step S - 1,
+    // whose region is two sites wider
+    static __device__ __forceinline__ void run(const ModEqArgs& a, const Geom& g, int x0, int y0,
+                                               const Real* src, Real* dst, Real* rs, Real (&f)[Q],
+                                               const Real* z, bool noise,
+                                               Real* __restrict__ fout) {
+        constexpr int PW = W + 4, PN = PW * (HH + 4);
+        int lx, ly, x, y;
+        const bool in = place(g, x0, y0, lx, ly, x, y);
+        if constexpr (S > 0) {
+            auto pulled = [&](int px, int py, Real (&h)[Q]) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    h[i] = src[i * PN + (py - L::cy[i]) * PW + px - L::cx[i]];
+            };
+            if (in) pulled(lx + 2, ly + 2, f);
+            for (int l = threadIdx.x; l < SX * (HH + 2); l += NT) {
+                const int ry = l / SX, rx = l - ry * SX;
+                Real h[Q], acc = Real(0);
+                pulled(rx + 1, ry + 1, h);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) acc += h[i];
+                rs[l] = acc;
+            }
+            __syncthreads();
         }
-        Real h[L::Q];
-        pull<0, Real>(fin, wrap(x0 - 1 + lx, g.nx), wrap(y0 - 1 + ly, g.ny), 0, g, h);
+        if (!in) return;
+        Real m[Q];
+        M::forward(f, m);
+        const int c = (ly + 1) * SX + lx + 1;
+        Real lap = Real(0);
+#pragma unroll
+        for (int i = 1; i < Q; ++i)
+            lap += Real(L::w[i]) * (rs[c + L::cy[i] * SX + L::cx[i]] - rs[c]);
+        lap *= Real(6);
+        const Real D = Real(6.0 * (a.cs2_0 - 1.0 / 3.0)) * m[0] - Real(6.0 * a.kappa * a.rho0) * lap;
+        const Real le = Real(a.rate_bulk), ls = Real(a.rate_shear), lg = Real(a.rate_ghost);
+        m[3] -= le * (m[3] - D);
+        m[4] -= ls * m[4];
+        m[5] -= ls * m[5];
+        m[6] -= lg * m[6];
+        m[7] -= lg * m[7];
+        m[8] -= lg * (m[8] + D);
+        if (noise) {
+            m[3] += z[0];
+            m[4] += Real(a.amp[0]) * z[1];
+            m[5] += Real(a.amp[1]) * z[2];
+            m[6] += Real(a.amp[2]) * z[3];
+            m[7] += Real(a.amp[3]) * z[4];
+            m[8] += z[5];
+        }
+        M::inverse(m, f);
+        if constexpr (S + 1 < T) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) dst[i * N + (int)threadIdx.x] = f[i];
+        } else if (x0 + lx < g.nx && y0 + ly < g.ny) {
+            const uint32_t site = (uint32_t)(x + g.nx * y);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) plane_st(fout + (size_t)i * g.V, site, f[i]);
+        }
+    }
+};
+
+template <typename Real, int T, int TX, int TY>
+__global__ __launch_bounds__((MeqTile<T, TX, TY>::NT)) void k_meq_step(
+    ModEqArgs a, Geom g, const Real* __restrict__ fin, Real* __restrict__ fout, uint32_t step,
+    const Real* __restrict__ xi) {
+    using L = Lattice<0>;
+    using MT = MeqTile<T, TX, TY>;
+    using S0 = MeqStep<Real, T, TX, TY, 0>;
+    constexpr int Q = L::Q, SX = S0::SX, SY = S0::HH + 2;
+    constexpr int NRING = MT::NR - S0::N;   // two rows of SX, two columns of HH
+    static_assert(NRING <= MT::NT, "one ring site per thread at most");
+    __shared__ Real rs[MT::NR];
+    __shared__ Real s0[MT::NS0];
+    __shared__ Real s1[MT::NS1];
+    const uint32_t lin = xcd_remap(blockIdx.x, g.nblocks);
+    const int by = (int)(lin / (uint32_t)g.nbx);
+    const int x0 = (int)(lin - (uint32_t)by * (uint32_t)g.nbx) * TX, y0 = by * TY;
+    // density of the pulled populations on the region and a one-site ring:
+    // each thread pulls its own site (a periodic image past a ragged edge) and
+    // keeps the populations, the first NRING threads pull the ring
+    int lx, ly, x, y;
+    const bool in = S0::place(g, x0, y0, lx, ly, x, y);
+    Real f[Q], h[Q];
+    if (in) pull<0, Real>(fin, x, y, 0, g, f);
+    int rx = 0, ry = 0;
+    if ((int)threadIdx.x < NRING) {
+        const int r = (int)threadIdx.x;
+        if (r < 2 * SX) {
+            rx = r < SX ? r : r - SX;
+            ry = r < SX ? 0 : SY - 1;
+        } else {
+            const int c = r - 2 * SX;   // 0 .. 2 HH - 1
+            rx = c < S0::HH ? 0 : SX - 1;
+            ry = 1 + (c < S0::HH ? c : c - S0::HH);
+        }
+        pull<0, Real>(fin, wrap_any(x0 - S0::B - 1 + rx, g.nx), wrap_any(y0 - S0::B - 1 + ry, g.ny), 0,
+                      g, h);
+    }
+    const double2* tab = noise_table<Real, MT::NT>();
+    Real z[T][6];   // drawn while the populations are in flight
+    S0::draw(a, g, x0, y0, step, xi, tab, z[0]);
+    if constexpr (T > 1) MeqStep<Real, T, TX, TY, 1>::draw(a, g, x0, y0, step, xi, tab, z[1]);
+    if constexpr (T > 2) MeqStep<Real, T, TX, TY, 2>::draw(a, g, x0, y0, step, xi, tab, z[2]);
+    if (in) {
         Real s = Real(0);
 #pragma unroll
-        for (int i = 0; i < L::Q; ++i) s += h[i];
-        rs[ly * SX + lx] = s;
+        for (int i = 0; i < Q; ++i) s += f[i];
+        rs[(ly + 1) * SX + lx + 1] = s;
+    }
+    if ((int)threadIdx.x < NRING) {
+        Real s = Real(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) s += h[i];
+        rs[ry * SX + rx] = s;
     }
     __syncthreads();
-    if (x >= g.nx || y >= g.ny) return;
-    Real m[L::Q];
-#pragma unroll
-    for (int q = 0; q < L::Q; ++q) {
-        Real s = Real(0);
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i)
-            if (L::T[q][i] != 0) s += Real(L::T[q][i]) * f[i];
-        m[q] = s;
+    const bool noise = xi != nullptr;
+    S0::run(a, g, x0, y0, nullptr, s0, rs, f, z[0], noise, fout);
+    if constexpr (T > 1) {
+        __syncthreads();
+        MeqStep<Real, T, TX, TY, 1>::run(a, g, x0, y0, s0, s1, rs, f, z[1], noise, fout);
     }
-    const int c = (ty + 1) * SX + tx + 1;
-    Real lap = Real(0);
-#pragma unroll
-    for (int i = 1; i < L::Q; ++i) lap += Real(L::w[i]) * (rs[c + L::cy[i] * SX + L::cx[i]] - rs[c]);
-    lap *= Real(6);
-    const Real D = Real(6.0 * (a.cs2_0 - 1.0 / 3.0)) * m[0] - Real(6.0 * a.kappa * a.rho0) * lap;
-    const Real le = Real(a.rate_bulk), ls = Real(a.rate_shear), lg = Real(a.rate_ghost);
-    m[3] -= le * (m[3] - D);
-    m[4] -= ls * m[4];
-    m[5] -= ls * m[5];
-    m[6] -= lg * m[6];
-    m[7] -= lg * m[7];
-    m[8] -= lg * (m[8] + D);
-    const uint32_t site = (uint32_t)(x + g.nx * y);
-    if (xi) {
-        Real z[6];
-        site_normals<3, Real>(site, step, 0u, 0u, a.k0, a.k1, z);
-        m[3] += xi[site];
-        m[4] += Real(a.amp[0]) * z[1];
-        m[5] += Real(a.amp[1]) * z[2];
-        m[6] += Real(a.amp[2]) * z[3];
-        m[7] += Real(a.amp[3]) * z[4];
-        m[8] += xi[g.V + site];
-    }
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) {
-        Real s = Real(0);
-#pragma unroll
-        for (int q = 0; q < L::Q; ++q)
-            if (L::T[q][i] != 0) s += Real(L::T[q][i] / L::N[q]) * m[q];
-        plane_st(fout + (size_t)i * g.V, site, Real(L::w[i]) * s);
+    if constexpr (T > 2) {
+        __syncthreads();
+        MeqStep<Real, T, TX, TY, 2>::run(a, g, x0, y0, s1, s0, rs, f, z[2], noise, fout);
     }
 }
 
@@ -643,27 +722,53 @@ hipError_t launch_modeq_noise(const ModEqArgs& a, int prec, uint32_t step0, int 
     return launch_noise_t<double>(a, step0, nb, W, (double*)xi, st);
 }
 
-hipError_t launch_modeq_step(const ModEqArgs& a, int prec, const void* fin, void* fout,
-                             uint32_t step, const void* xi, hipStream_t st) {
-    const size_t V = (size_t)a.nx * a.ny;
+namespace {
+
+template <typename Real, int T, int TX, int TY>
+hipError_t step_tile(const ModEqArgs& a, const void* fin, void* fout, uint32_t step,
+                     const void* xi, hipStream_t st) {
     Geom g{};
     g.nx = a.nx;
     g.ny = a.ny;
     g.nz = 1;
-    g.nbx = (a.nx + MQ_TX - 1) / MQ_TX;
-    g.nby = (a.ny + MQ_TY - 1) / MQ_TY;
+    g.nbx = (a.nx + TX - 1) / TX;
+    g.nby = (a.ny + TY - 1) / TY;
     g.nbz = 1;
     g.nblocks = (uint32_t)(g.nbx * g.nby);
-    g.V = (uint32_t)V;
-    g.zc = 0;
-    const dim3 grid((unsigned)g.nbx, (unsigned)g.nby);
-    if (prec == 0)
-        hipLaunchKernelGGL(k_meq_step<float>, grid, dim3(MQ_TX * MQ_TY), 0, st, a, g,
-                           (const float*)fin, (float*)fout, step, (const float*)xi);
-    else
-        hipLaunchKernelGGL(k_meq_step<double>, grid, dim3(MQ_TX * MQ_TY), 0, st, a, g,
-                           (const double*)fin, (double*)fout, step, (const double*)xi);
+    g.V = (uint32_t)((size_t)a.nx * a.ny);
+    hipLaunchKernelGGL((k_meq_step<Real, T, TX, TY>), dim3(g.nblocks),
+                       dim3(MeqTile<T, TX, TY>::NT), 0, st, a, g, (const Real*)fin, (Real*)fout, step,
+                       (const Real*)xi);
     return hipGetLastError();
+}
+
+template <typename Real>
+hipError_t launch_step_t(const ModEqArgs& a, int T, const void* fin, void* fout, uint32_t step,
+                         const void* xi, hipStream_t st) {
+    if (T == 1) return step_tile<Real, 1, 64, 4>(a, fin, fout, step, xi, st);
+    if (T == 2) return step_tile<Real, 2, 16, 16>(a, fin, fout, step, xi, st);
+    if (T == 3) return step_tile<Real, 3, 8, 8>(a, fin, fout, step, xi, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// us per step with its noise, one step per launch -> T = 2 on 16 x 16 tiles ->
+// T = 3 on 8 x 8 tiles: 128^2 FP32 4.97 -> 4.04 -> 3.64, 200 x 150 FP64 8.96 ->
+// 6.97 -> 6.95, 256^2 FP32 6.52 -> 5.40 -> 5.73, 1024^2 FP32 44.2 -> 42.2 -> 47.3.
+// So three steps while the chip is far from full, two otherwise, unless the
+// tiles of a strip cover far more than its sites.
+int modeq_steps(const ModEqArgs& a) {
+    auto tiled = [&](size_t t) { return (a.nx + t - 1) / t * ((a.ny + t - 1) / t) * t * t; };
+    const size_t V = (size_t)a.nx * a.ny;
+    if (tiled(8) <= 32768) return 3;
+    return tiled(16) <= 65536 || 4 * tiled(16) <= 5 * V ? 2 : 1;
+}
+
+hipError_t launch_modeq_step(const ModEqArgs& a, int prec, int T, const void* fin, void* fout,
+                             uint32_t step, const void* xi, hipStream_t st) {
+    return prec == 0 ? launch_step_t<float>(a, T, fin, fout, step, xi, st)
+                     : launch_step_t<double>(a, T, fin, fout, step, xi, st);
 }
 
 }  // namespace flb

@@ -89,3 +89,25 @@ def test_multi_step_recompute_same_gradient(nx, ny, every, precision):
         out.append((abar, grad))
     assert torch.equal(out[0][0], out[1][0])
     np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("kT", [0.0, 1e-6])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 5), (9, 7), (24, 40), (130, 61), (200, 190), (250, 257),
+                                   (1024, 3), (400, 330)])
+def test_modeq_steps_per_launch_same_bits(nx, ny, kT, precision):
+    """A run, several steps per launch with leftovers and batch ends, equals
+    single flb_modeq_step calls."""
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    p = ModEqParams(nx=nx, ny=ny, precision=precision, kT=kT, cs2_0=0.265 ** 2, kappa=0.08,
+                    rate_bulk=1.2, rate_shear=1.6, rate_ghost=0.9, seed=8)
+    f0 = W.random_populations(9, (ny, nx), 5, 1e-3)
+    a, b = ModEq(p, f0=f0), ModEq(p, f0=f0)
+    fin, fout = b.f.clone(), b.f.clone()
+    n = 0
+    for k in (1, 2, 3, 4, 5, 19):
+        a.step(k)
+        for _ in range(k):
+            b.step_into(fin, fout, n)
+            fin, fout, n = fout, fin, n + 1
+        assert torch.equal(a.f, fin), n
