@@ -496,7 +496,9 @@ flb_status flb_batch_destroy(flb_batch* b);
  * Until then a handle uses, for the ideal gas, the flat shapes (15, and 16 for
  * pairs unless one population buffer exceeds 400 MiB; shape 0 where a box is
  * past their 32-bit offsets), for D2Q9 force steps shape 4 (32 x 8, forming its
- * own density tile) and for D3Q19 force steps shape 0.
+ * own density tile) and for D3Q19 force steps the flat shape 12 (shape 3, a
+ * z-march, past 12 million sites with rows of 64 or more; shape 0 where a box
+ * is past the flat shape's 32-bit offsets).
  * Small D2Q9 lattices (at most 2^18 sites in FP32, less in FP64 and with
  * statistics) take two to four steps per launch, with the bits of as many
  * ordinary steps in populations and noise (statistics are summed in another
@@ -518,7 +520,7 @@ flb_status flb_launch_configs(const flb_handle* h, int32_t* count, int32_t* curr
  * populations itself (no density pass before it; D2Q9), 2 for a z-marching
  * force step that forms the next step's density (D3Q19, FP32; in FP64 such a
  * shape runs the plain march of its tile), 3 for a flat shape (blocks of 256
- * consecutive sites, ideal gas). */
+ * consecutive sites). */
 flb_status flb_launch_shape(const flb_handle* h, int32_t config, int32_t* shape);
 /* The same for a batch: there is one grid, a block per tile, so best[2] is 0;
  * best_ms[2] as for flb_autotune.  It then

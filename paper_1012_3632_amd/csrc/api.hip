@@ -154,7 +154,8 @@ struct flb_handle {
     // scratch regions
     unsigned long long* step_dev;
     void* drho;             // V reals (force model)
-    void* rho_part;         // V reals: the march's partial next density (D3Q19 force, FP32)
+    void* rho_part;         // D3Q19 force: the march's partial next density (FP32) or the
+                            // flat shape's chemical potential
     void* adj_work;
     double* gpartial;       // adjoint gradient partials
     uint32_t gslots;
@@ -179,14 +180,36 @@ void scratch_layout(const StepSpec& s, size_t V, size_t rb, size_t* drho_off, si
     size_t off = SCRATCH_HEADER;
     *drho_off = off;
     off += align_up(V * rb);
-    // the partial-density march's output (D3Q19 force steps in FP32)
+    // the partial-density march's output, or the flat force shape's chemical
+    // potential (D3Q19 force steps)
     *part_off = off;
-    off += align_up(partial_density_bytes(s));
+    off += align_up(force_work_bytes(s));
     *adj_off = off;
     off += align_up(adjoint_work_bytes(s));
     *gpart_off = off;
     off += align_up(((size_t)adjoint_slots(s) + 1) * 4 * sizeof(double));
     *total = off;
+}
+
+// The untuned shape of D3Q19 force steps: flat, past 12 M sites and from 64
+// sites per row up the 64 x 4 march, whose columns then fill the chip.  us per
+// step with statistics, FP32 (FP64) unless noted, 32 x 4 x 2 tile / march / flat:
+// 16^3 12.8 / 52 / 10.9; 101 x 77 x 53 38 (81) / 58 (95) / 26 (50); 700 x 40 x 40
+// 73 / 80 / 53; 128^3 141 (330) / 109 (244) / 109 (254); 200^3 546 (1282) / 505
+// (1075) / 431 (891); 256^3 981 (2759) / 768 (1847) / 837 (1946); 320 x 256 x 256
+// 1280 / 1020 / 1275.
+int force3_default(const StepSpec& s) {
+    if ((uint64_t)s.nx * s.ny * s.nz > 12000000ull && s.nx >= 64) return 3;
+    return flat_fits(s) ? FLAT_FORCE_CFG : 0;
+}
+
+// The work field launch_step needs for shape cfg, or null (pd false: partial-
+// density shapes run as plain marches).
+void* step_work(const flb_handle* h, int cfg, bool pd = true) {
+    const StepSpec& s = h->spec;
+    return (pd && config_partial_density(s, cfg)) ||
+                   (s.force && config_shape(s.lat, s.force, cfg).fl)
+               ? h->rho_part : nullptr;
 }
 
 // One forward step of the handle: cur -> other, then swap.  drho_ready: the
@@ -199,7 +222,7 @@ flb_status do_step(flb_handle* h, bool sample, const unsigned long long* step_de
     if (h->spec.force && !config_fused(h->spec, cfg) && !(pd && *drho_ready))
         HIP_TRY(launch_density(h->spec, h->cur(), h->drho, st));
     HIP_TRY(launch_step(h->spec, cfg, h->cur(), h->other(), h->drho, step_dev, step_host,
-                        sample ? h->stats : nullptr, st, nullptr, pd ? h->rho_part : nullptr));
+                        sample ? h->stats : nullptr, st, nullptr, step_work(h, cfg)));
     if (pd) HIP_TRY(launch_density_fix(h->spec, cfg, h->other(), h->rho_part, h->drho, st));
     *drho_ready = pd;
     h->cur_a = !h->cur_a;
@@ -349,8 +372,9 @@ flb_status flb_init(const flb_params* p, void* f_a, void* f_b, void* scratch, vo
     // shapes: pairs in place while one population buffer is not far above the
     // 256 MB last-level cache (176 x 150 x 140: FP32, 281 MB, 121 us in pairs and
     // 134 between two buffers; FP64, 562 MB, 268 and 250)
-    const bool flat = flat_fits(h->spec);
-    h->cfg = h->cfg_stats = h->spec.force ? (h->spec.lat == 0 ? 4 : 0) : (flat ? FLAT_CFG : 0);
+    const bool flat = !h->spec.force && flat_fits(h->spec);
+    h->cfg = h->cfg_stats = h->spec.force ? (h->spec.lat == 0 ? 4 : force3_default(h->spec))
+                                          : (flat ? FLAT_CFG : 0);
     h->pair_cfg = flat && (size_t)h->q * h->V * h->real_bytes <= (size_t)400 << 20 ? FLAT_PAIR_CFG : -1;
     h->multi[0] = h->multi[1] = true;
     h->graph[0] = h->graph[1] = nullptr;
@@ -659,7 +683,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     // row tiles that a ragged box leaves more than a fifth empty lose to the
     // flat shapes wherever those fit (101 x 77 x 53: 14.6 against 11.8 us) and
     // are not timed
-    const bool flat = flat_fits(h->spec);
+    const bool flat = !h->spec.force && flat_fits(h->spec);
     auto sparse = [&](int c) {
         const TileShape t = config_shape(h->spec.lat, h->spec.force, c);
         return flat && !t.fl &&
@@ -696,7 +720,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
                     if (r != hipSuccess) return r;
                 }
                 hipError_t r = launch_step(h->spec, c, in, out, h->drho, nullptr, h->step, part, st,
-                                           nullptr, pd ? h->rho_part : nullptr);
+                                           nullptr, step_work(h, c));
                 if (r == hipSuccess && pd)
                     r = launch_density_fix(h->spec, c, out, h->rho_part, h->drho, st);
                 return r;
@@ -932,7 +956,7 @@ flb_status seg_recompute(const SegWork& sw, uint64_t k0, hipStream_t st) {
     for (size_t j = 1; j < sw.k; ++j) {
         HIP_TRY(launch_step(h->spec, h->cfg, sw.state(j - 1), (void*)sw.state(j),
                             sw.density(j - 1), nullptr, (unsigned long long)(k0 + j - 1), nullptr,
-                            st));
+                            st, nullptr, step_work(h, h->cfg, false)));
         if (h->spec.force) HIP_TRY(launch_density(h->spec, sw.state(j), sw.density(j), st));
     }
     return FLB_OK;

@@ -108,14 +108,31 @@ struct FlatBox {
     uint32_t V, inv_nx, inv_ny;   // the inverses of div_small
 };
 
-// One ideal-gas step of site s: KIND 0 from fin to fout, 1 and 2 the phases of
-// an in-place pair (fin == fout).  With STATS the site's moments and their
-// squares are added to v.
-template <int LAT, typename Real, bool STATS, int KIND>
+// One plane of V reals as a buffer resource.
+template <typename Real>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const Real* p, uint32_t V) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<Real*>(p), 0,
+                                             (int)(V * (uint32_t)sizeof(Real)), 0x00020000);
+}
+
+// The density and chemical potential fields of a force step.
+template <typename Real>
+struct FlatForce {
+    const Real* drho;
+    const Real* mu;
+    ForceParams<Real> fp;
+};
+
+// One step of site s: KIND 0 from fin to fout, 1 and 2 the phases of an
+// in-place pair (fin == fout).  With STATS the site's moments and their
+// squares are added to v.  FORCE (KIND 0): F = -rho grad_h mu + eta cs2 grad_h
+// rho from the fields of ff (the sums of ForceTile::force).
+template <int LAT, typename Real, bool STATS, int KIND, bool FORCE = false>
 __device__ __forceinline__ void flat_site(const Real* fin, Real* fout, uint32_t s, const FlatBox& B,
                                           const CollideParams<Real>& P, uint32_t replica,
                                           uint32_t key0, uint32_t key1, uint32_t step,
-                                          const double2* tab, Real* v) {
+                                          const double2* tab, Real* v,
+                                          const FlatForce<Real>& ff = FlatForce<Real>()) {
     using L = Lattice<LAT>;
     using M = Moments<LAT, Real>;
     constexpr int Q = L::Q, D = L::D;
@@ -136,6 +153,27 @@ __device__ __forceinline__ void flat_site(const Real* fin, Real* fout, uint32_t 
 #pragma unroll
         for (int i = 0; i < Q; ++i) f[i] = rep_ld(in, Vr, L::opp[i], se, Real(0));
     }
+    Real F[D] = {};
+    if constexpr (FORCE) {
+        const Nbr<Real> nb(s, x, y, (int)z, B.nx, B.ny, B.nz, B.V);
+        const __amdgpu_buffer_rsrc_t mu = plane_rsrc(ff.mu, B.V), dr = plane_rsrc(ff.drho, B.V);
+        Real gm[D] = {}, gr[D] = {};
+        auto grad = [&](__amdgpu_buffer_rsrc_t field, Real (&o)[D]) {
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                const Real w = rep_ld(field, 0u, 0, nb.at(L::cx[i], L::cy[i], L::cz[i]), Real(0));
+                const int c3[3] = {L::cx[i], L::cy[i], L::cz[i]};
+#pragma unroll
+                for (int a = 0; a < D; ++a)
+                    if (c3[a] != 0) o[a] += Real(L::w[i] * c3[a]) * w;
+            }
+        };
+        grad(mu, gm);
+        if (ff.fp.eta != Real(0)) grad(dr, gr);   // uniform
+        const Real rho = P.rho0 + rep_ld(dr, 0u, 0, se, Real(0));
+#pragma unroll
+        for (int a = 0; a < D; ++a) F[a] = -rho * Real(3) * gm[a] + ff.fp.eta * gr[a];
+    }
     M::forward(f, m);
     if constexpr (STATS) {
 #pragma unroll
@@ -146,8 +184,7 @@ __device__ __forceinline__ void flat_site(const Real* fin, Real* fout, uint32_t 
     }
     Real zn[2 * L::NPAIR];
     if (P.noise_on) site_normals<L::NPAIR, Real>(s, step, 0u, replica, key0, key1, zn, tab);
-    const Real F[D] = {};
-    collide_moments<LAT, Real, false>(m, F, zn, P);
+    collide_moments<LAT, Real, FORCE>(m, F, zn, P);
     M::inverse(m, f);
     uint32_t Vs = Vr;   // the store offsets are not those of the loads
     asm volatile("" : "+s"(Vs));

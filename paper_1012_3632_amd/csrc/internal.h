@@ -19,8 +19,9 @@ struct TileShape {
                       //    density from its own sources (FP32), completed by
                       //    launch_density_fix (no density pass between steps)
     int fl;           // 1: a block takes 256 consecutive sites in storage order (ideal
-                      //    gas; flat.h), so ragged rows leave no lane idle; boxes
-                      //    past its 32-bit offsets run the 256 x 1 tile
+                      //    gas, D3Q19 force; flat.h), so ragged rows leave no lane
+                      //    idle; boxes past its 32-bit offsets run the 256 x 1
+                      //    (force: 16 x 4 x 4) tile
 };
 
 // Candidate tiles (the autotuner picks one per handle).
@@ -32,13 +33,14 @@ constexpr TileShape IDEAL_CFG[N_IDEAL_CFG] = {
     {128, 2, 1, 1, 1}, {256, 1, 1, 1, 1}, {128, 2, 1, 1, 0, 0, 1}, {64, 4, 1, 1, 0, 0, 1},
     {256, 1, 1, 1, 0, 0, 1}, {128, 2, 1, 2, 0, 0, 1}, {64, 4, 1, 2, 0, 0, 1},
     {256, 1, 1, 1, 0, 0, 0, 0, 0, 1}, {256, 1, 1, 1, 0, 0, 1, 0, 0, 1}};
-constexpr int N_FORCE3_CFG = 12;
+constexpr int N_FORCE3_CFG = 13;
+constexpr int FLAT_FORCE_CFG = 12;
 constexpr TileShape FORCE3_CFG[N_FORCE3_CFG] = {
     {32, 4, 2, 1, 0},     {16, 4, 4, 1, 0},     {64, 2, 2, 1, 0},
     {64, 4, 1, 1, 0, 16}, {64, 4, 1, 1, 0, 32}, {32, 8, 1, 1, 0, 16},
     {64, 8, 1, 1, 0, 16}, {128, 2, 1, 1, 0, 16}, {128, 2, 1, 1, 1, 16},
     {128, 2, 1, 1, 1, 16, 0, 0, 1}, {64, 4, 1, 1, 0, 16, 0, 0, 1},
-    {64, 8, 1, 1, 0, 16, 0, 0, 1}};
+    {64, 8, 1, 1, 0, 16, 0, 0, 1}, {256, 1, 1, 1, 0, 0, 0, 0, 0, 1}};
 constexpr int N_FORCE2_CFG = 6;
 constexpr TileShape FORCE2_CFG[N_FORCE2_CFG] = {
     {64, 4, 1, 1, 0},          {32, 8, 1, 1, 0},          {128, 2, 1, 1, 0},
@@ -74,7 +76,8 @@ hipError_t launch_density(const StepSpec& s, const void* fin, void* drho_out, hi
 // launch_density would write; ignored otherwise.
 // rho_part: for the partial-density shapes (config_partial_density), if
 // non-null, receives the part of fout's density that the march forms; null
-// runs the plain march of the same shape.
+// runs the plain march of the same shape.  The flat force shape takes the same
+// pointer as its work field (null: the 16 x 4 x 4 tile).
 hipError_t launch_step(const StepSpec& s, int cfg, const void* fin, void* fout, const void* drho,
                        const unsigned long long* step_dev, unsigned long long step_host,
                        double* partial, hipStream_t st, void* rho_out = nullptr,
@@ -83,9 +86,10 @@ hipError_t launch_step(const StepSpec& s, int cfg, const void* fin, void* fout, 
 // march's rho_part (the step fin was written by, same shape) and the
 // populations of fin whose sources lie outside the forming block.
 bool config_partial_density(const StepSpec& s, int cfg);
-// Bytes of the partial-density work area (the partial density and the
-// march's edge records; 0 where no shape forms a partial density).
-size_t partial_density_bytes(const StepSpec& s);
+// Bytes of the D3Q19 force steps' work area: in FP32 the partial density and
+// the march's edge records, of which the flat force shape uses V reals for the
+// chemical potential, in FP64 those V reals; else 0.
+size_t force_work_bytes(const StepSpec& s);
 hipError_t launch_density_fix(const StepSpec& s, int cfg, const void* fin, const void* rho_part,
                               void* out, hipStream_t st);
 // In-place shapes: one step of a pair on the single buffer f (phase 0 then 1;

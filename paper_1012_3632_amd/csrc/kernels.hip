@@ -317,11 +317,16 @@ __global__ __launch_bounds__(TX* TY) void k_step_ip(Real* f, Geom g, CollidePara
 // statistics, best row tile -> here (pairs): 128^3 FP32 53.1 -> 49.8, FP64 130
 // -> 122 (plain 126 -> 110), 120 x 100 x 90 FP64 70.5 -> 58.1, 101 x 77 x 53
 // FP32 14.6 -> 11.8, 17 x 120 x 90 FP32 10.9 -> 7.5.
-template <int LAT, typename Real, bool STATS, int KIND>
+// FORCE (KIND 0): the force from the density and chemical potential fields
+// of ff (k_density, k_mu_flat).  For lattices that the z-march cannot fill the
+// chip with: its blocks own 16-plane columns, and the tiles that form mu
+// themselves stage five densities and 2.5 chemical potentials per site.
+template <int LAT, typename Real, bool STATS, int KIND, bool FORCE = false>
 __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fout, Geom g,
                                                        uint32_t inv_nx, uint32_t inv_ny,
                                                        CollideParams<Real> P, StepIndex st,
-                                                       double* __restrict__ partial) {
+                                                       double* __restrict__ partial,
+                                                       FlatForce<Real> ff) {
     constexpr int Q = Lattice<LAT>::Q;
     __shared__ double lds_stats[STATS ? 4 * (FLAT_NT / 64) * 2 * Q : 1];
     const double2* tab = noise_table<Real, FLAT_NT>();
@@ -334,9 +339,35 @@ __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fo
         for (int k = 0; k < 2 * Q; ++k) v[k] = Real(0);
     }
     if (s < g.V)
-        flat_site<LAT, Real, STATS, KIND>(fin, fout, s, FlatBox{g.nx, g.ny, g.nz, g.V, inv_nx, inv_ny},
-                                          P, P.replica, P.key0, P.key1, step, tab, v);
+        flat_site<LAT, Real, STATS, KIND, FORCE>(
+            fin, fout, s, FlatBox{g.nx, g.ny, g.nz, g.V, inv_nx, inv_ny}, P, P.replica, P.key0,
+            P.key1, step, tab, v, ff);
     if constexpr (STATS) block_accumulate<2 * Q, FLAT_NT>(v, partial + (size_t)b * 2 * Q, lds_stats);
+}
+
+// mu = psi'(rho) - kappa lap_h rho of the density field (the sums of
+// ForceTile::mu_rows).
+template <int LAT, typename Real>
+__global__ __launch_bounds__(FLAT_NT) void k_mu_flat(const Real* __restrict__ drho,
+                                                     Real* __restrict__ mu, Geom g, uint32_t inv_nx,
+                                                     uint32_t inv_ny, ForceParams<Real> fp) {
+    using L = Lattice<LAT>;
+    const uint32_t s = xcd_remap(blockIdx.x, g.nblocks) * (uint32_t)FLAT_NT + threadIdx.x;
+    if (s >= g.V) return;
+    const uint32_t yz = div_small(s, inv_nx);
+    const uint32_t z = div_small(yz, inv_ny);
+    const Nbr<Real> nb(s, (int)(s - yz * (uint32_t)g.nx), (int)(yz - z * (uint32_t)g.ny), (int)z, g.nx,
+                       g.ny, g.nz, g.V);
+    const __amdgpu_buffer_rsrc_t r = plane_rsrc(drho, g.V);
+    const Real rc = rep_ld(r, 0u, 0, s * (uint32_t)sizeof(Real), Real(0));
+    Real lap = Real(0);
+#pragma unroll
+    for (int i = 1; i < L::Q; ++i)
+        lap += Real(L::w[i]) *
+               (rep_ld(r, 0u, 0, nb.at(L::cx[i], L::cy[i], L::cz[i]), Real(0)) - rc);
+    lap *= Real(6);   // 2 / cs2
+    const Real d = rc + fp.shift;
+    mu[s] = Real(2) * fp.a * d + Real(4) * fp.b * d * d * d - fp.kappa * lap;
 }
 
 // The next step's density formed inside the z-march.  After streaming, the
@@ -1027,7 +1058,7 @@ bool flat_fits(const StepSpec& s) {
     const uint64_t V = (uint64_t)s.nx * s.ny * s.nz;
     const uint64_t Q = s.lat == 0 ? 9 : 19, lim = 1ull << 32;
     // the populations as one buffer resource; s / nx and (s / nx) / ny exact
-    return !s.force && Q * V * (s.prec ? 8 : 4) < lim && (V - 1) * (uint64_t)s.nx < lim &&
+    return Q * V * (s.prec ? 8 : 4) < lim && (V - 1) * (uint64_t)s.nx < lim &&
            (V / s.nx - 1) * (uint64_t)s.ny < lim;
 }
 
@@ -1041,11 +1072,34 @@ static void flat_launch(const StepSpec& s, int kind, const void* fin, void* fout
     const uint32_t ix = (uint32_t)(((1ull << 32) + s.nx - 1) / s.nx);
     const uint32_t iy = (uint32_t)(((1ull << 32) + s.ny - 1) / s.ny);
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, block, 0, st, (const Real*)fin, (Real*)fout, g, ix, iy, P, si, partial);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, (const Real*)fin, (Real*)fout, g, ix, iy, P, si, partial,
+                           FlatForce<Real>());
     };
     if (kind == 0) partial ? go(k_step_flat<LAT, Real, true, 0>) : go(k_step_flat<LAT, Real, false, 0>);
     else if (kind == 1) partial ? go(k_step_flat<LAT, Real, true, 1>) : go(k_step_flat<LAT, Real, false, 1>);
     else partial ? go(k_step_flat<LAT, Real, true, 2>) : go(k_step_flat<LAT, Real, false, 2>);
+}
+
+// The force step of the same blocks: mu from the density drho into the work
+// field, then the step.
+template <typename Real>
+static void flat_force_launch(const StepSpec& s, const void* fin, void* fout, const void* drho,
+                              void* mu, StepIndex si, double* partial, hipStream_t st) {
+    Geom g = make_geom(s, TileShape{1, 1, 1, 1, 0, 0, 0});
+    g.nblocks = (g.V + FLAT_NT - 1) / FLAT_NT;
+    const dim3 grid(g.nblocks), block(FLAT_NT);
+    const CollideParams<Real> P = collide_params<Real>(s);
+    const uint32_t ix = (uint32_t)(((1ull << 32) + s.nx - 1) / s.nx);
+    const uint32_t iy = (uint32_t)(((1ull << 32) + s.ny - 1) / s.ny);
+    const FlatForce<Real> ff{(const Real*)drho, (const Real*)mu, force_params<Real>(s)};
+    hipLaunchKernelGGL((k_mu_flat<1, Real>), grid, block, 0, st, (const Real*)drho, (Real*)mu, g, ix,
+                       iy, ff.fp);
+    if (partial)
+        hipLaunchKernelGGL((k_step_flat<1, Real, true, 0, true>), grid, block, 0, st, (const Real*)fin,
+                           (Real*)fout, g, ix, iy, P, si, partial, ff);
+    else
+        hipLaunchKernelGGL((k_step_flat<1, Real, false, 0, true>), grid, block, 0, st, (const Real*)fin,
+                           (Real*)fout, g, ix, iy, P, si, partial, ff);
 }
 
 template <int LAT, typename Real>
@@ -1090,7 +1144,13 @@ static void step_dispatch(const StepSpec& s, int cfg, const void* fin, void* fou
             // the march also forms the next density (rho_part, completed by k_density_fix)
             case 9: step_march<Real, 128, 2, true>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
             case 10: step_march<Real, 64, 4>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
-            default: step_march<Real, 64, 8>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
+            case 11: step_march<Real, 64, 8>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
+            default:
+                if (flat_fits(s) && rho_part)
+                    flat_force_launch<Real>(s, fin, fout, drho, rho_part, si, partial, st);
+                else
+                    step_tile<LAT, Real, true, 16, 4, 4>(s, fin, fout, drho, si, partial, st);
+                break;
         }
     } else {
         switch (cfg) {
@@ -1144,8 +1204,9 @@ bool config_partial_density(const StepSpec& s, int cfg) {
            cfg < n_configs(s.lat, s.force) && config_shape(s.lat, s.force, cfg).pd;
 }
 
-size_t partial_density_bytes(const StepSpec& s) {
-    if (!(s.force && s.lat == 1 && s.prec == 0)) return 0;
+size_t force_work_bytes(const StepSpec& s) {
+    if (!(s.force && s.lat == 1)) return 0;
+    if (s.prec) return (size_t)s.nx * s.ny * s.nz * 8;
     return pd_layout(s.nx, s.ny, s.nz).total * 4;
 }
 

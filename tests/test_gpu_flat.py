@@ -58,3 +58,35 @@ def test_batch_of_thin_boxes():
         one.set_launch(0)
         one.step(5)
         assert torch.equal(b.replica_state(r), one.state()), n
+
+
+FORCE_BOXES = [(1, 1, 1), (1, 1, 300), (1, 7, 40), (9, 1, 31), (300, 1, 1), (17, 16, 1), (255, 2, 3),
+               (256, 3, 2), (257, 5, 3), (2, 2, 2), (33, 20, 7), (64, 4, 4)]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", FORCE_BOXES)
+def test_flat_force_shape(n, precision):
+    """The flat D3Q19 force shape (density, chemical potential and step as
+    three launches) against the 32 x 4 x 2 tile, with eta zero and one."""
+    from paper_1012_3632_amd import Simulation
+    tol = 1e-12 if precision == "fp64" else 5e-6   # as for every force shape against another
+    for eta in (0, 1):
+        p = gpu_params(lattice="D3Q19", precision=precision, nx=n[0], ny=n[1], nz=n[2], eta=eta,
+                       force_model=1, a=-0.01, b=0.1, rho_c=1.0, kappa=0.05, **dict(KW, kT=1e-6))
+        drho = W.initial_drho((n[2], n[1], n[0]), 9, 0.01)
+        sims = {}
+        for cfg in (0, 12):
+            sim = sims[cfg] = Simulation(p, drho_init=drho)
+            sim.set_launch(cfg)
+            for k, stride in ((1, 1), (4, 1), (3, 2), (2, 0)):
+                sim.step(k, stats_stride=stride)
+        assert sims[12].launch_shape(12)[7] == 3
+        a, b = sims[12].state().double(), sims[0].state().double()
+        assert float((a - b).abs().max()) <= tol * float(b.abs().max())
+        s0, q0, n0 = sims[0].moments()
+        s1, q1, n1 = sims[12].moments()
+        assert n1 == n0
+        # modes that a thin box leaves at rounding level have no scale of their own
+        assert np.all(np.abs(q1 - q0) <= 20 * tol * q0.max())
+        assert np.all(np.abs(s1 - s0) <= 20 * tol * np.sqrt(n0 * np.prod(n) * q0.max()))
