@@ -5,7 +5,7 @@
 // transform at (j / Ns) Ns r + j mod Ns + u Ns, Ns the product of the earlier
 // radices, so input and output are both in natural order.  n is split into
 // radices 8, 4, 2, 3 and 5 (in registers); a prime factor p >= 7 takes a stage
-// of direct p-term sums, so a prime n is one direct sum per output.
+// of direct sums (p / 2 term pairs for two outputs), before the others.
 // A line of n costs about n sum(r) complex multiply-adds instead of n^2.
 //
 // Two LDS buffers per line are alternated, one barrier per stage.  Element i
@@ -33,6 +33,13 @@ inline FftPlan fft_plan(int n) {
     FftPlan p{};
     p.n = n;
     int e = 0, m = n;
+    // direct sums first: the first stage needs no twiddles
+    for (int f = 7; f <= n; f += 2)
+        while (m % f == 0 && f % 3 != 0 && f % 5 != 0) {
+            p.radix[p.stages++] = f;
+            p.any = 1;
+            m /= f;
+        }
     while (m % 2 == 0) {
         m /= 2;
         ++e;
@@ -47,7 +54,6 @@ inline FftPlan fft_plan(int n) {
     for (int f = 3; m > 1; f += 2)
         while (m % f == 0) {
             p.radix[p.stages++] = f;
-            if (f > 5) p.any = 1;
             m /= f;
         }
     return p;
@@ -204,34 +210,71 @@ __device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>
     }
 }
 
-// Any radix: every output as a direct sum over its group.  tw: the n roots.
+// Any odd radix, of inputs that carry their twiddles already: outputs u and
+// rad - u as direct sums.  Inputs v and rad - v enter as their sum (cosines)
+// and difference (sines), which both outputs share: 4 multiply-adds and 3 LDS
+// reads for two inputs and two outputs, against 16 and 8 of plain sums.  The
+// reads are a serial chain when a line has few outputs per lane, so a line
+// of a large prime is bound by their latency.  Modified-equilibrium runs with
+// plain sums and one thread per four elements -> these and one per two: 32 x 71
+// FP32 5.4 -> 3.7 us a step, 101 x 53 6.0 -> 4.1, 127 x 131 11.3 -> 5.8 (FP64
+// 14.2 -> 7.9), 211 x 307 33 -> 19; the spectra of 19 fields of 101^3 take 857 us.
+// tw: the n roots.
 template <typename R, bool INV>
 __device__ __forceinline__ void fft_stage_any(const cx_t<R>* __restrict__ a,
                                               cx_t<R>* __restrict__ b,
                                               const cx_t<R>* __restrict__ tw, int NL, int n, int Ns,
                                               int rad) {
     using C = cx_t<R>;
+    const int m = n / rad, ld = fft_ld(n), h = rad / 2, w = m * (h + 1);
+    const float rw = 1.0f / (float)w, rm = 1.0f / (float)m, rN = 1.0f / (float)Ns;
+    for (int t = threadIdx.x; t < NL * w; t += blockDim.x) {
+        const int L = fft_div(t, rw), i = t - L * w;
+        const int u = fft_div(i, rm), j = i - u * m;     // outputs u and rad - u of group j
+        const int q = fft_div(j, rN), k = j - q * Ns;
+        const C* src = a + L * ld;
+        const int inc = u * m;                           // < n
+        const C x0 = src[fft_pos(j)];
+        R cr = x0.x, ci = x0.y, sr = R(0), si = R(0);
+        int idx = 0;
+#pragma unroll 4
+        for (int v = 1; v <= h; ++v) {
+            idx += inc;
+            if (idx >= n) idx -= n;
+            const C x = src[fft_pos(j + v * m)], y = src[fft_pos(j + (rad - v) * m)];
+            const C e = tw[idx];                         // (cos, -sin)
+            cr = fma(x.x + y.x, e.x, cr);
+            ci = fma(x.y + y.y, e.x, ci);
+            sr = fma(x.y - y.y, e.y, sr);
+            si = fma(x.x - y.x, e.y, si);
+        }
+        if (!INV) {
+            sr = -sr;
+            si = -si;
+        }
+        C* dst = b + L * ld;
+        const int o = q * Ns * rad + k;
+        dst[fft_pos(o + u * Ns)] = Cx<R>::make(cr + sr, ci - si);
+        if (u > 0) dst[fft_pos(o + (rad - u) * Ns)] = Cx<R>::make(cr - sr, ci + si);
+    }
+}
+
+// The twiddles of a stage of radix rad after Ns > 1, in place.  tw: the n roots.
+template <typename R, bool INV>
+__device__ __forceinline__ void fft_twist(cx_t<R>* a, const cx_t<R>* __restrict__ tw, int NL, int n,
+                                          int Ns, int rad) {
     const int m = n / rad, ld = fft_ld(n), ts = m / Ns;
     const float rn = 1.0f / (float)n, rm = 1.0f / (float)m, rN = 1.0f / (float)Ns;
     for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
         const int L = fft_div(t, rn), i = t - L * n;
-        const int u = fft_div(i, rm), j = i - u * m;     // output u of group j
-        const int q = fft_div(j, rN), k = j - q * Ns;
-        const C* src = a + L * ld;
-        const int inc = k * ts + u * m;                  // < n
-        R re = R(0), im = R(0);
-        int idx = 0;
-        for (int v = 0; v < rad; ++v) {
-            const C x = src[fft_pos(j + v * m)];
-            const C w = tw[idx];
-            const R wi = INV ? -w.y : w.y;
-            re = fma(x.x, w.x, fma(-x.y, wi, re));
-            im = fma(x.x, wi, fma(x.y, w.x, im));
-            idx += inc;
-            if (idx >= n) idx -= n;
-        }
-        b[L * ld + fft_pos(q * Ns * rad + k + u * Ns)] = Cx<R>::make(re, im);
+        const int v = fft_div(i, rm), j = i - v * m;
+        const int k = j - fft_div(j, rN) * Ns;
+        cx_t<R> w = tw[k * ts * v];                      // k ts v < n
+        if (INV) w.y = -w.y;
+        cx_t<R>* x = a + L * ld + fft_pos(i);
+        *x = cx_mul<R>(*x, w);
     }
+    __syncthreads();
 }
 
 // The NL lines of `a` (line L at a + L fft_ld(n)), already visible to the
@@ -249,7 +292,10 @@ __device__ __forceinline__ cx_t<R>* fft_lines(cx_t<R>* a, cx_t<R>* b, const cx_t
             case 4: fft_stage<R, INV, 4>(a, b, tw, NL, p.n, Ns); break;
             case 5: fft_stage<R, INV, 5>(a, b, tw, NL, p.n, Ns); break;
             case 8: fft_stage<R, INV, 8>(a, b, tw, NL, p.n, Ns); break;
-            default: fft_stage_any<R, INV>(a, b, tw + p.n, NL, p.n, Ns, r); break;
+            default:
+                if (Ns > 1) fft_twist<R, INV>(a, tw + p.n, NL, p.n, Ns, r);
+                fft_stage_any<R, INV>(a, b, tw + p.n, NL, p.n, Ns, r);
+                break;
         }
         __syncthreads();
         Ns *= r;

@@ -657,9 +657,10 @@ size_t modeq_work_bytes(int nx, int ny, int prec) {
 
 namespace {
 
-// Threads for `lines` lines of n: one per four elements.
-int mq_block(int lines, int n) {
-    return std::min(MQ_THREADS, std::max(64, (lines * n / 4 + 63) / 64 * 64));
+// Threads for `lines` lines: one per four elements, per two where a stage of
+// direct sums has an output pair for each.
+int mq_block(int lines, const FftPlan& p) {
+    return std::min(MQ_THREADS, std::max(64, (lines * p.n / (p.any ? 2 : 4) + 63) / 64 * 64));
 }
 
 size_t mq_lds(int lines, const FftPlan& p, size_t csize) {
@@ -687,7 +688,7 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
         NL /= 2;
     const size_t lx = mq_lds(NL, px, sizeof(C));
     const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
-    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, a.nx));
+    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px));
     hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, bx, lx, st, a, px, NL, step0, nb, W);
     // columns per block: two for the in-place passes (four columns halve the
     // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
@@ -707,7 +708,7 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
         const size_t ly = mq_lds(2 * NC, py, sizeof(C));
         hipError_t e = mq_lds_limit(k_meq_filter<Real, false>, ly);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, a.ny)), ly, st, a,
+        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py)), ly, st, a,
                            py, NC, W);
     }
     hipLaunchKernelGGL(k_meq_noise_ix<Real>, gx, bx, lx, st, a, px, NL, nb, (const C*)W, xi);

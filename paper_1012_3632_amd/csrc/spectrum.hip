@@ -253,9 +253,10 @@ int fft_lines_per_block(const FftPlan& p, size_t lines, size_t total, size_t* ld
 }
 
 // Four elements per thread: with eight (one radix-8 group each) too few
-// wavefronts hide the LDS latency (x pass 119 us against 96).
-int fft_block(int NL, int n) {
-    const int t = (NL * n / 4 + 63) / 64 * 64;
+// wavefronts hide the LDS latency (x pass 119 us against 96).  Two where a
+// stage of direct sums has an output pair for each.
+int fft_block(int NL, const FftPlan& p) {
+    const int t = (NL * p.n / (p.any ? 2 : 4) + 63) / 64 * 64;
     return t < 64 ? 64 : (t > FFT_THREADS ? FFT_THREADS : t);
 }
 
@@ -283,7 +284,7 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         hipError_t e = fft_lds((const void*)k_fft_rows, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_fft_rows, dim3((unsigned)std::min<size_t>(blocks, FFT_GRID)),
-                           dim3(fft_block(NL, nx)), lds, st, fields, W, p, NL, rows, nlines);
+                           dim3(fft_block(NL, p)), lds, st, fields, W, p, NL, rows, nlines);
     }
     // y: hx adjacent lines per (field, z); z: hx ny adjacent lines per field
     for (int axis = 1; axis < 3; ++axis) {
@@ -298,7 +299,7 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         hipError_t e = fft_lds((const void*)k_fft_cols, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_fft_cols, dim3((unsigned)std::min<size_t>(ngroups, FFT_GRID)),
-                           dim3(fft_block(NL, n)), lds, st, W, p, NL, (uint32_t)inner, outer,
+                           dim3(fft_block(NL, p)), lds, st, W, p, NL, (uint32_t)inner, outer,
                            groups, ngroups);
     }
     const size_t blocks = (V + 255) / 256 < 4096 ? (V + 255) / 256 : 4096;
