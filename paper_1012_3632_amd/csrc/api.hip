@@ -194,7 +194,7 @@ void scratch_layout(const StepSpec& s, size_t V, size_t rb, size_t* drho_off, si
 // The untuned shape of D3Q19 force steps: flat, past 12 M sites and from 64
 // sites per row up the 64 x 4 march, whose columns then fill the chip.  us per
 // step with statistics, FP32 (FP64) unless noted, 32 x 4 x 2 tile / march / flat:
-// 16^3 12.8 / 52 / 10.9; 101 x 77 x 53 38 (81) / 58 (95) / 26 (50); 700 x 40 x 40
+// 16^3 12.8 / 52 / 9.1; 101 x 77 x 53 38 (81) / 58 (95) / 26 (50); 700 x 40 x 40
 // 73 / 80 / 53; 128^3 141 (330) / 109 (244) / 109 (254); 200^3 546 (1282) / 505
 // (1075) / 431 (891); 256^3 981 (2759) / 768 (1847) / 837 (1946); 320 x 256 x 256
 // 1280 / 1020 / 1275.
@@ -203,12 +203,10 @@ int force3_default(const StepSpec& s) {
     return flat_fits(s) ? FLAT_FORCE_CFG : 0;
 }
 
-// The work field launch_step needs for shape cfg, or null (pd false: partial-
-// density shapes run as plain marches).
-void* step_work(const flb_handle* h, int cfg, bool pd = true) {
+// The work field launch_step needs for shape cfg, or null.
+void* step_work(const flb_handle* h, int cfg) {
     const StepSpec& s = h->spec;
-    return (pd && config_partial_density(s, cfg)) ||
-                   (s.force && config_shape(s.lat, s.force, cfg).fl)
+    return config_partial_density(s, cfg) || (s.force && config_shape(s.lat, s.force, cfg).fl)
                ? h->rho_part : nullptr;
 }
 
@@ -948,7 +946,7 @@ flb_status seg_recompute(const SegWork& sw, uint64_t k0, hipStream_t st) {
         for (size_t j = 1; j < sw.k; ++j)
             HIP_TRY(launch_step(h->spec, h->cfg, sw.state(j - 1), (void*)sw.state(j), nullptr,
                                 nullptr, (unsigned long long)(k0 + j - 1), nullptr, st,
-                                (void*)sw.density(j - 1)));
+                                (void*)sw.density(j - 1), step_work(h, h->cfg)));
         HIP_TRY(launch_density(h->spec, sw.state(sw.k - 1), sw.density(sw.k - 1), st));
         return FLB_OK;
     }
@@ -956,7 +954,7 @@ flb_status seg_recompute(const SegWork& sw, uint64_t k0, hipStream_t st) {
     for (size_t j = 1; j < sw.k; ++j) {
         HIP_TRY(launch_step(h->spec, h->cfg, sw.state(j - 1), (void*)sw.state(j),
                             sw.density(j - 1), nullptr, (unsigned long long)(k0 + j - 1), nullptr,
-                            st, nullptr, step_work(h, h->cfg, false)));
+                            st));
         if (h->spec.force) HIP_TRY(launch_density(h->spec, sw.state(j), sw.density(j), st));
     }
     return FLB_OK;

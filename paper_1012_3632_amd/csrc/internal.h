@@ -76,8 +76,9 @@ hipError_t launch_density(const StepSpec& s, const void* fin, void* drho_out, hi
 // launch_density would write; ignored otherwise.
 // rho_part: for the partial-density shapes (config_partial_density), if
 // non-null, receives the part of fout's density that the march forms; null
-// runs the plain march of the same shape.  The flat force shape takes the same
-// pointer as its work field (null: the 16 x 4 x 4 tile).
+// runs the plain march of the same shape.  The flat force shape (config_fused
+// where it fits) takes the same pointer as its work field and writes fin's
+// density to rho_out or, if that is null, to drho.
 hipError_t launch_step(const StepSpec& s, int cfg, const void* fin, void* fout, const void* drho,
                        const unsigned long long* step_dev, unsigned long long step_host,
                        double* partial, hipStream_t st, void* rho_out = nullptr,

@@ -318,9 +318,9 @@ __global__ __launch_bounds__(TX* TY) void k_step_ip(Real* f, Geom g, CollidePara
 // -> 122 (plain 126 -> 110), 120 x 100 x 90 FP64 70.5 -> 58.1, 101 x 77 x 53
 // FP32 14.6 -> 11.8, 17 x 120 x 90 FP32 10.9 -> 7.5.
 // FORCE (KIND 0): the force from the density and chemical potential fields
-// of ff (k_density, k_mu_flat).  For lattices that the z-march cannot fill the
-// chip with: its blocks own 16-plane columns, and the tiles that form mu
-// themselves stage five densities and 2.5 chemical potentials per site.
+// of ff (k_density and k_mu_flat, or k_rho_mu).  For lattices that the z-march
+// cannot fill the chip with: its blocks own 16-plane columns, and the tiles that
+// form mu themselves stage five densities and 2.5 chemical potentials per site.
 template <int LAT, typename Real, bool STATS, int KIND, bool FORCE = false>
 __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fout, Geom g,
                                                        uint32_t inv_nx, uint32_t inv_ny,
@@ -345,8 +345,16 @@ __global__ __launch_bounds__(FLAT_NT) void k_step_flat(const Real* fin, Real* fo
     if constexpr (STATS) block_accumulate<2 * Q, FLAT_NT>(v, partial + (size_t)b * 2 * Q, lds_stats);
 }
 
-// mu = psi'(rho) - kappa lap_h rho of the density field (the sums of
-// ForceTile::mu_rows).
+// mu = psi'(rho) - kappa lap_h rho from the density and its weighted
+// differences w_i (rho(x + c_i) - rho(x)) (as ForceTile::mu_rows).
+template <typename Real>
+__device__ __forceinline__ Real mu_of(Real rc, Real lap, const ForceParams<Real>& fp) {
+    lap *= Real(6);   // 2 / cs2
+    const Real d = rc + fp.shift;
+    return Real(2) * fp.a * d + Real(4) * fp.b * d * d * d - fp.kappa * lap;
+}
+
+// mu of the density field.
 template <int LAT, typename Real>
 __global__ __launch_bounds__(FLAT_NT) void k_mu_flat(const Real* __restrict__ drho,
                                                      Real* __restrict__ mu, Geom g, uint32_t inv_nx,
@@ -365,9 +373,60 @@ __global__ __launch_bounds__(FLAT_NT) void k_mu_flat(const Real* __restrict__ dr
     for (int i = 1; i < L::Q; ++i)
         lap += Real(L::w[i]) *
                (rep_ld(r, 0u, 0, nb.at(L::cx[i], L::cy[i], L::cz[i]), Real(0)) - rc);
-    lap *= Real(6);   // 2 / cs2
-    const Real d = rc + fp.shift;
-    mu[s] = Real(2) * fp.a * d + Real(4) * fp.b * d * d * d - fp.kappa * lap;
+    mu[s] = mu_of(rc, lap, fp);
+}
+
+// Density and mu in one launch, for small boxes, which launches and latency
+// bound: a block forms the density of its tile and one site around it in LDS
+// (2.3 densities per site, from cache at these sizes), a thread per density
+// (16^3 FP32 9.1 us per step; 320 threads 9.4, 256 9.7), and writes both fields
+// of its tile.
+constexpr int RM_X = 8, RM_Y = 8, RM_Z = 4, RM_NT = 640;
+template <int LAT, typename Real>
+__global__ __launch_bounds__(RM_NT) void k_rho_mu(const Real* __restrict__ fin,
+                                                  Real* __restrict__ drho, Real* __restrict__ mu,
+                                                  Geom g, ForceParams<Real> fp) {
+    using L = Lattice<LAT>;
+    constexpr int HX = RM_X + 2, HY = RM_Y + 2, HZ = RM_Z + 2, NH = HX * HY * HZ;
+    static_assert(RM_NT >= RM_X * RM_Y * RM_Z, "a thread per site of the tile");
+    __shared__ Real rho[NH];
+    uint32_t b = xcd_remap(blockIdx.x, g.nblocks);
+    const int bx = (int)(b % (uint32_t)g.nbx);
+    b /= (uint32_t)g.nbx;
+    const int by = (int)(b % (uint32_t)g.nby), bz = (int)(b / (uint32_t)g.nby);
+    const int x0 = bx * RM_X, y0 = by * RM_Y, z0 = bz * RM_Z;
+    const __amdgpu_buffer_rsrc_t in = rep_rsrc<LAT>(fin, g.V);
+    // i in [-1, n + the tile's extent]
+    auto wrap = [](int i, int n) {
+        if (i < 0) i += n;
+        while (i >= n) i -= n;
+        return i;
+    };
+    for (int t = threadIdx.x; t < NH; t += RM_NT) {
+        const int hz = t / (HX * HY), r = t - hz * (HX * HY), hy = r / HX, hx = r - hy * HX;
+        const int x = wrap(x0 - 1 + hx, g.nx), y = wrap(y0 - 1 + hy, g.ny), z = wrap(z0 - 1 + hz, g.nz);
+        const Nbr<Real> nb((uint32_t)(x + g.nx * (y + g.ny * z)), x, y, z, g.nx, g.ny, g.nz, g.V);
+        Real f[L::Q];
+        rep_pull<LAT, Real>(in, g.V, nb, f);
+        Real acc = Real(0);
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) acc += f[i];
+        rho[t] = acc;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    const int lz = t / (RM_X * RM_Y), ly = t / RM_X % RM_Y, lx = t % RM_X;
+    const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+    if (lz >= RM_Z || x >= g.nx || y >= g.ny || z >= g.nz) return;
+    const Real* c = rho + (lx + 1) + HX * ((ly + 1) + HY * (lz + 1));
+    const Real rc = c[0];
+    Real lap = Real(0);
+#pragma unroll
+    for (int i = 1; i < L::Q; ++i)
+        lap += Real(L::w[i]) * (c[L::cx[i] + HX * (L::cy[i] + HY * L::cz[i])] - rc);
+    const size_t s = (size_t)x + (size_t)g.nx * (y + (size_t)g.ny * z);
+    drho[s] = rc;
+    mu[s] = mu_of(rc, lap, fp);
 }
 
 // The next step's density formed inside the z-march.  After streaming, the
@@ -1080,11 +1139,11 @@ static void flat_launch(const StepSpec& s, int kind, const void* fin, void* fout
     else partial ? go(k_step_flat<LAT, Real, true, 2>) : go(k_step_flat<LAT, Real, false, 2>);
 }
 
-// The force step of the same blocks: mu from the density drho into the work
-// field, then the step.
+// The force step of the same blocks: fin's density into drho and mu into the
+// work field, then the step.
 template <typename Real>
-static void flat_force_launch(const StepSpec& s, const void* fin, void* fout, const void* drho,
-                              void* mu, StepIndex si, double* partial, hipStream_t st) {
+static void flat_force_launch(const StepSpec& s, const void* fin, void* fout, void* drho, void* mu,
+                              StepIndex si, double* partial, hipStream_t st) {
     Geom g = make_geom(s, TileShape{1, 1, 1, 1, 0, 0, 0});
     g.nblocks = (g.V + FLAT_NT - 1) / FLAT_NT;
     const dim3 grid(g.nblocks), block(FLAT_NT);
@@ -1092,8 +1151,20 @@ static void flat_force_launch(const StepSpec& s, const void* fin, void* fout, co
     const uint32_t ix = (uint32_t)(((1ull << 32) + s.nx - 1) / s.nx);
     const uint32_t iy = (uint32_t)(((1ull << 32) + s.ny - 1) / s.ny);
     const FlatForce<Real> ff{(const Real*)drho, (const Real*)mu, force_params<Real>(s)};
-    hipLaunchKernelGGL((k_mu_flat<1, Real>), grid, block, 0, st, (const Real*)drho, (Real*)mu, g, ix,
-                       iy, ff.fp);
+    // one launch for both fields while launches and latency bound them (up to
+    // two blocks per compute unit), us per step with statistics, two launches ->
+    // one: 16^3 FP32 10.3 -> 9.1 (FP64 13.2 -> 11.6), 48 x 19 x 104 (468 blocks)
+    // 14.7 -> 13.2 (20.4 -> 19.8), but 125 x 18 x 42 (528) FP64 19.6 -> 21.2, 64^3
+    // 18.0 -> 21.1 (33.2 -> 35.8), 101 x 77 x 53 25.4 -> 34.5
+    const Geom t = make_geom(s, TileShape{RM_X, RM_Y, RM_Z, 1, 0, 0, 0});
+    if (t.nblocks <= 512) {
+        hipLaunchKernelGGL((k_rho_mu<1, Real>), dim3(t.nblocks), dim3(RM_NT), 0, st,
+                           (const Real*)fin, (Real*)drho, (Real*)mu, t, ff.fp);
+    } else {
+        hipLaunchKernelGGL((k_density<1, Real>), grid, block, 0, st, (const Real*)fin, (Real*)drho, g);
+        hipLaunchKernelGGL((k_mu_flat<1, Real>), grid, block, 0, st, (const Real*)drho, (Real*)mu, g,
+                           ix, iy, ff.fp);
+    }
     if (partial)
         hipLaunchKernelGGL((k_step_flat<1, Real, true, 0, true>), grid, block, 0, st, (const Real*)fin,
                            (Real*)fout, g, ix, iy, P, si, partial, ff);
@@ -1146,8 +1217,9 @@ static void step_dispatch(const StepSpec& s, int cfg, const void* fin, void* fou
             case 10: step_march<Real, 64, 4>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
             case 11: step_march<Real, 64, 8>(s, 16, fin, fout, drho, si, partial, st, rho_part); break;
             default:
-                if (flat_fits(s) && rho_part)
-                    flat_force_launch<Real>(s, fin, fout, drho, rho_part, si, partial, st);
+                if (flat_fits(s))
+                    flat_force_launch<Real>(s, fin, fout, rho_out ? rho_out : (void*)drho, rho_part, si,
+                                            partial, st);
                 else
                     step_tile<LAT, Real, true, 16, 4, 4>(s, fin, fout, drho, si, partial, st);
                 break;
@@ -1233,7 +1305,8 @@ hipError_t launch_density_fix(const StepSpec& s, int cfg, const void* fin, const
 
 bool config_fused(const StepSpec& s, int cfg) {
     return s.force && cfg >= 0 && cfg < n_configs(s.lat, s.force) &&
-           config_shape(s.lat, s.force, cfg).fd;
+           (config_shape(s.lat, s.force, cfg).fd ||
+            (config_shape(s.lat, s.force, cfg).fl && flat_fits(s)));
 }
 
 bool config_in_place(const StepSpec& s, int cfg) {

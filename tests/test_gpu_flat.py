@@ -61,7 +61,8 @@ def test_batch_of_thin_boxes():
 
 
 FORCE_BOXES = [(1, 1, 1), (1, 1, 300), (1, 7, 40), (9, 1, 31), (300, 1, 1), (17, 16, 1), (255, 2, 3),
-               (256, 3, 2), (257, 5, 3), (2, 2, 2), (33, 20, 7), (64, 4, 4)]
+               (256, 3, 2), (257, 5, 3), (2, 2, 2), (33, 20, 7), (64, 4, 4),
+               (64, 64, 32), (64, 64, 33)]   # the last box of one launch for both fields, the first of two
 
 
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
