@@ -95,11 +95,19 @@ def fdt_check(sim):
 def profile_key(shape):
     """Name(s) of a stats-on D3Q19 FP32 step launch in the committed counter
     table (an in-place shape has one entry per phase of a pair)."""
-    tx, ty, tz, spt, nt, _, ip, _ = shape
+    tx, ty, tz, spt, nt, _, ip, kind = shape
+    if kind == 3:   # flat: one step (kind 0) or the phases of a pair (kinds 1 and 2)
+        return ["k_step_flat_d3q19_fp32_stats_kind%d" % k for k in ((1, 2) if ip else (0,))]
     if ip:
         sp = "x%d" % spt if spt > 1 else ""
         return ["k_step_ip_d3q19_fp32_stats_%dx%d%s_ph%d" % (tx, ty, sp, ph) for ph in (0, 1)]
     return ["k_step_d3q19_fp32_stats_%dx%dx%dx%d%s" % (tx, ty, tz, spt, "_nt" if nt else "")]
+
+
+def kernel_label(shape):
+    """What the roofline line calls a stats-on D3Q19 FP32 ideal-gas launch."""
+    name = "k_step_flat" if shape[7] == 3 else ("k_step_ip" if shape[6] else "k_step")
+    return "%s<D3Q19,float,stats>%s" % (name, " (in-place pair)" if shape[6] else "")
 
 
 def bench_main(args):
@@ -154,8 +162,7 @@ def bench_main(args):
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic_from_profiles(profile_key(sim.launch_shape(run_cfg))),
-                     "kernel": ("k_step_ip<D3Q19,float,stats> (in-place pair, phases 0 and 1)"
-                                if pair_cfg >= 0 else "k_step<D3Q19,float,ideal,stats>"),
+                     "kernel": kernel_label(sim.launch_shape(run_cfg)),
                      "bytes_per_site": bytes_site,
                      "working_set_bytes": (1 if pair_cfg >= 0 else 2) * 19 * 4 * V},
         "wall_timed_s": round(wall, 3),
@@ -284,10 +291,10 @@ def ideal_256(stream, copy_gbs):
     if "two_buffers" in res:
         res["two_buffers"]["frac_of_19plane_pattern"] = round(
             res["two_buffers"]["achieved_GBps_152B"] / pat_two, 4)
-    res["roofline"] = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                       "kernel": "k_step_ip<D3Q19,float,stats> (in-place pair)"}
     best = min((v for k, v in res.items() if k in ("in_place_pairs", "two_buffers")),
                key=lambda v: v["ms_per_step"])
+    res["roofline"] = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                       "kernel": kernel_label(best["launch_shape"])}
     res["roofline"].update(achieved=best["achieved_GBps_152B"], frac=best["frac_of_8TBps"])
     return res
 
@@ -484,8 +491,8 @@ def extras(args, stream):
     ms_step = e0.elapsed_time(e1) / wl["interval"]
     us_spec = e1.elapsed_time(e2) / nspec * 1e3
     Ve = pe.nx * pe.ny
-    # direct DFT along x then y: 8 FP64 flops per complex multiply-add
-    dft_flops = 8 * pe.q * Ve * (pe.nx + pe.ny)
+    # nominal FP64 flops of a transform of real fields: 2.5 n log2 n
+    dft_flops = 2.5 * pe.q * Ve * np.log2(Ve)
     se.close()
     del se, spec
     t0 = time.perf_counter()

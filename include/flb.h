@@ -482,9 +482,10 @@ flb_status flb_batch_destroy(flb_batch* b);
  * call runs a density pass; the trials time steady steps, so for calls of a
  * few steps the plain march of the same tile, which needs no such first
  * pass, can be the faster choice) the way a run uses it (ordinary
- * steps alternate the two buffers over `repeats` steps; in-place pairs are
- * timed after about 4 ms of settling steps, round-robin over at least three
- * rounds of about 2 ms each, best round kept) and afterwards
+ * steps alternate the two buffers over `repeats` steps; in-place pairs and the
+ * fastest ordinary step with statistics are timed after about 4 ms of settling
+ * steps, round-robin over at least three rounds of about 2 ms each, best round
+ * kept) and afterwards
  * restores the state and the accumulated statistics from a host copy (host
  * memory of one population buffer plus the statistics slots); it writes
  * best[4]: the fastest shape for plain steps, for steps with statistics, the

@@ -733,9 +733,13 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     // only after its buffer has settled, and the candidates differ by a few
     // percent.  So the state is first stepped for about 4 ms with the first
     // candidate, then every candidate is timed for about 2 ms per trial,
-    // round-robin, and each keeps its best round.
+    // round-robin, and each keeps its best round.  The fastest ordinary step
+    // with statistics takes part: its own trial above is a few steps on cold
+    // buffers, up to 3 % above what it reaches in a run, and FP64 pairs on
+    // 128^3 and 160^3 beat that trial but lose the run (us per step 127 against
+    // 122, 259 against 253).
     int best_pair = -1;
-    float pair_ms = 1e30f;
+    float pair_ms = 1e30f, ord_ms = 1e30f;
     std::vector<int> cands;
     for (int c = 0; c < ncfg; ++c)
         if (config_in_place(h->spec, c) && !sparse(c)) cands.push_back(c);
@@ -745,9 +749,16 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
             r = launch_step_in_place(h->spec, c, 1, A, nullptr, h->step + 1, h->stats, st);
         return r;
     };
-    auto time_pairs = [&](int c, int n, float* ms_per_step) {
+    // two ordinary steps with statistics, A -> B -> A
+    auto ordinary = [&](int c) {
+        hipError_t r = launch_step(h->spec, c, A, B, h->drho, nullptr, h->step, h->stats, st);
+        if (r == hipSuccess)
+            r = launch_step(h->spec, c, B, A, h->drho, nullptr, h->step + 1, h->stats, st);
+        return r;
+    };
+    auto time_pairs = [&](auto&& two, int c, int n, float* ms_per_step) {
         hipError_t r = hipEventRecord(e0, st);
-        for (int k = 0; k < n && r == hipSuccess; ++k) r = pair(c);
+        for (int k = 0; k < n && r == hipSuccess; ++k) r = two(c);
         if (r == hipSuccess) r = hipEventRecord(e1, st);
         if (r == hipSuccess) r = hipEventSynchronize(e1);
         float ms = 0.f;
@@ -758,18 +769,24 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     if (!cands.empty() && e == hipSuccess) {
         float t1 = 0.f;
         e = pair(cands[0]);
-        if (e == hipSuccess) e = time_pairs(cands[0], 1, &t1);
+        if (e == hipSuccess) e = time_pairs(pair, cands[0], 1, &t1);
         const float pair_est = std::max(2.f * t1, 1e-3f);   // ms per pair
         const int settle = std::min(400, std::max(2, (int)(4.f / pair_est)));
         const int per = std::min(200, std::max(repeats, (int)(2.f / pair_est)));
         for (int k = 0; k < settle && e == hipSuccess; ++k) e = pair(cands[0]);
         std::vector<float> bt_c(cands.size(), 1e30f);
-        for (int round = 0; round < std::max(3, repeats) && e == hipSuccess; ++round)
+        for (int round = 0; round < std::max(3, repeats) && e == hipSuccess; ++round) {
+            float ms = 0.f;
             for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i) {
-                float ms = 0.f;
-                e = time_pairs(cands[i], per, &ms);
+                e = time_pairs(pair, cands[i], per, &ms);
                 if (e == hipSuccess) bt_c[i] = std::min(bt_c[i], ms);
             }
+            if (e == hipSuccess) e = ordinary(bi[1]);
+            if (e == hipSuccess) e = time_pairs(ordinary, bi[1], per, &ms);
+            if (e == hipSuccess) ord_ms = std::min(ord_ms, ms);
+            if (e == hipSuccess) e = pair(cands[0]);
+        }
+        bt[1] = std::min(bt[1], ord_ms);
         for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i)
             if (bt_c[i] < pair_ms) {
                 pair_ms = bt_c[i];
