@@ -412,7 +412,7 @@ def extras(args, stream):
     torch.cuda.empty_cache()
 
     # 64 replicas of uneven size (the realised draw is tests/golden/
-    # d3q19_batch64_edges.json), one persistent launch per step, the
+    # d3q19_batch64_edges.json), one launch per step, the
     # workload's 1000 steps captured in one graph
     from paper_1012_3632_amd import Batch, lattice_tables
     wl = W.WORKLOADS["d3q19_batch64"]

@@ -959,11 +959,14 @@ flb_status seg_recompute(const SegWork& sw, uint64_t k0, hipStream_t st) {
     }
     if (h->spec.force && config_fused(h->spec, h->cfg)) {
         // the step forms its input's density itself and writes it out, so a
-        // recomputed step is one launch; the last state's density is a pass
+        // recomputed step needs no pass before it; the last state's density is
+        // one.  The flat D3Q19 shape's work field is the next state's density
+        // field, which the next step fills: the handle's own may be in use by
+        // forward steps on another stream.
         for (size_t j = 1; j < sw.k; ++j)
             HIP_TRY(launch_step(h->spec, h->cfg, sw.state(j - 1), (void*)sw.state(j), nullptr,
                                 nullptr, (unsigned long long)(k0 + j - 1), nullptr, st,
-                                (void*)sw.density(j - 1), step_work(h, h->cfg)));
+                                (void*)sw.density(j - 1), sw.density(j)));
         HIP_TRY(launch_density(h->spec, sw.state(sw.k - 1), sw.density(sw.k - 1), st));
         return FLB_OK;
     }

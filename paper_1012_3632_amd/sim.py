@@ -406,7 +406,7 @@ class Simulation:
 
 class Batch:
     """Many independent ideal-gas replicas of uneven size advanced together
-    (one persistent launch per step over a flat tile table)."""
+    (one launch per step over a flat tile table)."""
 
     def __init__(self, params, dims, seeds=None, device="cuda", stream=None):
         self.params = params
