@@ -91,3 +91,25 @@ def test_flat_force_shape(n, precision):
         # modes that a thin box leaves at rounding level have no scale of their own
         assert np.all(np.abs(q1 - q0) <= 20 * tol * q0.max())
         assert np.all(np.abs(s1 - s0) <= 20 * tol * np.sqrt(n0 * np.prod(n) * q0.max()))
+
+
+@pytest.mark.parametrize("n", [(24, 30, 20), (101, 77, 53)])   # one launch for both fields, two
+def test_flat_force_graph_replays(n):
+    """Captured flat force steps replayed three times = eager calls, bit for bit."""
+    from paper_1012_3632_amd import Simulation
+    p = gpu_params(lattice="D3Q19", precision="fp32", nx=n[0], ny=n[1], nz=n[2], eta=1, force_model=1,
+                   a=-0.01, b=0.1, rho_c=1.0, kappa=0.05, **dict(KW, kT=1e-6))
+    drho = W.initial_drho((n[2], n[1], n[0]), 9, 0.01)
+    eager, graph = (Simulation(p, drho_init=drho) for _ in range(2))
+    assert eager.launch_shape(eager.launch_configs()[1][1])[7] == 3   # the untuned shape
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph.graph_capture(4, stats_stride=1, stream=stream)
+    for _ in range(3):
+        eager.step(4, stats_stride=1)
+        with torch.cuda.stream(stream):
+            graph.graph_launch(stream)
+        torch.cuda.synchronize()
+        assert torch.equal(eager.state(), graph.state())
+    for a, b in zip(eager.moments(), graph.moments()):
+        assert np.array_equal(a, b)
