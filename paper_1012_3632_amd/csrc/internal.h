@@ -171,6 +171,14 @@ struct ModEqArgs {
 // in FP64.
 constexpr int MODEQ_MAX_BATCH = 16;
 size_t modeq_work_bytes(int nx, int ny, int prec);
+// How the noise of nb steps is split over blocks: rows and columns per block
+// and the dynamic LDS of either, at most LDS_BYTES, what a compute unit has.
+constexpr size_t LDS_BYTES = 163840;
+struct ModEqNoiseShape {
+    int NL, NC;
+    size_t lds_rows, lds_cols;
+};
+ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb);
 // The noise of steps step0 .. step0 + nb - 1: spectra of step b at
 // W + 2 V b (complex), filtered fields at xi + 2 V b (reals of prec).
 hipError_t launch_modeq_noise(const ModEqArgs& a, int prec, uint32_t step0, int nb, void* W,

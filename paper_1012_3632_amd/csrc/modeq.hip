@@ -667,6 +667,39 @@ size_t mq_lds(int lines, const FftPlan& p, size_t csize) {
     return (2 * (size_t)lines * fft_ld(p.n) + fft_twiddles(p)) * csize;
 }
 
+}  // namespace
+
+ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb) {
+    const size_t csize = prec == 0 ? sizeof(float2) : sizeof(double2);
+    const FftPlan px = fft_plan(a.nx), py = fft_plan(a.ny);
+    ModEqNoiseShape s;
+    // rows per block: up to 2048 elements (512 threads) and 48 KB, fewer
+    // where that leaves less than 1024 turns
+    s.NL = 16;
+    while (s.NL > 1 && (s.NL * a.nx > 2048 || mq_lds(s.NL, px, csize) > 49152 ||
+                        (size_t)a.ny * nb < 1024 * (size_t)s.NL))
+        s.NL /= 2;
+    s.lds_rows = mq_lds(s.NL, px, csize);
+    // columns per block: two for the in-place passes (four columns halve the
+    // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
+    // for the staged ones as far as their lines and twiddles fit the LDS (931
+    // elements with a direct sum, FP64, two columns: 164 KB); fewer where that
+    // leaves less than 512 blocks
+    const int hx = a.nx / 2 + 1;
+    const bool p2 = (a.ny & (a.ny - 1)) == 0;
+    auto cols = [&](int NC) {
+        return p2 ? (2 * (size_t)NC + 1) * a.ny * csize : mq_lds(2 * NC, py, csize);
+    };
+    s.NC = p2 ? 2 : 4;
+    while (s.NC > 1 && ((!p2 && 2 * s.NC * a.ny > 4096) || cols(s.NC) > LDS_BYTES ||
+                        hx * nb < 512 * s.NC))
+        s.NC /= 2;
+    s.lds_cols = cols(s.NC);
+    return s;
+}
+
+namespace {
+
 template <typename K>
 hipError_t mq_lds_limit(K kernel, size_t lds) {
     if (lds <= 65536) return hipSuccess;
@@ -680,32 +713,21 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
     using C = cx_t<Real>;
     C* W = (C*)Wv;
     const FftPlan px = fft_plan(a.nx), py = fft_plan(a.ny);
-    // rows per block: up to 2048 elements (512 threads) and 48 KB, fewer
-    // where that leaves less than 1024 turns
-    int NL = 16;
-    while (NL > 1 && (NL * a.nx > 2048 || mq_lds(NL, px, sizeof(C)) > 49152 ||
-                      (size_t)a.ny * nb < 1024 * (size_t)NL))
-        NL /= 2;
-    const size_t lx = mq_lds(NL, px, sizeof(C));
+    const ModEqNoiseShape sh = modeq_noise_shape(a, sizeof(Real) == 4 ? 0 : 1, nb);
+    const int NL = sh.NL, NC = sh.NC;
+    const size_t lx = sh.lds_rows, ly = sh.lds_cols;
     const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
     const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px));
     hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, bx, lx, st, a, px, NL, step0, nb, W);
-    // columns per block: two for the in-place passes (four columns halve the
-    // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
-    // for the staged ones; fewer where that leaves less than 512 blocks
     const int hx = a.nx / 2 + 1;
     const bool p2 = (a.ny & (a.ny - 1)) == 0;
-    int NC = p2 ? 2 : 4;
-    while (NC > 1 && ((!p2 && 2 * NC * a.ny > 4096) || hx * nb < 512 * NC)) NC /= 2;
     const dim3 gy((unsigned)((hx + NC - 1) / NC), (unsigned)nb);
     if (p2) {
-        const size_t ly = (2 * (size_t)NC + 1) * a.ny * sizeof(C);
         hipError_t e = mq_lds_limit(k_meq_filter<Real, true>, ly);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_meq_filter<Real, true>), gy, dim3(MQ_P2_THREADS), ly, st, a, py, NC,
                            W);
     } else {
-        const size_t ly = mq_lds(2 * NC, py, sizeof(C));
         hipError_t e = mq_lds_limit(k_meq_filter<Real, false>, ly);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py)), ly, st, a,

@@ -71,3 +71,23 @@ def test_modeq_batches_same_bits(nx, ny):
     a.step(18)
     b.step(18)
     assert torch.equal(a.f, b.f)
+
+
+@pytest.mark.parametrize("nx,ny", [(126, 931), (126, 1008), (130, 1021)])
+def test_modeq_long_staged_columns(nx, ny):
+    """FP64 columns with a direct sum, near the longest: a batch that would give
+    a block two columns (more LDS than a compute unit has) draws the noise of
+    single steps, and that noise is the oracle's."""
+    from helpers import F64_TOL, rel_err
+    from oracle import modeq as OM
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    d = dict(nx=nx, ny=ny, rho0=1.0, kT=1e-5, cs2_0=0.265 ** 2, kappa=0.08, seed=4)
+    p = ModEqParams(precision="fp64", **d)
+    a, b = ModEq(p, batch=1), ModEq(p, batch=16)
+    a.step(16)
+    b.step(16)
+    assert torch.equal(a.f, b.f)
+    xi = a.noise(3).cpu().numpy()
+    ref = OM.noise(3, OM.ModEqParams(**d))
+    for got, want in ((xi[0], ref[0]), (xi[1], ref[5])):
+        assert rel_err(got, want) < F64_TOL
