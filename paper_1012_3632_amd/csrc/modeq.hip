@@ -718,17 +718,21 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
     const size_t lx = sh.lds_rows, ly = sh.lds_cols;
     const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
     const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px));
+    // a single row of 964 or more FP64 elements with a direct sum takes up to 70 KB
+    hipError_t e = mq_lds_limit(k_meq_noise_x<Real>, lx);
+    if (e == hipSuccess) e = mq_lds_limit(k_meq_noise_ix<Real>, lx);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, bx, lx, st, a, px, NL, step0, nb, W);
     const int hx = a.nx / 2 + 1;
     const bool p2 = (a.ny & (a.ny - 1)) == 0;
     const dim3 gy((unsigned)((hx + NC - 1) / NC), (unsigned)nb);
     if (p2) {
-        hipError_t e = mq_lds_limit(k_meq_filter<Real, true>, ly);
+        e = mq_lds_limit(k_meq_filter<Real, true>, ly);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_meq_filter<Real, true>), gy, dim3(MQ_P2_THREADS), ly, st, a, py, NC,
                            W);
     } else {
-        hipError_t e = mq_lds_limit(k_meq_filter<Real, false>, ly);
+        e = mq_lds_limit(k_meq_filter<Real, false>, ly);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py)), ly, st, a,
                            py, NC, W);

@@ -91,3 +91,21 @@ def test_modeq_long_staged_columns(nx, ny):
     ref = OM.noise(3, OM.ModEqParams(**d))
     for got, want in ((xi[0], ref[0]), (xi[1], ref[5])):
         assert rel_err(got, want) < F64_TOL
+
+
+@pytest.mark.parametrize("nx,ny", [(966, 3), (1008, 20), (1021, 8)])
+def test_modeq_long_staged_rows(nx, ny):
+    """FP64 rows with a direct sum whose one line takes more than 64 KB of LDS."""
+    from helpers import F64_TOL, rel_err
+    from oracle import modeq as OM
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    d = dict(nx=nx, ny=ny, rho0=1.0, kT=1e-5, cs2_0=0.265 ** 2, kappa=0.08, seed=4)
+    p = ModEqParams(precision="fp64", **d)
+    a, b = ModEq(p, batch=1), ModEq(p, batch=16)
+    xi = a.noise(3).cpu().numpy()
+    ref = OM.noise(3, OM.ModEqParams(**d))
+    for got, want in ((xi[0], ref[0]), (xi[1], ref[5])):
+        assert rel_err(got, want) < F64_TOL
+    a.step(16)
+    b.step(16)
+    assert torch.equal(a.f, b.f)
