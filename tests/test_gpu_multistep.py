@@ -111,3 +111,37 @@ def test_modeq_steps_per_launch_same_bits(nx, ny, kT, precision):
             b.step_into(fin, fout, n)
             fin, fout, n = fout, fin, n + 1
         assert torch.equal(a.f, fin), n
+
+
+# four steps on 8 x 8 and 16 x 16 tiles (ideal), three and two (force)
+STATS_BOXES = [(32, 32, "ideal"), (136, 130, "ideal"), (64, 48, "landau"), (160, 136, "landau")]
+
+
+@pytest.mark.parametrize("nx,ny,fluid", STATS_BOXES)
+def test_multi_steps_sum_steps_in_fp64(nx, ny, fluid):
+    """FP32 statistics of several steps per launch are summed over the steps in
+    FP64.  The uniform shear mode p_xx = 1 decays by 2^-13 a step, so the steps of
+    a launch add 1, 2^-13, 2^-26, 2^-39 per site (squares 1, 2^-26, ...): FP32
+    sums of several steps drop all past 2^-24.  Each step's own sums carry at
+    most the 24 roundings of its transforms and 16-lane sums (step 0: none, its
+    values are ones), so what follows step 0 errs by less than 2^-13 x 24 x 2^-24."""
+    from paper_1012_3632_amd import Simulation
+    kw = dict(FLUIDS[fluid], kT=0.0, rho0=1.0, rate_bulk=1.0, rate_shear=1.0 - 2.0 ** -13, rate_ghost=1.0)
+    sim = Simulation(gpu_params(lattice="D2Q9", precision="fp32", nx=nx, ny=ny, nz=1, **kw))
+    from paper_1012_3632_amd import lattice_tables
+    t = lattice_tables("D2Q9")
+    a = 4                                            # the mode p_xx - p_yy: four populations
+    row = np.asarray(t["T"])[a]
+    f = np.zeros((9, 1, ny, nx))
+    for i, c in enumerate(t["c"]):
+        if abs(c).sum() == 1:
+            f[i] = 0.25 * np.sign(row[i])
+    assert np.abs(np.asarray(t["T"]) @ f[:, 0, 0, 0] - np.eye(9)[a]).max() == 0
+    sim.load_state(f)
+    n = 4
+    sim.step(n, stats_stride=1)
+    s, q, ns = sim.moments()
+    assert ns == n
+    V = nx * ny
+    assert abs(s[a] / V - sum(2.0 ** (-13 * k) for k in range(n))) < 24 * 2.0 ** -37
+    assert abs(q[a] / V - sum(2.0 ** (-26 * k) for k in range(n))) < 24 * 2.0 ** -50
