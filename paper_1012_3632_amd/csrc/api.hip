@@ -1342,6 +1342,14 @@ flb_status flb_modeq_run(const flb_modeq_params* p, void* f, void* tmp, uint64_t
                                   : (size_t)MODEQ_MAX_BATCH;
     const int nb_max = (int)(fit < (size_t)MODEQ_MAX_BATCH ? fit : MODEQ_MAX_BATCH);
     const int T = modeq_steps(a);
+    // The number of launches has the parity of the steps for T = 1 and 3; for
+    // T = 2 one pair goes as two launches where it would be odd, so that the
+    // state ends in f: a copy costs more than a launch (kT = 0, two steps per
+    // call: 512^2 FP32 9.5 us a step with a copy, 1024^2 FP64 31.7)
+    const auto launches = [T](int32_t n) { return n / T + n % T; };
+    const int32_t total = nsteps / nb_max * launches(nb_max) + launches(nsteps % nb_max);
+    bool split = T == 2 && (total & 1);
+    int ones = 0;   // steps of the split pair still to go
     void* in = f;
     void* out = tmp;
     for (int32_t k0 = 0; k0 < nsteps; k0 += nb_max) {
@@ -1352,7 +1360,12 @@ flb_status flb_modeq_run(const flb_modeq_params* p, void* f, void* tmp, uint64_t
             HIP_TRY(launch_modeq_noise(a, p->precision, (uint32_t)(step0 + k0), nb, work, xi, st));
         }
         for (int b = 0, n; b < nb; b += n) {
-            n = b + T <= nb ? T : 1;
+            if (split && b + T <= nb) {
+                ones = T;
+                split = false;
+            }
+            n = b + T <= nb && ones == 0 ? T : 1;
+            if (ones > 0) --ones;
             HIP_TRY(launch_modeq_step(a, p->precision, n, in, out, (uint32_t)(step0 + k0 + b),
                                       xi ? xi + (size_t)b * 2 * V * rsize : nullptr, st));
             std::swap(in, out);

@@ -1,6 +1,7 @@
-"""The LDS of the modified-equilibrium noise kernels fits a compute unit, and
-the limit of every launch, at the extents, precisions and batches that the
-model accepts (no GPU needed)."""
+"""Host-side checks of the modified-equilibrium model (no GPU needed): the LDS
+of its noise kernels fits a compute unit, and the limit of every launch, at the
+extents, precisions and batches that the model accepts; a run makes no copy of
+the populations that its steps can do without."""
 
 import os
 import shutil
@@ -34,3 +35,7 @@ def test_noise_lds_fits_every_extent(tmp_path):
 
 def test_noise_launches_raise_their_lds_limit(tmp_path):
     assert _run(tmp_path, "noise_launch_check").endswith(" 0 over their limit\n")
+
+
+def test_even_runs_make_no_copy(tmp_path):
+    assert _run(tmp_path, "modeq_run_check").endswith(" 0 with a copy too many\n")
