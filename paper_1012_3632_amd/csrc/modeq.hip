@@ -37,13 +37,17 @@
 // kernels draws and filters the noise of a batch of consecutive steps: at
 // small lattices a single step's lines are far fewer blocks than the chip has
 // CUs.
-// Lines sit in LDS and are transformed by the staged passes of fft.h (any
-// extent up to 1024).  The transforms and the filtered fields are in the
+// Lines sit in LDS and are transformed in place where the extent is a power of
+// two, else by the staged passes of fft.h (any extent up to 1024).  In place
+// because a row of few steps is a chain of latencies: the staged passes look up
+// their plan and twiddles by stage (512^2 FP32, one step: rows 6.9 us in place,
+// 9.5 staged), and because one padded buffer leaves room for twice the lines
+// (1024^2, 16 steps: 98 against 121 us).  The transforms and the filtered fields are in the
 // state's precision (R = float or double; twiddles and Cholesky factors formed
 // in FP64 and rounded once).  Then k_meq_step applies the step.
 //
-// 1024^2 FP32, noise per step of a 16-step launch: rows 7.4 us (mostly the Philox
-// normals), columns 10.6 us, rows back 6.0 us; 11.6, 20.3 and 11.6 us with two
+// 1024^2 FP32, noise per step of a 16-step launch: rows 6.1 us (mostly the Philox
+// normals), columns 11.0 us, rows back 4.6 us; 11.6, 20.3 and 11.6 us with two
 // full spectra.  200 x 150 FP64, noise and one step per launch: 11.3 us, 31 us
 // when extents that are not powers of two took n^2 direct sums; 7.0 us with
 // several steps per launch (modeq_steps).
@@ -73,8 +77,6 @@ __device__ __forceinline__ void roots(cx_t<R>* tw, int n) {
     }
 }
 
-__device__ __forceinline__ bool pow2(int n) { return (n & (n - 1)) == 0; }
-
 __device__ __forceinline__ int log2i(int n) { return 31 - __clz(n); }
 
 // Position of element j in the bit-reversed order of a 2^logn line.
@@ -82,176 +84,68 @@ __device__ __forceinline__ int brev(int j, int logn) {
     return logn == 0 ? 0 : (int)(__brev((unsigned)j) >> (32 - logn));
 }
 
-// a + w x, a - w x for complex values, w's imaginary part negated for an
-// inverse transform
-template <typename R>
-__device__ __forceinline__ void bfly(cx_t<R>& a, cx_t<R>& x, cx_t<R> w, bool inverse) {
-    const R wi = inverse ? -w.y : w.y;
-    const R vr = x.x * w.x - x.y * wi, vi = x.x * wi + x.y * w.x;
-    x = Cx<R>::make(a.x - vr, a.y - vi);
-    a = Cx<R>::make(a.x + vr, a.y + vi);
+// Element i of an in-place line, and the elements a line takes: PAD as in fft.h,
+// so that the elements of a pass fall into different banks.
+template <bool PAD>
+__host__ __device__ __forceinline__ int p2_pos(int i) { return PAD ? fft_pos(i) : i; }
+template <bool PAD>
+__host__ __device__ __forceinline__ int p2_ld(int n) { return PAD ? fft_ld(n) : n; }
+
+// One in-place pass over lines of n = 2^logn elements: LR = log2 RAD radix-2
+// stages at once, of the groups of RAD elements h = 2^lh apart.  The RAD-point transform is one of fft_small with one twiddle
+// exp(-+ 2 pi i u pos / (RAD h)) per element u, before it in a decimation in
+// time (elements in bit-reversed order on the way in), behind it in a
+// decimation in frequency (on the way out).  Against a twiddle in each of the
+// stages a third of the multiplications, each of which rounds.  tw: the n roots.
+template <typename R, bool INV, bool DIF, bool PAD, int LR>
+__device__ __forceinline__ void p2_pass(cx_t<R>* b, const cx_t<R>* __restrict__ tw, int NL, int n,
+                                        int logn, int lh) {
+    constexpr int RAD = 1 << LR;
+    constexpr int br[8] = {0, RAD / 2, RAD >= 8 ? 2 : 1, RAD >= 8 ? 6 : 3, 1, 5, 3, 7};
+    const int lg = logn - LR, h = 1 << lh, sh = lg - lh;
+    for (int t = threadIdx.x; t < NL << lg; t += blockDim.x) {
+        const int L = t >> lg, q = t - (L << lg), pos = q & (h - 1);
+        const int i0 = ((q >> lh) << (lh + LR)) + pos;
+        cx_t<R>* line = b + L * p2_ld<PAD>(n);
+        cx_t<R> x[RAD];
+#pragma unroll
+        for (int u = 0; u < RAD; ++u) x[u] = line[p2_pos<PAD>(i0 + ((DIF ? u : br[u]) << lh))];
+        auto turn = [&] {
+            if (lh == 0) return;   // uniform
+#pragma unroll
+            for (int u = 1; u < RAD; ++u) {
+                cx_t<R> w = tw[(u * pos) << sh];
+                if (INV) w.y = -w.y;
+                x[u] = cx_mul<R>(x[u], w);
+            }
+        };
+        if constexpr (!DIF) turn();
+        fft_small<R, INV, RAD>(x);
+        if constexpr (DIF) turn();
+#pragma unroll
+        for (int u = 0; u < RAD; ++u) line[p2_pos<PAD>(i0 + ((DIF ? br[u] : u) << lh))] = x[u];
+    }
+    __syncthreads();
 }
 
-// In place, the NL lines b[L n .. (L + 1) n) (n = 2^logn), each loaded in
-// bit-reversed order, become their transforms in natural order
-// (exp(-+ 2 pi i j k / n), sign - forward, + inverse): decimation in time.
-// Radix-2 stages are taken three at a time: stages s, s + 1, s + 2 (half
-// h = 2^(s-1)) combine the eight elements a + k h (k = 0 .. 7) of a group, so
-// a thread loads them once, applies the three stages in registers and stores
-// them; the groups of a pass are disjoint.  The one or two stages left over
-// take a pass of four-element groups or a plain radix-2 pass.  Every
-// butterfly is the one of the stage-by-stage transform.  Ends with a barrier.
-template <typename R>
+// In place, the NL lines of b (n = 2^logn), each in bit-reversed order, become
+// their transforms in natural order.
+template <typename R, bool INV, bool PAD>
 __device__ __forceinline__ void fft_lines_dit(cx_t<R>* b, const cx_t<R>* __restrict__ tw, int NL,
-                                              int n, int logn, bool inverse) {
-    int s = 1;
-    for (; s + 2 <= logn; s += 3) {
-        const int h = 1 << (s - 1);
-        const int st1 = n >> s, st2 = n >> (s + 1), st3 = n >> (s + 2);
-        const int ng = n >> 3;
-        for (int t = threadIdx.x; t < NL * ng; t += blockDim.x) {
-            const int L = t >> (logn - 3);
-            const int q = t - L * ng;
-            const int pos = q & (h - 1);
-            const int a = L * n + ((q >> (s - 1)) << (s + 2)) + pos;
-            cx_t<R> x[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = b[a + k * h];
-            const cx_t<R> w1 = tw[pos * st1];
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) bfly<R>(x[k], x[k + 1], w1, inverse);   // stage s
-            const cx_t<R> w20 = tw[pos * st2], w21 = tw[(pos + h) * st2];
-            bfly<R>(x[0], x[2], w20, inverse);                                    // stage s + 1
-            bfly<R>(x[1], x[3], w21, inverse);
-            bfly<R>(x[4], x[6], w20, inverse);
-            bfly<R>(x[5], x[7], w21, inverse);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) bfly<R>(x[k], x[k + 4], tw[(pos + k * h) * st3], inverse);   // stage s + 2
-#pragma unroll
-            for (int k = 0; k < 8; ++k) b[a + k * h] = x[k];
-        }
-        __syncthreads();
-    }
-    for (; s + 1 <= logn; s += 2) {
-        const int h = 1 << (s - 1);
-        const int st1 = n >> s, st2 = n >> (s + 1);
-        const int nq = n >> 2;
-        for (int t = threadIdx.x; t < NL * nq; t += blockDim.x) {
-            const int L = t >> (logn - 2);
-            const int q = t - L * nq;
-            const int pos = q & (h - 1);
-            const int a = L * n + ((q >> (s - 1)) << (s + 1)) + pos;
-            cx_t<R> x0 = b[a], x1 = b[a + h], x2 = b[a + 2 * h], x3 = b[a + 3 * h];
-            const cx_t<R> w1 = tw[pos * st1];
-            bfly<R>(x0, x1, w1, inverse);   // stage s
-            bfly<R>(x2, x3, w1, inverse);
-            bfly<R>(x0, x2, tw[pos * st2], inverse);         // stage s + 1
-            bfly<R>(x1, x3, tw[(pos + h) * st2], inverse);
-            b[a] = x0;
-            b[a + h] = x1;
-            b[a + 2 * h] = x2;
-            b[a + 3 * h] = x3;
-        }
-        __syncthreads();
-    }
-    if (s == logn) {
-        const int h = 1 << (s - 1);
-        const int st1 = n >> s;
-        const int nh = n >> 1;
-        for (int t = threadIdx.x; t < NL * nh; t += blockDim.x) {
-            const int L = t >> (logn - 1);
-            const int bt = t - L * nh;
-            const int pos = bt & (h - 1);
-            const int i0 = L * n + ((bt >> (s - 1)) << s) + pos;
-            cx_t<R> u = b[i0], x = b[i0 + h];
-            bfly<R>(u, x, tw[pos * st1], inverse);
-            b[i0] = u;
-            b[i0 + h] = x;
-        }
-        __syncthreads();
-    }
+                                              int n, int logn) {
+    int lh = 0;
+    for (; lh + 3 <= logn; lh += 3) p2_pass<R, INV, false, PAD, 3>(b, tw, NL, n, logn, lh);
+    if (logn - lh == 2) p2_pass<R, INV, false, PAD, 2>(b, tw, NL, n, logn, lh);
+    if (logn - lh == 1) p2_pass<R, INV, false, PAD, 1>(b, tw, NL, n, logn, lh);
 }
-
-// (u, v) -> (u + v, (u - v) w): the decimation-in-frequency butterfly
-template <typename R>
-__device__ __forceinline__ void bfly_dif(cx_t<R>& u, cx_t<R>& v, cx_t<R> w) {
-    const R dr = u.x - v.x, di = u.y - v.y;
-    u = Cx<R>::make(u.x + v.x, u.y + v.y);
-    v = Cx<R>::make(dr * w.x - di * w.y, dr * w.y + di * w.x);
-}
-
-// In place, the NL lines of b (natural order) become their forward
-// transforms in bit-reversed order: decimation in frequency, stages from
-// half n/2 down to 1, three per pass (halves 4 q, 2 q and q combine the
-// elements a + k q, k = 0 .. 7, of a group of 8 q); one or two stages left
-// over take a pass of four-element groups (halves 2 q, q) or the last stage
-// (half 1) alone.  Every butterfly is the one of the stage-by-stage
-// transform.  Ends with a barrier.
-template <typename R>
+// From natural to bit-reversed order: the same passes the other way round.
+template <typename R, bool INV, bool PAD>
 __device__ __forceinline__ void fft_lines_dif(cx_t<R>* b, const cx_t<R>* __restrict__ tw, int NL,
                                               int n, int logn) {
-    int s = logn;
-    for (; s >= 3; s -= 3) {
-        const int q8 = 1 << (s - 3);
-        const int stA = n >> s, stB = n >> (s - 1), stC = n >> (s - 2);
-        const int ng = n >> 3;
-        for (int t = threadIdx.x; t < NL * ng; t += blockDim.x) {
-            const int L = t >> (logn - 3);
-            const int qq = t - L * ng;
-            const int pos = qq & (q8 - 1);
-            const int a = L * n + ((qq >> (s - 3)) << s) + pos;
-            cx_t<R> x[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = b[a + k * q8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) bfly_dif<R>(x[k], x[k + 4], tw[(pos + k * q8) * stA]);   // half 4 q8
-            const cx_t<R> wB0 = tw[pos * stB], wB1 = tw[(pos + q8) * stB];
-            bfly_dif<R>(x[0], x[2], wB0);                                                      // half 2 q8
-            bfly_dif<R>(x[1], x[3], wB1);
-            bfly_dif<R>(x[4], x[6], wB0);
-            bfly_dif<R>(x[5], x[7], wB1);
-            const cx_t<R> wC = tw[pos * stC];                                                  // half q8
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) bfly_dif<R>(x[k], x[k + 1], wC);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) b[a + k * q8] = x[k];
-        }
-        __syncthreads();
-    }
-    for (; s >= 2; s -= 2) {
-        const int q4 = 1 << (s - 2);
-        const int stA = n >> s, stC = n >> (s - 1);
-        const int nq = n >> 2;
-        for (int t = threadIdx.x; t < NL * nq; t += blockDim.x) {
-            const int L = t >> (logn - 2);
-            const int qq = t - L * nq;
-            const int pos = qq & (q4 - 1);
-            const int a = L * n + ((qq >> (s - 2)) << s) + pos;
-            cx_t<R> x0 = b[a], x1 = b[a + q4], x2 = b[a + 2 * q4], x3 = b[a + 3 * q4];
-            bfly_dif<R>(x0, x2, tw[pos * stA]);          // half 2 q4
-            bfly_dif<R>(x1, x3, tw[(pos + q4) * stA]);
-            const cx_t<R> wC = tw[pos * stC];         // half q4
-            bfly_dif<R>(x0, x1, wC);
-            bfly_dif<R>(x2, x3, wC);
-            b[a] = x0;
-            b[a + q4] = x1;
-            b[a + 2 * q4] = x2;
-            b[a + 3 * q4] = x3;
-        }
-        __syncthreads();
-    }
-    if (s == 1) {
-        const int nh = n >> 1;
-        for (int t = threadIdx.x; t < NL * nh; t += blockDim.x) {
-            const int L = t >> (logn - 1);
-            const int i0 = L * n + 2 * (t - L * nh);
-            cx_t<R> u = b[i0], v = b[i0 + 1];
-            bfly_dif<R>(u, v, Cx<R>::make(R(1), R(0)));
-            b[i0] = u;
-            b[i0 + 1] = v;
-        }
-        __syncthreads();
-    }
+    int lh = logn / 3 * 3;
+    if (logn - lh == 1) p2_pass<R, INV, true, PAD, 1>(b, tw, NL, n, logn, lh);
+    if (logn - lh == 2) p2_pass<R, INV, true, PAD, 2>(b, tw, NL, n, logn, lh);
+    for (lh -= 3; lh >= 0; lh -= 3) p2_pass<R, INV, true, PAD, 3>(b, tw, NL, n, logn, lh);
 }
 
 // Lower Cholesky factor of the (e, eps) noise block at wavenumber (kx, ky),
@@ -287,17 +181,18 @@ extern __shared__ __align__(16) unsigned char lds_mq[];
 
 // Half spectra of step b: e at W + 2 V b, eps hx ny values behind it, each
 // (y, kx), kx = 0 .. nx / 2.  A turn is NL rows of one step.
-template <typename Real>
+template <typename Real, bool P2>
 __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan p, int NL,
                                                             uint32_t step0, int nb,
                                                             cx_t<Real>* __restrict__ W) {
     using C = cx_t<Real>;
-    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n);
+    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n), logn = log2i(n);
     const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * a.ny;
     C* buf = (C*)lds_mq;
     C* alt = buf + NL * ld;
-    C* tw = alt + NL * ld;
-    twiddles<Real>(tw, p);
+    C* tw = P2 ? alt : alt + NL * ld;
+    if constexpr (P2) roots<Real>(tw, n);
+    else twiddles<Real>(tw, p);
     const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx;
     const uint32_t groups = (uint32_t)((a.ny + NL - 1) / NL);
     for (uint32_t g = blockIdx.x; g < groups * (uint32_t)nb; g += gridDim.x) {
@@ -311,10 +206,12 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan
                 site_normals<3, Real>((uint32_t)(x + n * (y0 + L)), step0 + b, 0u, 0u, a.k0, a.k1, z);
                 v = Cx<Real>::make(z[0], z[5]);
             }
-            buf[L * ld + fft_pos(x)] = v;
+            buf[L * ld + fft_pos(P2 ? brev(x, logn) : x)] = v;
         }
         __syncthreads();
-        const C* z = fft_lines<Real, false>(buf, alt, tw, NL, p);
+        const C* z = buf;
+        if constexpr (P2) fft_lines_dit<Real, false, true>(buf, tw, NL, n, logn);
+        else z = fft_lines<Real, false>(buf, alt, tw, NL, p);
         C* out = W + (size_t)b * 2 * V + (size_t)y0 * hx;
         for (int t = threadIdx.x; t < nl * hx; t += blockDim.x) {
             const int L = fft_div(t, rh), k = t - L * hx;
@@ -327,11 +224,12 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan
 }
 
 // NC adjacent columns kx of one step per block.  LDS lines: e of the columns,
-// then eps.  P2 (ny a power of two): in-place radix-2 passes, decimation in
+// then eps.  P2 (ny a power of two): in-place passes, decimation in
 // frequency forward and in time back, so that position j holds wavenumber
-// brev(j) in between and no line is permuted; at 1024 they take 168 us per
+// brev(j) in between and no line is permuted; at 1024 they take 177 us per
 // 16 steps where the staged passes, with two buffers and more index
-// arithmetic, take 311.
+// arithmetic, take 311.  The lines are not padded: in FP64 two padded columns
+// of 1024 leave one block per CU (411 against 305 us).
 template <typename Real, bool P2>
 __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
     ModEqArgs a, FftPlan p, int NC, cx_t<Real>* __restrict__ W) {
@@ -362,7 +260,7 @@ __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
     }
     __syncthreads();
     C* z = buf;
-    if constexpr (P2) fft_lines_dif<Real>(z, tw, 2 * NC, n, logn);
+    if constexpr (P2) fft_lines_dif<Real, false, false>(z, tw, 2 * NC, n, logn);
     else z = fft_lines<Real, false>(buf, alt, tw, 2 * NC, p);
     double se, sp;
     meq_scales(a, se, sp);
@@ -381,7 +279,7 @@ __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
         *pq = Cx<Real>::make(l21 * e.x + l22 * q.x, l21 * e.y + l22 * q.y);
     }
     __syncthreads();
-    if constexpr (P2) fft_lines_dit<Real>(z, tw, 2 * NC, n, logn, true);
+    if constexpr (P2) fft_lines_dit<Real, true, false>(z, tw, 2 * NC, n, logn);
     else z = fft_lines<Real, true>(z, z == buf ? alt : buf, tw, 2 * NC, p);
     for (int t = threadIdx.x; t < nc * n; t += blockDim.x) {
         const int j = fft_div(t, rn), c = t - j * nc;
@@ -392,17 +290,18 @@ __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
 
 // X(k) = E(k) + i P(k), k = 0 .. nx - 1, from the half spectra (E(n - k) =
 // conj E(k)); its inverse transform is xi_e + i xi_eps.
-template <typename Real>
+template <typename Real, bool P2>
 __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_ix(ModEqArgs a, FftPlan p, int NL, int nb,
                                                              const cx_t<Real>* __restrict__ W,
                                                              Real* __restrict__ xi) {
     using C = cx_t<Real>;
-    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n);
+    const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n), logn = log2i(n);
     const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * a.ny;
     C* buf = (C*)lds_mq;
     C* alt = buf + NL * ld;
-    C* tw = alt + NL * ld;
-    twiddles<Real>(tw, p);
+    C* tw = P2 ? alt : alt + NL * ld;
+    if constexpr (P2) roots<Real>(tw, n);
+    else twiddles<Real>(tw, p);
     double se, sp;
     meq_scales(a, se, sp);
     const Real fe = (Real)(se / (double)V), fp = (Real)(sp / (double)V);
@@ -421,10 +320,12 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_ix(ModEqArgs a, FftPla
                 v = k < hx ? Cx<Real>::make(e.x - q.y, e.y + q.x)
                            : Cx<Real>::make(e.x + q.y, q.x - e.y);
             }
-            buf[L * ld + fft_pos(k)] = v;
+            buf[L * ld + fft_pos(P2 ? brev(k, logn) : k)] = v;
         }
         __syncthreads();
-        const C* z = fft_lines<Real, true>(buf, alt, tw, NL, p);
+        const C* z = buf;
+        if constexpr (P2) fft_lines_dit<Real, true, true>(buf, tw, NL, n, logn);
+        else z = fft_lines<Real, true>(buf, alt, tw, NL, p);
         Real* out = xi + (size_t)b * 2 * V + (size_t)y0 * n;
         for (int t = threadIdx.x; t < nl * n; t += blockDim.x) {
             const int L = fft_div(t, rn), x = t - L * n;
@@ -666,13 +567,23 @@ size_t modeq_work_bytes(int nx, int ny, int prec) {
 namespace {
 
 // Threads for `lines` lines: one per four elements, per two where a stage of
-// direct sums has an output pair for each.
-int mq_block(int lines, const FftPlan& p) {
-    return std::min(MQ_THREADS, std::max(64, (lines * p.n / (p.any ? 2 : 4) + 63) / 64 * 64));
+// direct sums has an output pair for each; up to one per element while the
+// blocks leave the chip two wavefronts per SIMD, which then wait for each
+// thread's twiddles and normals.
+int mq_block(int lines, const FftPlan& p, size_t blocks) {
+    int per = p.any ? 2 : 4;
+    while (per > 1 && blocks * ((size_t)lines * p.n / per) < 2048 * 64) per /= 2;
+    return std::min(MQ_THREADS, std::max(64, (lines * p.n / per + 63) / 64 * 64));
 }
+
+bool is_pow2(int n) { return (n & (n - 1)) == 0; }
 
 size_t mq_lds(int lines, const FftPlan& p, size_t csize) {
     return (2 * (size_t)lines * fft_ld(p.n) + fft_twiddles(p)) * csize;
+}
+// One buffer of padded lines, transformed in place, and the roots.
+size_t mq_lds_p2(int lines, int n, size_t csize) {
+    return ((size_t)lines * fft_ld(n) + n) * csize;
 }
 
 }  // namespace
@@ -684,17 +595,20 @@ ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb) {
     // rows per block: up to 2048 elements (512 threads) and 48 KB, fewer
     // where that leaves less than 1024 turns
     s.NL = 16;
-    while (s.NL > 1 && (s.NL * a.nx > 2048 || mq_lds(s.NL, px, csize) > 49152 ||
+    auto rows = [&](int NL) {
+        return is_pow2(a.nx) ? mq_lds_p2(NL, a.nx, csize) : mq_lds(NL, px, csize);
+    };
+    while (s.NL > 1 && (s.NL * a.nx > 2048 || rows(s.NL) > 49152 ||
                         (size_t)a.ny * nb < 1024 * (size_t)s.NL))
         s.NL /= 2;
-    s.lds_rows = mq_lds(s.NL, px, csize);
+    s.lds_rows = rows(s.NL);
     // columns per block: two for the in-place passes (four columns halve the
     // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
     // for the staged ones as far as their lines and twiddles fit the LDS (931
     // elements with a direct sum, FP64, two columns: 164 KB); fewer where that
     // leaves less than 512 blocks
     const int hx = a.nx / 2 + 1;
-    const bool p2 = (a.ny & (a.ny - 1)) == 0;
+    const bool p2 = is_pow2(a.ny);
     auto cols = [&](int NC) {
         return p2 ? (2 * (size_t)NC + 1) * a.ny * csize : mq_lds(2 * NC, py, csize);
     };
@@ -725,14 +639,19 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
     const int NL = sh.NL, NC = sh.NC;
     const size_t lx = sh.lds_rows, ly = sh.lds_cols;
     const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
-    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px));
+    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px, turns));
     // a single row of 964 or more FP64 elements with a direct sum takes up to 70 KB
-    hipError_t e = mq_lds_limit(k_meq_noise_x<Real>, lx);
-    if (e == hipSuccess) e = mq_lds_limit(k_meq_noise_ix<Real>, lx);
+    auto rows = [&](auto kern, auto... args) {
+        hipError_t e = mq_lds_limit(kern, lx);
+        if (e == hipSuccess) hipLaunchKernelGGL(kern, gx, bx, lx, st, a, px, NL, args...);
+        return e;
+    };
+    const bool xp2 = is_pow2(a.nx);
+    hipError_t e = xp2 ? rows(k_meq_noise_x<Real, true>, step0, nb, W)
+                       : rows(k_meq_noise_x<Real, false>, step0, nb, W);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_meq_noise_x<Real>, gx, bx, lx, st, a, px, NL, step0, nb, W);
     const int hx = a.nx / 2 + 1;
-    const bool p2 = (a.ny & (a.ny - 1)) == 0;
+    const bool p2 = is_pow2(a.ny);
     const dim3 gy((unsigned)((hx + NC - 1) / NC), (unsigned)nb);
     if (p2) {
         e = mq_lds_limit(k_meq_filter<Real, true>, ly);
@@ -742,11 +661,12 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
     } else {
         e = mq_lds_limit(k_meq_filter<Real, false>, ly);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py)), ly, st, a,
+        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py, (size_t)gy.x * gy.y)), ly, st, a,
                            py, NC, W);
     }
-    hipLaunchKernelGGL(k_meq_noise_ix<Real>, gx, bx, lx, st, a, px, NL, nb, (const C*)W, xi);
-    return hipGetLastError();
+    e = xp2 ? rows(k_meq_noise_ix<Real, true>, nb, (const C*)W, xi)
+            : rows(k_meq_noise_ix<Real, false>, nb, (const C*)W, xi);
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace

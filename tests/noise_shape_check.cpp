@@ -1,7 +1,6 @@
 // The split of the modified-equilibrium noise over blocks for every extent,
 // both precisions and every batch of steps: the LDS its kernels ask for must
-// be what they lay out there (two buffers of lines and the twiddles) and no
-// more than a compute unit has.  Host only.  Prints the number of splits that
+// hold their lines and be no more than a compute unit has.  Host only.  Prints the number of splits that
 // do not fit and the first of them.
 
 #include <cstdio>
@@ -19,7 +18,7 @@ int main() {
         const size_t c = prec == 0 ? 8 : 16;
         // never less than the lines themselves
         const bool ok = s.NL >= 1 && s.NC >= 1 && s.lds_rows <= flb::LDS_BYTES &&
-                        s.lds_cols <= flb::LDS_BYTES && s.lds_rows >= 2 * c * s.NL * nx &&
+                        s.lds_cols <= flb::LDS_BYTES && s.lds_rows >= c * (s.NL + 1) * nx &&
                         s.lds_cols >= 2 * c * s.NC * ny;
         ++tried;
         if (!ok && bad++ == 0)
