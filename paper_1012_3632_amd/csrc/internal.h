@@ -171,12 +171,15 @@ struct ModEqArgs {
 // in FP64.
 constexpr int MODEQ_MAX_BATCH = 16;
 size_t modeq_work_bytes(int nx, int ny, int prec);
-// How the noise of nb steps is split over blocks: rows and columns per block
-// and the dynamic LDS of either, at most LDS_BYTES, what a compute unit has.
+// How the noise of nb steps is split over blocks: rows of the transforms along x
+// and of those back, columns, whether the rows and the columns are transformed
+// in FP64 there, and the dynamic LDS of each, at most LDS_BYTES, what a compute
+// unit has.
 constexpr size_t LDS_BYTES = 163840;
 struct ModEqNoiseShape {
-    int NL, NC;
-    size_t lds_rows, lds_cols;
+    int NX, NI, NC;
+    bool x64, y64;
+    size_t lds_x, lds_i, lds_cols;
 };
 ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb);
 // The noise of steps step0 .. step0 + nb - 1: spectra of step b at

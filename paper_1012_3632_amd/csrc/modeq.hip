@@ -42,12 +42,13 @@
 // because a row of few steps is a chain of latencies: the staged passes look up
 // their plan and twiddles by stage (512^2 FP32, one step: rows 6.9 us in place,
 // 9.5 staged), and because one padded buffer leaves room for twice the lines
-// (1024^2, 16 steps: 98 against 121 us).  The transforms and the filtered fields are in the
+// (1024^2, 16 steps: 98 against 121 us).  The transforms are in the
 // state's precision (R = float or double; twiddles and Cholesky factors formed
-// in FP64 and rounded once).  Then k_meq_step applies the step.
+// in FP64 and rounded once) or, some of them in FP32 runs, in FP64 (MQ_THIN); the
+// spectra and the filtered fields in the state's.  Then k_meq_step applies the step.
 //
-// 1024^2 FP32, noise per step of a 16-step launch: rows 6.1 us (mostly the Philox
-// normals), columns 11.0 us, rows back 4.6 us; 11.6, 20.3 and 11.6 us with two
+// 1024^2 FP32, noise per step of a 16-step launch: rows 9.0 us (6.1 if they were
+// FP32), columns 11.1 us, rows back 4.5 us; 11.6, 20.3 and 11.6 us with two
 // full spectra.  200 x 150 FP64, noise and one step per launch: 11.3 us, 31 us
 // when extents that are not powers of two took n^2 direct sums; 7.0 us with
 // several steps per launch (modeq_steps).
@@ -66,6 +67,16 @@ namespace {
 
 constexpr int MQ_THREADS = 1024;     // of the staged line transforms, at most
 constexpr int MQ_P2_THREADS = 256;   // of the in-place power-of-two passes
+// FP32 noise: two real fields in one complex line round at sqrt 2 times the error
+// of a line each (their independent errors at k and -k averaged out), so some
+// passes run in FP64, as few as keep the rms error below that of two full
+// spectra: the rows of a power of two, and rows and columns where nx is small
+// and one direction carries the whole error.  Relative rms error of e, two
+// spectra / all FP32 / these: 1024^2 2.44e-7 / 2.69e-7 / 2.35e-7, 128^2 2.17 /
+// 2.26 / 1.99, 32 x 1024 2.12 / 2.33 / 1.19, 3 x 1024 1.68 / 1.94 / 0.95; long
+// rows that are no power of two were direct sums and stay FP32 (200 x 150 5.55 /
+// 2.18).  1024^2, 16 steps: the rows take 144 us, 98 in FP32.
+constexpr int MQ_THIN = 64;
 
 // tw[j] = exp(-2 pi i j / n), evaluated in FP64 and rounded to R.
 template <typename R>
@@ -181,18 +192,19 @@ extern __shared__ __align__(16) unsigned char lds_mq[];
 
 // Half spectra of step b: e at W + 2 V b, eps hx ny values behind it, each
 // (y, kx), kx = 0 .. nx / 2.  A turn is NL rows of one step.
-template <typename Real, bool P2>
+template <typename Real, typename A, bool P2>
 __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan p, int NL,
                                                             uint32_t step0, int nb,
                                                             cx_t<Real>* __restrict__ W) {
-    using C = cx_t<Real>;
+    using C = cx_t<A>;
+    using S = cx_t<Real>;   // as stored
     const int n = a.nx, hx = n / 2 + 1, ld = fft_ld(n), logn = log2i(n);
     const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * a.ny;
     C* buf = (C*)lds_mq;
     C* alt = buf + NL * ld;
     C* tw = P2 ? alt : alt + NL * ld;
-    if constexpr (P2) roots<Real>(tw, n);
-    else twiddles<Real>(tw, p);
+    if constexpr (P2) roots<A>(tw, n);
+    else twiddles<A>(tw, p);
     const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx;
     const uint32_t groups = (uint32_t)((a.ny + NL - 1) / NL);
     for (uint32_t g = blockIdx.x; g < groups * (uint32_t)nb; g += gridDim.x) {
@@ -200,24 +212,24 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan
         const int y0 = (int)(g - b * groups) * NL, nl = min(NL, a.ny - y0);
         for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
             const int L = fft_div(t, rn), x = t - L * n;
-            C v = Cx<Real>::make(Real(0), Real(0));
+            C v = Cx<A>::make(A(0), A(0));
             if (L < nl) {
                 Real z[6];
                 site_normals<3, Real>((uint32_t)(x + n * (y0 + L)), step0 + b, 0u, 0u, a.k0, a.k1, z);
-                v = Cx<Real>::make(z[0], z[5]);
+                v = Cx<A>::make((A)z[0], (A)z[5]);
             }
             buf[L * ld + fft_pos(P2 ? brev(x, logn) : x)] = v;
         }
         __syncthreads();
         const C* z = buf;
-        if constexpr (P2) fft_lines_dit<Real, false, true>(buf, tw, NL, n, logn);
-        else z = fft_lines<Real, false>(buf, alt, tw, NL, p);
-        C* out = W + (size_t)b * 2 * V + (size_t)y0 * hx;
+        if constexpr (P2) fft_lines_dit<A, false, true>(buf, tw, NL, n, logn);
+        else z = fft_lines<A, false>(buf, alt, tw, NL, p);
+        S* out = W + (size_t)b * 2 * V + (size_t)y0 * hx;
         for (int t = threadIdx.x; t < nl * hx; t += blockDim.x) {
             const int L = fft_div(t, rh), k = t - L * hx;
             const C u = z[L * ld + fft_pos(k)], v = z[L * ld + fft_pos(k == 0 ? 0 : n - k)];
-            out[t] = Cx<Real>::make(Real(0.5) * (u.x + v.x), Real(0.5) * (u.y - v.y));
-            out[H + t] = Cx<Real>::make(Real(0.5) * (u.y + v.y), Real(0.5) * (v.x - u.x));
+            out[t] = Cx<Real>::make((Real)(A(0.5) * (u.x + v.x)), (Real)(A(0.5) * (u.y - v.y)));
+            out[H + t] = Cx<Real>::make((Real)(A(0.5) * (u.y + v.y)), (Real)(A(0.5) * (v.x - u.x)));
         }
         __syncthreads();   // the result is read before the next turn's loads
     }
@@ -230,38 +242,40 @@ __global__ __launch_bounds__(MQ_THREADS) void k_meq_noise_x(ModEqArgs a, FftPlan
 // 16 steps where the staged passes, with two buffers and more index
 // arithmetic, take 311.  The lines are not padded: in FP64 two padded columns
 // of 1024 leave one block per CU (411 against 305 us).
-template <typename Real, bool P2>
+template <typename Real, typename A, bool P2>
 __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
     ModEqArgs a, FftPlan p, int NC, cx_t<Real>* __restrict__ W) {
-    using C = cx_t<Real>;
+    using C = cx_t<A>;
+    using S = cx_t<Real>;   // as stored
     // neighbouring column groups share cache lines: same XCD, one L2
     const uint32_t lin = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
     const int n = a.ny, hx = a.nx / 2 + 1, ld = P2 ? n : fft_ld(n), logn = log2i(n);
     const uint32_t step = lin / gridDim.x;
     const int c0 = (int)(lin - step * gridDim.x) * NC, nc = min(NC, hx - c0);
     const size_t V = (size_t)a.nx * a.ny, H = (size_t)hx * n;
-    C* base = W + (size_t)step * 2 * V + c0;
+    S* base = W + (size_t)step * 2 * V + c0;
     C* buf = (C*)lds_mq;
     C* alt = buf + 2 * NC * ld;
     C* tw = P2 ? alt : alt + 2 * NC * ld;
-    if constexpr (P2) roots<Real>(tw, n);
-    else twiddles<Real>(tw, p);
+    if constexpr (P2) roots<A>(tw, n);
+    else twiddles<A>(tw, p);
     const float rc = 1.0f / (float)NC, rn = 1.0f / (float)nc;
     auto pos = [](int i) { return P2 ? i : fft_pos(i); };
     for (int t = threadIdx.x; t < NC * n; t += blockDim.x) {
         const int j = fft_div(t, rc), c = t - j * NC;
-        C e = Cx<Real>::make(Real(0), Real(0)), q = e;
+        C e = Cx<A>::make(A(0), A(0)), q = e;
         if (c < nc) {
-            e = base[(size_t)j * hx + c];
-            q = base[H + (size_t)j * hx + c];
+            const S es = base[(size_t)j * hx + c], qs = base[H + (size_t)j * hx + c];
+            e = Cx<A>::make((A)es.x, (A)es.y);
+            q = Cx<A>::make((A)qs.x, (A)qs.y);
         }
         buf[c * ld + pos(j)] = e;
         buf[(NC + c) * ld + pos(j)] = q;
     }
     __syncthreads();
     C* z = buf;
-    if constexpr (P2) fft_lines_dif<Real, false, false>(z, tw, 2 * NC, n, logn);
-    else z = fft_lines<Real, false>(buf, alt, tw, 2 * NC, p);
+    if constexpr (P2) fft_lines_dif<A, false, false>(z, tw, 2 * NC, n, logn);
+    else z = fft_lines<A, false>(buf, alt, tw, 2 * NC, p);
     double se, sp;
     meq_scales(a, se, sp);
     for (int t = threadIdx.x; t < nc * n; t += blockDim.x) {
@@ -271,20 +285,21 @@ __global__ __launch_bounds__(P2 ? MQ_P2_THREADS : MQ_THREADS) void k_meq_filter(
         if constexpr (P2) cy = (double)tw[brev(j, logn)].x;
         else sincospi(2.0 * (double)j / (double)n, &sn, &cy);
         meq_chol(a, cx, cy, d11, d21, d22);
-        const Real l11 = (Real)(d11 / se), l21 = (Real)(d21 / sp), l22 = (Real)(d22 / sp);
+        const A l11 = (A)(d11 / se), l21 = (A)(d21 / sp), l22 = (A)(d22 / sp);
         C* pe = z + c * ld + pos(j);
         C* pq = pe + NC * ld;
         const C e = *pe, q = *pq;
-        *pe = Cx<Real>::make(l11 * e.x, l11 * e.y);
-        *pq = Cx<Real>::make(l21 * e.x + l22 * q.x, l21 * e.y + l22 * q.y);
+        *pe = Cx<A>::make(l11 * e.x, l11 * e.y);
+        *pq = Cx<A>::make(l21 * e.x + l22 * q.x, l21 * e.y + l22 * q.y);
     }
     __syncthreads();
-    if constexpr (P2) fft_lines_dit<Real, true, false>(z, tw, 2 * NC, n, logn);
-    else z = fft_lines<Real, true>(z, z == buf ? alt : buf, tw, 2 * NC, p);
+    if constexpr (P2) fft_lines_dit<A, true, false>(z, tw, 2 * NC, n, logn);
+    else z = fft_lines<A, true>(z, z == buf ? alt : buf, tw, 2 * NC, p);
     for (int t = threadIdx.x; t < nc * n; t += blockDim.x) {
         const int j = fft_div(t, rn), c = t - j * nc;
-        base[(size_t)j * hx + c] = z[c * ld + pos(j)];
-        base[H + (size_t)j * hx + c] = z[(NC + c) * ld + pos(j)];
+        const C e = z[c * ld + pos(j)], q = z[(NC + c) * ld + pos(j)];
+        base[(size_t)j * hx + c] = Cx<Real>::make((Real)e.x, (Real)e.y);
+        base[H + (size_t)j * hx + c] = Cx<Real>::make((Real)q.x, (Real)q.y);
     }
 }
 
@@ -594,14 +609,20 @@ ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb) {
     ModEqNoiseShape s;
     // rows per block: up to 2048 elements (512 threads) and 48 KB, fewer
     // where that leaves less than 1024 turns
-    s.NL = 16;
-    auto rows = [&](int NL) {
-        return is_pow2(a.nx) ? mq_lds_p2(NL, a.nx, csize) : mq_lds(NL, px, csize);
+    auto row_bytes = [&](int NL, size_t size) {
+        return is_pow2(a.nx) ? mq_lds_p2(NL, a.nx, size) : mq_lds(NL, px, size);
     };
-    while (s.NL > 1 && (s.NL * a.nx > 2048 || rows(s.NL) > 49152 ||
-                        (size_t)a.ny * nb < 1024 * (size_t)s.NL))
-        s.NL /= 2;
-    s.lds_rows = rows(s.NL);
+    auto rows = [&](size_t size, size_t* lds) {
+        int NL = 16;
+        while (NL > 1 && (NL * a.nx > 2048 || row_bytes(NL, size) > 49152 ||
+                          (size_t)a.ny * nb < 1024 * (size_t)NL))
+            NL /= 2;
+        *lds = row_bytes(NL, size);
+        return NL;
+    };
+    s.x64 = prec != 0 || is_pow2(a.nx) || a.nx <= MQ_THIN;
+    s.NX = rows(s.x64 ? sizeof(double2) : csize, &s.lds_x);
+    s.NI = rows(csize, &s.lds_i);
     // columns per block: two for the in-place passes (four columns halve the
     // resident blocks, 212 us at 1024^2), up to four of at most 4096 elements
     // for the staged ones as far as their lines and twiddles fit the LDS (931
@@ -609,8 +630,10 @@ ModEqNoiseShape modeq_noise_shape(const ModEqArgs& a, int prec, int nb) {
     // leaves less than 512 blocks
     const int hx = a.nx / 2 + 1;
     const bool p2 = is_pow2(a.ny);
+    s.y64 = prec != 0 || a.nx <= MQ_THIN;
+    const size_t ysize = s.y64 ? sizeof(double2) : csize;
     auto cols = [&](int NC) {
-        return p2 ? (2 * (size_t)NC + 1) * a.ny * csize : mq_lds(2 * NC, py, csize);
+        return p2 ? (2 * (size_t)NC + 1) * a.ny * ysize : mq_lds(2 * NC, py, ysize);
     };
     s.NC = p2 ? 2 : 4;
     while (s.NC > 1 && ((!p2 && 2 * s.NC * a.ny > 4096) || cols(s.NC) > LDS_BYTES ||
@@ -636,36 +659,35 @@ hipError_t launch_noise_t(const ModEqArgs& a, uint32_t step0, int nb, void* Wv, 
     C* W = (C*)Wv;
     const FftPlan px = fft_plan(a.nx), py = fft_plan(a.ny);
     const ModEqNoiseShape sh = modeq_noise_shape(a, sizeof(Real) == 4 ? 0 : 1, nb);
-    const int NL = sh.NL, NC = sh.NC;
-    const size_t lx = sh.lds_rows, ly = sh.lds_cols;
-    const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
-    const dim3 gx((unsigned)std::min<size_t>(turns, 2048)), bx(mq_block(NL, px, turns));
+    const bool xp2 = is_pow2(a.nx), yp2 = is_pow2(a.ny);
     // a single row of 964 or more FP64 elements with a direct sum takes up to 70 KB
-    auto rows = [&](auto kern, auto... args) {
-        hipError_t e = mq_lds_limit(kern, lx);
-        if (e == hipSuccess) hipLaunchKernelGGL(kern, gx, bx, lx, st, a, px, NL, args...);
+    auto rows = [&](auto kern, int NL, size_t lds, auto... args) {
+        const size_t turns = (size_t)((a.ny + NL - 1) / NL) * nb;
+        hipError_t e = mq_lds_limit(kern, lds);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min<size_t>(turns, 2048)),
+                               dim3(mq_block(NL, px, turns)), lds, st, a, px, NL, args...);
         return e;
     };
-    const bool xp2 = is_pow2(a.nx);
-    hipError_t e = xp2 ? rows(k_meq_noise_x<Real, true>, step0, nb, W)
-                       : rows(k_meq_noise_x<Real, false>, step0, nb, W);
+    auto cols = [&](auto kern) {
+        const dim3 grid((unsigned)((a.nx / 2 + sh.NC) / sh.NC), (unsigned)nb);
+        const int nt = yp2 ? MQ_P2_THREADS : mq_block(2 * sh.NC, py, (size_t)grid.x * grid.y);
+        hipError_t e = mq_lds_limit(kern, sh.lds_cols);
+        if (e == hipSuccess) hipLaunchKernelGGL(kern, grid, dim3(nt), sh.lds_cols, st, a, py, sh.NC, W);
+        return e;
+    };
+    auto rows_x = [&](auto kern) { return rows(kern, sh.NX, sh.lds_x, step0, nb, W); };
+    hipError_t e = xp2      ? rows_x(k_meq_noise_x<Real, double, true>)
+                   : sh.x64 ? rows_x(k_meq_noise_x<Real, double, false>)
+                            : rows_x(k_meq_noise_x<Real, Real, false>);
     if (e != hipSuccess) return e;
-    const int hx = a.nx / 2 + 1;
-    const bool p2 = is_pow2(a.ny);
-    const dim3 gy((unsigned)((hx + NC - 1) / NC), (unsigned)nb);
-    if (p2) {
-        e = mq_lds_limit(k_meq_filter<Real, true>, ly);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_meq_filter<Real, true>), gy, dim3(MQ_P2_THREADS), ly, st, a, py, NC,
-                           W);
-    } else {
-        e = mq_lds_limit(k_meq_filter<Real, false>, ly);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_meq_filter<Real, false>), gy, dim3(mq_block(2 * NC, py, (size_t)gy.x * gy.y)), ly, st, a,
-                           py, NC, W);
-    }
-    e = xp2 ? rows(k_meq_noise_ix<Real, true>, nb, (const C*)W, xi)
-            : rows(k_meq_noise_ix<Real, false>, nb, (const C*)W, xi);
+    if (sh.y64)
+        e = yp2 ? cols(k_meq_filter<Real, double, true>) : cols(k_meq_filter<Real, double, false>);
+    else
+        e = yp2 ? cols(k_meq_filter<Real, Real, true>) : cols(k_meq_filter<Real, Real, false>);
+    if (e != hipSuccess) return e;
+    e = xp2 ? rows(k_meq_noise_ix<Real, true>, sh.NI, sh.lds_i, nb, (const C*)W, xi)
+            : rows(k_meq_noise_ix<Real, false>, sh.NI, sh.lds_i, nb, (const C*)W, xi);
     return e != hipSuccess ? e : hipGetLastError();
 }
 

@@ -15,15 +15,17 @@ int main() {
         a.ny = ny;
         a.prec = prec;
         const flb::ModEqNoiseShape s = flb::modeq_noise_shape(a, prec, nb);
-        const size_t c = prec == 0 ? 8 : 16;
+        const size_t c = prec == 0 ? 8 : 16, cx = s.x64 ? 16 : c, cy = s.y64 ? 16 : c;
         // never less than the lines themselves
-        const bool ok = s.NL >= 1 && s.NC >= 1 && s.lds_rows <= flb::LDS_BYTES &&
-                        s.lds_cols <= flb::LDS_BYTES && s.lds_rows >= c * (s.NL + 1) * nx &&
-                        s.lds_cols >= 2 * c * s.NC * ny;
+        const bool ok = s.NX >= 1 && s.NI >= 1 && s.NC >= 1 && s.lds_x <= flb::LDS_BYTES &&
+                        s.lds_i <= flb::LDS_BYTES && s.lds_cols <= flb::LDS_BYTES &&
+                        s.lds_x >= cx * (s.NX + 1) * nx && s.lds_i >= c * (s.NI + 1) * nx &&
+                        s.lds_cols >= 2 * cy * s.NC * ny;
         ++tried;
         if (!ok && bad++ == 0)
-            std::printf("first: %d x %d prec %d batch %d: NL %d, %zu bytes; NC %d, %zu bytes\n", nx,
-                        ny, prec, nb, s.NL, s.lds_rows, s.NC, s.lds_cols);
+            std::printf("first: %d x %d prec %d batch %d: rows %d, %zu and %d, %zu bytes; columns "
+                        "%d, %zu bytes\n", nx, ny, prec, nb, s.NX, s.lds_x, s.NI, s.lds_i, s.NC,
+                        s.lds_cols);
     };
     for (int prec = 0; prec < 2; ++prec) {
         for (int nx = 1; nx <= 1024; ++nx)

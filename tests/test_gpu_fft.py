@@ -109,3 +109,27 @@ def test_modeq_long_staged_rows(nx, ny):
     a.step(16)
     b.step(16)
     assert torch.equal(a.f, b.f)
+
+
+# relative rms errors of the FP32 (e, eps) noise of step 0 .. against the oracle's, when each
+# field was transformed by itself over the full spectrum: what a packed pair may not exceed
+NOISE_RMS = [((1024, 1024), 2.44e-7, 2.91e-7), ((128, 128), 2.17e-7, 2.21e-7), ((32, 1024), 2.12e-7, 2.15e-7),
+             ((64, 1024), 2.22e-7, 5.59e-7), ((3, 1024), 1.68e-7, 1.72e-7), ((1024, 32), 2.22e-7, 2.25e-7),
+             ((17, 64), 1.95e-7, 1.96e-7), ((9, 9), 1.61e-7, 1.67e-7), ((100, 1024), 3.31e-7, 6.02e-7)]
+
+
+@pytest.mark.parametrize("n,e,eps", NOISE_RMS)
+def test_modeq_noise_rms_error(n, e, eps):
+    from oracle import modeq as OM
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    d = dict(nx=n[0], ny=n[1], rho0=1.0, kT=1e-7, cs2_0=0.265 ** 2, kappa=0.08, seed=7)
+    sim = ModEq(ModEqParams(precision="fp32", **d))
+    err, ref = np.zeros(2), np.zeros(2)
+    for k in range(max(2, min(400, 200000 // (n[0] * n[1])))):
+        xi = sim.noise(k).cpu().numpy().astype(np.float64)
+        want = OM.noise(k, OM.ModEqParams(**d))
+        for i, j in enumerate((0, 5)):
+            err[i] += ((xi[i] - want[j]) ** 2).sum()
+            ref[i] += (want[j] ** 2).sum()
+    got = np.sqrt(err / ref)
+    assert got[0] <= e and got[1] <= eps, got
