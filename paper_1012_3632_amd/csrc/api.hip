@@ -701,27 +701,27 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
         *ms_out = ms / (float)(repeats * per_call);
         return r;
     };
+    // a force step that reads a density field pays for its pass; a
+    // partial-density march for the completion of the next density
+    auto ordinary_step = [&](int c, double* part, void* in, void* out) {
+        const bool pd = config_partial_density(h->spec, c);
+        hipError_t r = hipSuccess;
+        if (h->spec.force && !config_fused(h->spec, c) && !pd)
+            r = launch_density(h->spec, in, h->drho, st);
+        if (r == hipSuccess)
+            r = launch_step(h->spec, c, in, out, h->drho, nullptr, h->step, part, st, nullptr,
+                            step_work(h, c));
+        if (r == hipSuccess && pd)
+            r = launch_density_fix(h->spec, c, out, h->rho_part, h->drho, st);
+        return r;
+    };
     for (int mode = 0; mode < 2 && e == hipSuccess; ++mode) {
         double* part = mode ? h->stats : nullptr;
         for (int c = 0; c < ncfg && e == hipSuccess; ++c) {
             if (config_in_place(h->spec, c) || sparse(c)) continue;   // pairs: timed below
             float ms = 0.f;
-            // a force step that reads a density field pays for its pass; a
-            // partial-density march for the completion of the next density
-            const bool pd = config_partial_density(h->spec, c);
-            const bool pass = h->spec.force && !config_fused(h->spec, c) && !pd;
             e = timed([&](int k) {
-                void* in = (k & 1) ? B : A;
-                void* out = (k & 1) ? A : B;
-                if (pass) {
-                    hipError_t r = launch_density(h->spec, in, h->drho, st);
-                    if (r != hipSuccess) return r;
-                }
-                hipError_t r = launch_step(h->spec, c, in, out, h->drho, nullptr, h->step, part, st,
-                                           nullptr, step_work(h, c));
-                if (r == hipSuccess && pd)
-                    r = launch_density_fix(h->spec, c, out, h->rho_part, h->drho, st);
-                return r;
+                return (k & 1) ? ordinary_step(c, part, B, A) : ordinary_step(c, part, A, B);
             }, 1, &ms);
             if (e == hipSuccess && ms < bt[mode]) {
                 bt[mode] = ms;
@@ -743,48 +743,49 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     std::vector<int> cands;
     for (int c = 0; c < ncfg; ++c)
         if (config_in_place(h->spec, c) && !sparse(c)) cands.push_back(c);
-    auto pair = [&](int c) {
-        hipError_t r = launch_step_in_place(h->spec, c, 0, A, nullptr, h->step, h->stats, st);
+    auto pair = [&](int c, double* part) {
+        hipError_t r = launch_step_in_place(h->spec, c, 0, A, nullptr, h->step, part, st);
         if (r == hipSuccess)
-            r = launch_step_in_place(h->spec, c, 1, A, nullptr, h->step + 1, h->stats, st);
+            r = launch_step_in_place(h->spec, c, 1, A, nullptr, h->step + 1, part, st);
         return r;
     };
-    // two ordinary steps with statistics, A -> B -> A
-    auto ordinary = [&](int c) {
-        hipError_t r = launch_step(h->spec, c, A, B, h->drho, nullptr, h->step, h->stats, st);
-        if (r == hipSuccess)
-            r = launch_step(h->spec, c, B, A, h->drho, nullptr, h->step + 1, h->stats, st);
-        return r;
+    // two ordinary steps, A -> B -> A
+    auto ordinary = [&](int c, double* part) {
+        hipError_t r = ordinary_step(c, part, A, B);
+        return r == hipSuccess ? ordinary_step(c, part, B, A) : r;
     };
-    auto time_pairs = [&](auto&& two, int c, int n, float* ms_per_step) {
+    // ms per step of n calls of `steps` steps each
+    auto trial = [&](auto&& call, int n, int steps, float* ms_per_step) {
         hipError_t r = hipEventRecord(e0, st);
-        for (int k = 0; k < n && r == hipSuccess; ++k) r = two(c);
+        for (int k = 0; k < n && r == hipSuccess; ++k) r = call();
         if (r == hipSuccess) r = hipEventRecord(e1, st);
         if (r == hipSuccess) r = hipEventSynchronize(e1);
         float ms = 0.f;
         if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);
-        *ms_per_step = ms / (float)(2 * n);
+        *ms_per_step = ms / (float)(steps * n);
         return r;
     };
     if (!cands.empty() && e == hipSuccess) {
         float t1 = 0.f;
-        e = pair(cands[0]);
-        if (e == hipSuccess) e = time_pairs(pair, cands[0], 1, &t1);
+        auto first = [&] { return pair(cands[0], h->stats); };
+        e = first();
+        if (e == hipSuccess) e = trial(first, 1, 2, &t1);
         const float pair_est = std::max(2.f * t1, 1e-3f);   // ms per pair
         const int settle = std::min(400, std::max(2, (int)(4.f / pair_est)));
         const int per = std::min(200, std::max(repeats, (int)(2.f / pair_est)));
-        for (int k = 0; k < settle && e == hipSuccess; ++k) e = pair(cands[0]);
+        for (int k = 0; k < settle && e == hipSuccess; ++k) e = first();
         std::vector<float> bt_c(cands.size(), 1e30f);
         for (int round = 0; round < std::max(3, repeats) && e == hipSuccess; ++round) {
             float ms = 0.f;
             for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i) {
-                e = time_pairs(pair, cands[i], per, &ms);
+                e = trial([&] { return pair(cands[i], h->stats); }, per, 2, &ms);
                 if (e == hipSuccess) bt_c[i] = std::min(bt_c[i], ms);
             }
-            if (e == hipSuccess) e = ordinary(bi[1]);
-            if (e == hipSuccess) e = time_pairs(ordinary, bi[1], per, &ms);
+            auto ord = [&] { return ordinary(bi[1], h->stats); };
+            if (e == hipSuccess) e = ord();
+            if (e == hipSuccess) e = trial(ord, per, 2, &ms);
             if (e == hipSuccess) ord_ms = std::min(ord_ms, ms);
-            if (e == hipSuccess) e = pair(cands[0]);
+            if (e == hipSuccess) e = first();
         }
         bt[1] = std::min(bt[1], ord_ms);
         for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i)
@@ -793,20 +794,45 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
                 best_pair = cands[i];
             }
     }
-    // several steps per launch against the fastest of the others
+    // pairs are used when they beat ordinary steps with statistics
+    const int pair_cfg = best_pair >= 0 && pair_ms < bt[1] ? best_pair : -1;
+    // Several steps per launch against the steps chosen above, in turn in the
+    // same kind of trial (about 1 ms, at most 200 calls, best of three rounds): a
+    // few launches after one of another kind cost up to 20 % more than in a run.
+    // The others have to be faster by 3 %, since they alone lose in calls of a few
+    // hundred steps, on buffers not yet settled and at the host's launch rate
+    // (ideal gas FP32, 360^2: trials 3.6 us a step here, 3.5 for the others, calls
+    // of 240 steps 3.6 and 3.5 to 4.5; 400^2 3.7 and 3.8, 3.7 and 4.5).
     bool multi[2] = {false, false};
     for (int mode = 0; mode < 2 && e == hipSuccess; ++mode) {
         const int T = multi_steps(h->spec, mode == 1, h->slots);
         if (T == 0) continue;
-        float ms = 0.f;
-        e = timed([&](int k) {
-            MultiArgs a{};
-            a.out[T - 1] = (k & 1) ? A : B;
-            a.mask = mode ? (1u << T) - 1u : 0u;
-            return launch_multi(h->spec, mode == 1, h->slots, (k & 1) ? B : A, a, nullptr, h->step,
-                                h->stats, st);
-        }, T, &ms);
-        multi[mode] = ms < std::min(bt[mode], pair_ms);
+        double* part = mode ? h->stats : nullptr;
+        auto several = [&] {   // A -> B -> A
+            hipError_t r = hipSuccess;
+            for (int k = 0; k < 2 && r == hipSuccess; ++k) {
+                MultiArgs a{};
+                a.out[T - 1] = k ? A : B;
+                a.mask = mode ? (1u << T) - 1u : 0u;
+                r = launch_multi(h->spec, mode == 1, h->slots, k ? B : A, a, nullptr, h->step, h->stats,
+                                 st);
+            }
+            return r;
+        };
+        auto two = [&] { return pair_cfg >= 0 ? pair(pair_cfg, part) : ordinary(bi[mode], part); };
+        const int per = std::min(200, std::max(repeats, (int)(1.f / std::max(bt[mode], 1e-3f))));
+        float best_multi = 1e30f, best_other = 1e30f;
+        for (int round = 0; round < 3 && e == hipSuccess; ++round) {
+            auto take = [&](auto&& call, int n, int steps, float* least) {
+                float ms = 0.f;
+                if (e == hipSuccess) e = call();   // not the first of its kind
+                if (e == hipSuccess) e = trial(call, n, steps, &ms);
+                if (e == hipSuccess) *least = std::min(*least, ms);
+            };
+            take(several, std::max(1, per / T), 2 * T, &best_multi);
+            take(two, per, 2, &best_other);
+        }
+        multi[mode] = e == hipSuccess && best_multi < 1.03f * best_other;
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
@@ -820,8 +846,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     h->cfg = bi[0];
     h->cfg_stats = bi[1];
     for (int m = 0; m < 2; ++m) h->multi[m] = multi[m];
-    // pairs are used when they beat ordinary steps with statistics
-    h->pair_cfg = (best_pair >= 0 && pair_ms < bt[1]) ? best_pair : -1;
+    h->pair_cfg = pair_cfg;
     for (int m = 0; m < 2; ++m) {
         if (best) best[m] = bi[m];
         if (best_ms) best_ms[m] = bt[m];
