@@ -113,3 +113,92 @@ def test_flat_force_graph_replays(n):
         assert torch.equal(eager.state(), graph.state())
     for a, b in zip(eager.moments(), graph.moments()):
         assert np.array_equal(a, b)
+
+
+# the largest boxes of the flat shapes: populations (record count and plane
+# offsets) just below 2^32 bytes, (V - 1) nx or (V / nx - 1) ny (the division by
+# a reciprocal) just below 2^32, and one box past each limit, which runs the
+# row tile
+LARGEST = [("D3Q19", "fp32", (76, 743, 1000), True), ("D3Q19", "fp64", (152, 304, 611), True),
+           ("D3Q19", "fp32", (256, 256, 256), True), ("D3Q19", "fp32", (16384, 16, 1), True),
+           ("D3Q19", "fp64", (1, 256, 65536), True), ("D2Q9", "fp64", (256, 65535, 1), True),
+           ("D3Q19", "fp32", (76, 744, 1000), False), ("D3Q19", "fp64", (16385, 16, 1), False)]
+
+
+def _fits(lattice, precision, n):
+    V, Q, rb = n[0] * n[1] * n[2], 19 if lattice == "D3Q19" else 9, 4 if precision == "fp32" else 8
+    return Q * V * rb < 2 ** 32 and (V - 1) * n[0] < 2 ** 32 and (V // n[0] - 1) * n[1] < 2 ** 32
+
+
+@pytest.mark.parametrize("lattice,precision,n,fits", LARGEST)
+def test_flat_shapes_at_their_limits(lattice, precision, n, fits):
+    """A pair and a lone step of both flat shapes against the 32 x 8 tile."""
+    from paper_1012_3632_amd import Simulation
+    assert _fits(lattice, precision, n) == fits
+    p = gpu_params(lattice=lattice, precision=precision, nx=n[0], ny=n[1], nz=n[2], **KW)
+    ref, sim = Simulation(p), Simulation(p)
+    ref.set_launch(3)
+    for cfg in (15, 16):
+        sim.set_launch(cfg)
+        for s in (ref, sim):
+            s.step(3, stats_stride=1)
+        for a, b in zip(sim.state(), ref.state()):   # plane by plane
+            assert torch.equal(a, b), cfg
+    (s0, q0, n0), (s1, q1, n1) = ref.moments(), sim.moments()
+    assert n0 == n1 == 6
+    tol = 1e-12 if precision == "fp64" else 5e-6   # of FP32 sums over other rows, as for every shape
+    np.testing.assert_allclose(q1, q0, rtol=tol, atol=0)
+    assert np.all(np.abs(s1 - s0) <= tol * np.sqrt(n0 * np.prod(n) * q0) + 1e-300)
+
+
+@pytest.mark.parametrize("precision,n,fits", [c[1:] for c in LARGEST if c[0] == "D3Q19"])
+def test_flat_force_at_its_limits(precision, n, fits):
+    """The same for the force step (against the 32 x 4 x 2 tile)."""
+    from paper_1012_3632_amd import Simulation
+    tol = 1e-12 if precision == "fp64" else 5e-6   # as for every force shape against another
+    p = gpu_params(lattice="D3Q19", precision=precision, nx=n[0], ny=n[1], nz=n[2], eta=1,
+                   force_model=1, a=-0.01, b=0.1, rho_c=1.0, kappa=0.05, **KW)
+    ref, sim = Simulation(p), Simulation(p)   # the noise makes the density
+    ref.set_launch(0)
+    sim.set_launch(12)
+    for s in (ref, sim):
+        s.step(3)
+    for a, b in zip(sim.state(), ref.state()):
+        assert float((a - b).abs().max()) <= tol * float(b.abs().max())
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_forward_steps_beside_a_recompute(precision):
+    """Forward steps of the default (flat) force shape on one stream while a
+    reverse pass of the same handle recomputes its segments on others: both
+    give what they give alone, bit for bit."""
+    from paper_1012_3632_amd import Simulation
+    n, every, nsteps = (48, 40, 36), 4, 16
+    p = gpu_params(lattice="D3Q19", precision=precision, nx=n[0], ny=n[1], nz=n[2], eta=1,
+                   force_model=1, a=-0.01, b=0.1, rho_c=1.0, kappa=0.05, **dict(KW, kT=1e-6))
+    sim = Simulation(p, drho_init=W.initial_drho(n[::-1], 9, 0.01))
+    assert sim.launch_shape(sim.launch_configs()[1][0])[7] == 3
+    ckpts = []
+    for _ in range(0, nsteps, every):
+        ckpts.append(sim.state().clone())
+        sim.step(every)
+    start = sim.state().clone()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    seed = torch.randn(start.shape, generator=g, device="cuda", dtype=torch.float64).to(start.dtype)
+    want = seed.clone()
+    work = sim.adjoint_run(ckpts, want, every, nsteps)
+    sim.step(40)
+    end = sim.state().clone()
+    torch.cuda.synchronize()
+    fwd, rev = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(3):
+        got = seed.clone()
+        sim.load_state(start)
+        sim.seek(nsteps)
+        torch.cuda.synchronize()
+        sim.step(20, stream=fwd)
+        sim.adjoint_run(ckpts, got, every, nsteps, work=work, stream=rev)
+        sim.step(20, stream=fwd)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert torch.equal(sim.state(), end)
