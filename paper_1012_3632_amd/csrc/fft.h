@@ -79,10 +79,13 @@ __host__ __device__ __forceinline__ int fft_twiddles(const FftPlan& p) {
     return p.any ? 2 * p.n : p.n;
 }
 
-// a / b for 0 <= a < 2^16, 1 <= b, with rb = 1.0f / b: (a + 1/2) / b is at
-// least 1 / (2 b) from an integer, beyond the rounding of the two FP32
-// operations for quotients below 2^11.
-__device__ __forceinline__ int fft_div(int a, float rb) { return (int)(((float)a + 0.5f) * rb); }
+// a / b for 0 <= a < 2^22 - 1, 1 <= b <= 2^22, with rb = 1.0f / b: a + 1/2 is
+// exact, the reciprocal and the product each round by at most 2^-24 of their
+// value, so the quotient errs by less than (a + 1/2) / b 2^-23, below the 1 / (2 b)
+// that (a + 1/2) / b is at least from an integer.
+__host__ __device__ __forceinline__ int fft_div(int a, float rb) {
+    return (int)(((float)a + 0.5f) * rb);
+}
 
 // The twiddles of a plan, evaluated in FP64 and rounded to R: entry
 // Ns - 1 + (u - 1) Ns + k = exp(-2 pi i u k / (Ns r)) of the stage after Ns,

@@ -39,6 +39,13 @@ def test_field_spectrum_every_radix(shape):
     assert np.abs(spec.cpu().numpy() - start - ref).max() <= tol
 
 
+@pytest.mark.parametrize("shape", [(1, 1024, 1024, 2), (2, 700, 999, 1), (3, 1023, 513, 1)])
+def test_field_spectrum_of_many_rows(shape):
+    """More rows per field than 2^17: the row index of a line is a division of
+    numbers past 2^16."""
+    test_field_spectrum_every_radix(shape)
+
+
 # rows and columns that do not divide a block's share, every radix, primes, and
 # a power of two along one axis only (the columns' in-place passes)
 NOISE = [(17, 40, {}), (96, 101, {}), (60, 1024, {}), (1024, 77, {}), (7, 512, {}), (300, 210, {}),

@@ -1,7 +1,8 @@
 """Host-side checks of the modified-equilibrium model (no GPU needed): the LDS
 of its noise kernels fits a compute unit, and the limit of every launch, at the
 extents, precisions and batches that the model accepts; a run makes no copy of
-the populations that its steps can do without."""
+the populations that its steps can do without; the division that the line
+transforms index by is exact."""
 
 import os
 import shutil
@@ -39,3 +40,7 @@ def test_noise_launches_raise_their_lds_limit(tmp_path):
 
 def test_even_runs_make_no_copy(tmp_path):
     assert _run(tmp_path, "modeq_run_check").endswith(" 0 with a copy too many\n")
+
+
+def test_reciprocal_division(tmp_path):
+    assert _run(tmp_path, "fft_div_check").endswith(" 0 wrong\n")
