@@ -196,9 +196,9 @@ flb_status batch_layout(const flb_params* p, int32_t nrep, const int32_t* dims,
 
 }  // namespace
 
-// Consecutive replicas [r0, r1), whose tiles are [t0, t1).
+// The tiles [t0, t1) of consecutive replicas.
 struct BatchGroup {
-    uint32_t r0, r1, t0, t1;
+    uint32_t t0, t1;
 };
 
 struct flb_batch {
@@ -286,7 +286,7 @@ hipError_t batch_one(flb_batch* b, int kind, const BatchGroup& G, const void* fi
     return hipGetLastError();
 }
 
-BatchGroup batch_all(const flb_batch* b) { return BatchGroup{0, (uint32_t)b->nrep, 0, b->ntiles}; }
+BatchGroup batch_all(const flb_batch* b) { return BatchGroup{0, b->ntiles}; }
 
 // Consecutive replicas up to `bytes` of populations per group (a replica
 // larger than that forms a group of its own).
@@ -298,13 +298,13 @@ std::vector<BatchGroup> batch_groups(const flb_batch* b, uint64_t bytes) {
     for (uint32_t r = 0; r < (uint32_t)R.size(); ++r) {
         const uint64_t rb = (uint64_t)b->q * R[r].V * b->rb;
         if (r > r0 && acc + rb > bytes) {
-            out.push_back({r0, r, R[r0].tile0, R[r].tile0});
+            out.push_back({R[r0].tile0, R[r].tile0});
             r0 = r;
             acc = 0;
         }
         acc += rb;
     }
-    out.push_back({r0, (uint32_t)R.size(), R[r0].tile0, b->ntiles});
+    out.push_back({R[r0].tile0, b->ntiles});
     return out;
 }
 
