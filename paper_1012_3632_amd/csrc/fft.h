@@ -95,13 +95,16 @@ __device__ __forceinline__ void twiddles(cx_t<R>* tw, const FftPlan& p) {
     for (int e = threadIdx.x; e < fft_twiddles(p); e += blockDim.x) {
         int num = e - p.n, den = p.n;   // exp(-2 pi i num / den)
         if (num < 0) {
-            int Ns = 1, r = 1;
-            for (int s = 0; s < p.stages; ++s) {
-                r = p.radix[s];
-                if (e < Ns * r - 1) break;
-                Ns *= r;
+            int Ns = 1, r = max(p.radix[0], 1);   // e's stage: the last that starts at or before it
+            for (int s = 1, at = r; s < p.stages; ++s) {
+                const int rs = p.radix[s];
+                if (e >= at - 1) {
+                    Ns = at;
+                    r = rs;
+                }
+                at *= rs;
             }
-            const int o = e - (Ns - 1), u = o / Ns;
+            const int o = e - (Ns - 1), u = fft_div(o, 1.0f / (float)Ns);
             num = (u + 1) * (o - u * Ns);
             den = Ns * r;
         }

@@ -41,22 +41,50 @@ constexpr int FFT_THREADS = 512;   // at most, per block
 // Dynamic LDS of the line transforms: two buffers of NL lines, then the twiddles.
 extern __shared__ __align__(16) unsigned char lds_fft[];
 
+// a / b for a < 2^51, with rb = 1.0 / b from the host (fft_div in FP64: a 64-bit
+// division is hundreds of cycles at the start of every turn).
+__device__ __forceinline__ size_t div_big(size_t a, double rb) {
+    return (size_t)(((double)a + 0.5) * rb);
+}
+
+// The NL n elements of a block's first turn, put(t, get(t)): where each thread
+// has at most four, all are requested before the twiddles are formed, so that on a
+// small lattice the two latencies overlap.
+template <typename Get, typename Put>
+__device__ __forceinline__ void first_turn(double2* tw, const FftPlan& p, int count, Get get,
+                                           Put put) {
+    const int nt = (int)blockDim.x;
+    if (count <= 4 * nt) {
+        double2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if ((int)threadIdx.x + k * nt < count) v[k] = get((int)threadIdx.x + k * nt);
+        twiddles<double>(tw, p);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if ((int)threadIdx.x + k * nt < count) put((int)threadIdx.x + k * nt, v[k]);
+    } else {
+        twiddles<double>(tw, p);
+        for (int t = threadIdx.x; t < count; t += nt) put(t, get(t));
+    }
+}
+
 // Rows along x: line l of a field holds its rows 2 l (real part) and 2 l + 1
 // (imaginary part; zero past the last row).  Z = A + i B separates by
 // A(k) = (Z(k) + conj Z(n - k)) / 2, B(k) = (Z(k) - conj Z(n - k)) / 2i.
 // NL lines per block and turn; W[field][row][kx], kx = 0 .. n / 2.
 __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restrict__ fields,
                                                           double2* __restrict__ W, FftPlan p,
-                                                          int NL, uint32_t rows, size_t nlines) {
+                                                          int NL, uint32_t rows, size_t nlines,
+                                                          double rper) {
     const int n = p.n, hx = n / 2 + 1, ld = fft_ld(n);
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
-    twiddles<double>(tw, p);
-    const uint32_t per = (rows + 1) / 2;   // lines per field
+    const uint32_t per = (rows + 1) / 2;   // lines per field, 1 / rper
     const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx, rp = 1.0f / (float)per;
     for (size_t l0 = (size_t)blockIdx.x * NL; l0 < nlines; l0 += (size_t)gridDim.x * NL) {
-        const size_t f0 = l0 / per;
+        const size_t f0 = div_big(l0, rper);
         const uint32_t m0 = (uint32_t)(l0 - f0 * per);   // line l0 + L: line m0 + L of field f0
         const int nl = (int)(nlines - l0 < (size_t)NL ? nlines - l0 : (size_t)NL);
         // row of the real part of line L, over all fields
@@ -66,7 +94,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
             pair = r + 1 < rows;
             return (f0 + df) * rows + r;
         };
-        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
+        auto get = [&](int t) {
             const int L = fft_div(t, rn), x = t - L * n;
             double2 v = make_double2(0.0, 0.0);
             if (L < nl) {
@@ -75,8 +103,15 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
                 v.x = src[0];
                 if (pair) v.y = src[n];
             }
-            a[L * ld + fft_pos(x)] = v;
-        }
+            return v;
+        };
+        auto put = [&](int t, double2 v) {
+            const int L = fft_div(t, rn);
+            a[L * ld + fft_pos(t - L * n)] = v;
+        };
+        if (l0 == (size_t)blockIdx.x * NL) first_turn(tw, p, NL * n, get, put);
+        else
+            for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
         __syncthreads();
         const double2* z = fft_lines<double, false>(a, b, tw, NL, p);
         for (int t = threadIdx.x; t < nl * hx; t += blockDim.x) {
@@ -96,23 +131,29 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
 // takes NL adjacent lines at a time; groups do not cross an `inner` run.
 __global__ __launch_bounds__(FFT_THREADS) void k_fft_cols(double2* __restrict__ W, FftPlan p,
                                                           int NL, uint32_t inner, size_t outer,
-                                                          uint32_t groups, size_t ngroups) {
+                                                          uint32_t groups, size_t ngroups,
+                                                          double rgroups) {
     const int n = p.n, ld = fft_ld(n);
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
-    twiddles<double>(tw, p);
     const float rl = 1.0f / (float)NL;
     for (size_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
-        const size_t o = g / groups;
+        const size_t o = div_big(g, rgroups);
         const uint32_t c0 = (uint32_t)(g - o * groups) * (uint32_t)NL;
         const int nl = min(NL, (int)(inner - c0));
         double2* base = W + o * outer + c0;
-        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
+        auto get = [&](int t) {
             const int j = fft_div(t, rl), c = t - j * NL;
-            a[c * ld + fft_pos(j)] =
-                c < nl ? base[(size_t)j * inner + c] : make_double2(0.0, 0.0);
-        }
+            return c < nl ? base[(size_t)j * inner + c] : make_double2(0.0, 0.0);
+        };
+        auto put = [&](int t, double2 v) {
+            const int j = fft_div(t, rl);
+            a[(t - j * NL) * ld + fft_pos(j)] = v;
+        };
+        if (g == blockIdx.x) first_turn(tw, p, NL * n, get, put);
+        else
+            for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
         __syncthreads();
         const double2* z = fft_lines<double, false>(a, b, tw, NL, p);
         for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
@@ -284,7 +325,8 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         hipError_t e = fft_lds((const void*)k_fft_rows, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_fft_rows, dim3((unsigned)std::min<size_t>(blocks, FFT_GRID)),
-                           dim3(fft_block(NL, p)), lds, st, fields, W, p, NL, rows, nlines);
+                           dim3(fft_block(NL, p)), lds, st, fields, W, p, NL, rows, nlines,
+                           1.0 / (double)((rows + 1) / 2));
     }
     // y: hx adjacent lines per (field, z); z: hx ny adjacent lines per field
     for (int axis = 1; axis < 3; ++axis) {
@@ -300,7 +342,7 @@ hipError_t launch_spectrum(int q, int npairs, int nx, int ny, int nz, const doub
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_fft_cols, dim3((unsigned)std::min<size_t>(ngroups, FFT_GRID)),
                            dim3(fft_block(NL, p)), lds, st, W, p, NL, (uint32_t)inner, outer,
-                           groups, ngroups);
+                           groups, ngroups, 1.0 / (double)groups);
     }
     const size_t blocks = (V + 255) / 256 < 4096 ? (V + 255) / 256 : 4096;
     const int ygrid = npairs == 0 ? q : q - (npairs == 1 ? 1 : 2);
