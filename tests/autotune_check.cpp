@@ -1,8 +1,9 @@
-// The autotuner's choice of several D2Q9 steps per launch with every launch at
-// a known cost: 3.6 us a step in launches of several, 3.8 in all others, and
-// 20 us once per timed trial.  A choice from a handful of launches sees mostly
-// that once.  The runtime's calls are answered here, so nothing is launched and
-// no GPU is needed.  Prints the launches of several steps in 24 steps after it.
+// The autotuner's choices with every launch at a known cost: 3.6 us a step in
+// launches of several D2Q9 steps, 3 us in in-place pairs of row tiles, 3.8 in all
+// others, and 20 us once per timed trial.  A choice from a handful of launches
+// sees mostly that once.  The runtime's calls are answered here, so nothing is
+// launched and no GPU is needed.  Prints the launches of several steps in 24
+// steps after it, and the pairs chosen on a small thin box.
 
 #include <hip/hip_runtime.h>
 
@@ -19,6 +20,7 @@ static std::map<const void*, std::string>& kernels() {
 }
 static double now_us = 0.0;
 static long several = 0;
+static bool thin = false;
 static const int T = 4;   // steps per launch of this box
 static std::map<hipEvent_t, double> stamp;
 
@@ -43,7 +45,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
     const bool multi = kernels()[f].find("k_multi") != std::string::npos;
     several += multi;
-    now_us += multi ? 3.6 * T : 3.8;
+    const bool row_pair = thin && kernels()[f].find("k_step_ip") != std::string::npos;
+    now_us += multi ? 3.6 * T : row_pair ? 3.0 : 3.8;
     return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -98,5 +101,20 @@ int main() {
         flb_destroy(h);
         if (several != 24 / T) return 1;
     }
+    // a small box whose row tiles are three quarters empty: they are timed too
+    thin = true;
+    p.lattice = FLB_D3Q19;
+    p.precision = FLB_FP64;
+    p.nx = p.nz = 64;
+    p.ny = 1;
+    flb_handle* h = nullptr;
+    int32_t best[4], shape[8];
+    if (flb_init(&p, (void*)4096, (void*)(1 << 24), (void*)(2 << 24), (void*)(3 << 24), nullptr, nullptr,
+                 &h) != FLB_OK ||
+        flb_autotune(h, 5, best, nullptr, nullptr) != FLB_OK || best[3] < 0 ||
+        flb_launch_shape(h, best[3], shape) != FLB_OK)
+        return 2;
+    std::printf("pairs of %s\n", shape[7] == 3 ? "consecutive sites" : "row tiles");
+    flb_destroy(h);
     return 0;
 }

@@ -3,5 +3,9 @@
 from test_noise_shape import _run
 
 
-def test_autotune_keeps_several_steps_per_launch(tmp_path):
-    assert _run(tmp_path, "autotune_check").count(": 6 launches of several steps\n") == 2
+def test_autotune_choices_at_known_costs(tmp_path):
+    out = _run(tmp_path, "autotune_check")
+    # several D2Q9 steps per launch, without and with statistics
+    assert out.count(": 6 launches of several steps\n") == 2
+    # in-place pairs of row tiles on a small box that leaves them mostly empty
+    assert out.endswith("pairs of row tiles\n")
