@@ -140,3 +140,21 @@ def test_modeq_noise_rms_error(n, e, eps):
             ref[i] += (want[j] ** 2).sum()
     got = np.sqrt(err / ref)
     assert got[0] <= e and got[1] <= eps, got
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("logn", range(11))
+def test_modeq_power_of_two_lines(logn, prec):
+    """The in-place rows and columns of every power of two (passes of 8, 4 and 2
+    elements, and none), beside staged, thin and wide lines of the other axis."""
+    from helpers import F32_TOL, F64_TOL, rel_err
+    from oracle import modeq as OM
+    from paper_1012_3632_amd.modeq import ModEq, ModEqParams
+    n = 1 << logn
+    for nx, ny in ((n, 3), (3, n), (n, 8), (100, n)):
+        d = dict(nx=nx, ny=ny, rho0=1.0, kT=1e-5, cs2_0=0.265 ** 2, kappa=0.08, seed=6)
+        sim = ModEq(ModEqParams(precision=prec, **d))
+        xi = sim.noise(2).cpu().numpy()
+        ref = OM.noise(2, OM.ModEqParams(**d))
+        for got, want in ((xi[0], ref[0]), (xi[1], ref[5])):
+            assert rel_err(got, want) < (F64_TOL if prec == "fp64" else F32_TOL), (nx, ny)
