@@ -47,28 +47,6 @@ __device__ __forceinline__ size_t div_big(size_t a, double rb) {
     return (size_t)(((double)a + 0.5) * rb);
 }
 
-// The NL n elements of a block's first turn, put(t, get(t)): where each thread
-// has at most four, all are requested before the twiddles are formed, so that on a
-// small lattice the two latencies overlap.
-template <typename Get, typename Put>
-__device__ __forceinline__ void first_turn(double2* tw, const FftPlan& p, int count, Get get,
-                                           Put put) {
-    const int nt = (int)blockDim.x;
-    if (count <= 4 * nt) {
-        double2 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if ((int)threadIdx.x + k * nt < count) v[k] = get((int)threadIdx.x + k * nt);
-        twiddles<double>(tw, p);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if ((int)threadIdx.x + k * nt < count) put((int)threadIdx.x + k * nt, v[k]);
-    } else {
-        twiddles<double>(tw, p);
-        for (int t = threadIdx.x; t < count; t += nt) put(t, get(t));
-    }
-}
-
 // Rows along x: line l of a field holds its rows 2 l (real part) and 2 l + 1
 // (imaginary part; zero past the last row).  Z = A + i B separates by
 // A(k) = (Z(k) + conj Z(n - k)) / 2, B(k) = (Z(k) - conj Z(n - k)) / 2i.
@@ -81,6 +59,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
+    twiddles<double>(tw, p);
     const uint32_t per = (rows + 1) / 2;   // lines per field, 1 / rper
     const float rn = 1.0f / (float)n, rh = 1.0f / (float)hx, rp = 1.0f / (float)per;
     for (size_t l0 = (size_t)blockIdx.x * NL; l0 < nlines; l0 += (size_t)gridDim.x * NL) {
@@ -109,9 +88,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_rows(const double* __restri
             const int L = fft_div(t, rn);
             a[L * ld + fft_pos(t - L * n)] = v;
         };
-        if (l0 == (size_t)blockIdx.x * NL) first_turn(tw, p, NL * n, get, put);
-        else
-            for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
+        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
         __syncthreads();
         const double2* z = fft_lines<double, false>(a, b, tw, NL, p);
         for (int t = threadIdx.x; t < nl * hx; t += blockDim.x) {
@@ -137,6 +114,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_cols(double2* __restrict__ 
     double2* a = (double2*)lds_fft;
     double2* b = a + NL * ld;
     double2* tw = b + NL * ld;
+    twiddles<double>(tw, p);
     const float rl = 1.0f / (float)NL;
     for (size_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
         const size_t o = div_big(g, rgroups);
@@ -151,9 +129,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_cols(double2* __restrict__ 
             const int j = fft_div(t, rl);
             a[(t - j * NL) * ld + fft_pos(j)] = v;
         };
-        if (g == blockIdx.x) first_turn(tw, p, NL * n, get, put);
-        else
-            for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
+        for (int t = threadIdx.x; t < NL * n; t += blockDim.x) put(t, get(t));
         __syncthreads();
         const double2* z = fft_lines<double, false>(a, b, tw, NL, p);
         for (int t = threadIdx.x; t < NL * n; t += blockDim.x) {
