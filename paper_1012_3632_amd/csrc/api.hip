@@ -682,10 +682,12 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     // lose to the flat shapes wherever those fit and are not timed: on 19 such
     // boxes in both precisions, with and without statistics, the best of them took
     // 1.01 to 1.3 times the best of the others (101 x 77 x 53 14.6 against 11.8 us,
-    // 200 x 128 x 64 40.2 / 38.3, 150^3 FP64 218 / 211).  Smaller boxes time them
-    // all: idle lanes spread FP64 wavefronts over more of the chip (64 x 1 x 64 4.7
-    // against 5.1 us, 64 x 3 x 40 5.9 / 6.3 with statistics).
-    const bool flat = !h->spec.force && flat_fits(h->spec) && h->V > 32768;
+    // 200 x 128 x 64 40.2 / 38.3, 150^3 FP64 218 / 211).  Smaller D3Q19 boxes in FP64
+    // time them all: idle lanes spread the wavefronts over more of the chip (64 x 1 x
+    // 64 4.7 against 5.1 us, 64 x 3 x 40 5.9 / 6.3 with statistics; in FP32 and in two
+    // dimensions they are within 3 % at best).
+    const bool flat = !h->spec.force && flat_fits(h->spec) &&
+                      !(h->spec.lat == 1 && h->spec.prec == 1 && h->V <= 32768);
     auto sparse = [&](int c) {
         const TileShape t = config_shape(h->spec.lat, h->spec.force, c);
         return flat && !t.fl &&
