@@ -803,7 +803,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     // pairs are used when they beat ordinary steps with statistics
     const int pair_cfg = best_pair >= 0 && pair_ms < bt[1] ? best_pair : -1;
     // Several steps per launch against the steps chosen above, in turn in the
-    // same kind of trial (about 1 ms, at most 200 calls, best of three rounds): a
+    // same kind of trial (about 0.3 ms, at most 60 calls, best of three rounds): a
     // few launches after one of another kind cost up to 20 % more than in a run.
     // The others have to be faster by 3 %, since they alone lose in calls of a few
     // hundred steps, on buffers not yet settled and at the host's launch rate
@@ -826,7 +826,8 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
             return r;
         };
         auto two = [&] { return pair_cfg >= 0 ? pair(pair_cfg, part) : ordinary(bi[mode], part); };
-        const int per = std::min(200, std::max(repeats, (int)(1.f / std::max(bt[mode], 1e-3f))));
+        const int per =
+            std::min(60, std::max(repeats, (int)(0.15f / std::max(bt[mode], 1e-3f))));
         float best_multi = 1e30f, best_other = 1e30f;
         for (int round = 0; round < 3 && e == hipSuccess; ++round) {
             auto take = [&](auto&& call, int n, int steps, float* least) {
