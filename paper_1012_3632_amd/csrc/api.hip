@@ -366,7 +366,7 @@ flb_status flb_init(const flb_params* p, void* f_a, void* f_b, void* scratch, vo
     h->step = p->step0;
     h->nsamples = 0;
     // D2Q9 force steps default to the 32 x 8 tile that forms its own density
-    // tile (no density pass), D3Q19 ones to shape 0, the ideal gas to the flat
+    // tile (no density pass), D3Q19 ones to force3_default, the ideal gas to the flat
     // shapes: pairs in place while one population buffer is not far above the
     // 256 MB last-level cache (176 x 150 x 140: FP32, 281 MB, 121 us in pairs and
     // 134 between two buffers; FP64, 562 MB, 268 and 250)

@@ -224,7 +224,7 @@ __device__ __forceinline__ void fft_stage(const cx_t<R>* __restrict__ a, cx_t<R>
 // of a large prime is bound by their latency.  Modified-equilibrium runs with
 // plain sums and one thread per four elements -> these and one per two: 32 x 71
 // FP32 5.4 -> 3.7 us a step, 101 x 53 6.0 -> 4.1, 127 x 131 11.3 -> 5.8 (FP64
-// 14.2 -> 7.9), 211 x 307 33 -> 17; the spectra of 19 fields of 101^3 take 825 us.
+// 14.2 -> 7.9), 211 x 307 33 -> 19; the spectra of 19 fields of 101^3 take 825 us.
 // Not unrolled: four terms at a time took the column kernel from 67 to 98
 // registers, 449 against 398 us for the spectra of 128 x 96 x 80.
 // tw: the n roots.

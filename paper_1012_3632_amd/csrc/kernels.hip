@@ -1360,7 +1360,7 @@ static void multi_tile(const StepSpec& s, const void* fin, const MultiArgs& a, S
 // Tile edge (0: ordinary steps) and steps per launch.  Measured, us per step
 // in a captured graph, ordinary -> here: landau FP32 128^2 4.40 -> 2.78 (8, T
 // 3; 16, T 2: 3.22), 256^2 4.76 -> 3.39 (16; 8: 4.34), 512 x 256 5.54 -> 4.52,
-// 512^2 7.44 -> 6.80; with statistics 512 x 256 6.03 -> 5.22, 512^2 8.18 ->
+// 512^2 7.44 -> 6.80; with statistics 512 x 256 6.03 -> 5.30, 512^2 8.18 ->
 // 8.68; FP64 with statistics 256^2 6.89 -> 5.52, 512 x 256 8.50 -> 9.75.  Ideal
 // FP32 128^2 2.73 -> 1.82, 512^2 4.97 -> 4.59; FP64 with statistics 32^2 4.64
 // -> 2.67, 256^2 4.72 -> 3.52.  So small tiles while they leave a CU one

@@ -49,9 +49,9 @@
 //
 // 1024^2 FP32, noise per step of a 16-step launch: rows 9.0 us (6.1 if they were
 // FP32), columns 11.1 us, rows back 4.5 us; 11.6, 20.3 and 11.6 us with two
-// full spectra.  200 x 150 FP64, noise and one step per launch: 11.3 us, 31 us
-// when extents that are not powers of two took n^2 direct sums; 7.0 us with
-// several steps per launch (modeq_steps).
+// full spectra.  200 x 150 FP64, one step per call and launch: 31 us
+// when extents that are not powers of two took n^2 direct sums; 6.6 us a step
+// with several steps per launch (modeq_steps).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -731,8 +731,8 @@ hipError_t launch_step_t(const ModEqArgs& a, int T, const void* fin, void* fout,
 }  // namespace
 
 // us per step with its noise, one step per launch -> T = 2 on 16 x 16 tiles ->
-// T = 3 on 8 x 8 tiles: 128^2 FP32 4.97 -> 4.04 -> 3.64, 200 x 150 FP64 8.96 ->
-// 6.97 -> 6.95, 256^2 FP32 6.52 -> 5.40 -> 5.73, 1024^2 FP32 44.2 -> 42.2 -> 47.3.
+// T = 3 on 8 x 8 tiles: 128^2 FP32 4.53 -> 3.69 -> 3.18, 200 x 150 FP64 8.50 ->
+// 6.73 -> 6.58, 256^2 FP32 6.04 -> 5.00 -> 5.23, 1024^2 FP32 45.0 -> 41.9 -> 44.5.
 // So three steps while the chip is far from full, two otherwise, unless the
 // tiles of a strip cover far more than its sites.
 int modeq_steps(const ModEqArgs& a) {
