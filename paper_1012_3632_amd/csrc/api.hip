@@ -707,6 +707,9 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
         *ms_out = ms / (float)(repeats * per_call);
         return r;
     };
+    // every trial step draws the noise of a step of its own: thousands of steps
+    // under one and the same noise are driven far from any state of a run
+    unsigned long long at = h->step;
     // a force step that reads a density field pays for its pass; a
     // partial-density march for the completion of the next density
     auto ordinary_step = [&](int c, double* part, void* in, void* out) {
@@ -715,7 +718,7 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
         if (h->spec.force && !config_fused(h->spec, c) && !pd)
             r = launch_density(h->spec, in, h->drho, st);
         if (r == hipSuccess)
-            r = launch_step(h->spec, c, in, out, h->drho, nullptr, h->step, part, st, nullptr,
+            r = launch_step(h->spec, c, in, out, h->drho, nullptr, at++, part, st, nullptr,
                             step_work(h, c));
         if (r == hipSuccess && pd)
             r = launch_density_fix(h->spec, c, out, h->rho_part, h->drho, st);
@@ -750,9 +753,9 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
     for (int c = 0; c < ncfg; ++c)
         if (config_in_place(h->spec, c) && !sparse(c)) cands.push_back(c);
     auto pair = [&](int c, double* part) {
-        hipError_t r = launch_step_in_place(h->spec, c, 0, A, nullptr, h->step, part, st);
+        hipError_t r = launch_step_in_place(h->spec, c, 0, A, nullptr, at++, part, st);
         if (r == hipSuccess)
-            r = launch_step_in_place(h->spec, c, 1, A, nullptr, h->step + 1, part, st);
+            r = launch_step_in_place(h->spec, c, 1, A, nullptr, at++, part, st);
         return r;
     };
     // two ordinary steps, A -> B -> A
@@ -820,8 +823,8 @@ flb_status flb_autotune(flb_handle* h, int32_t repeats, int32_t* best, double* b
                 MultiArgs a{};
                 a.out[T - 1] = k ? A : B;
                 a.mask = mode ? (1u << T) - 1u : 0u;
-                r = launch_multi(h->spec, mode == 1, h->slots, k ? B : A, a, nullptr, h->step, h->stats,
-                                 st);
+                r = launch_multi(h->spec, mode == 1, h->slots, k ? B : A, a, nullptr, at, h->stats, st);
+                at += (unsigned long long)T;
             }
             return r;
         };

@@ -3,13 +3,15 @@
 // others, and 20 us once per timed trial.  A choice from a handful of launches
 // sees mostly that once.  The runtime's calls are answered here, so nothing is
 // launched and no GPU is needed.  Prints the launches of several steps in 24
-// steps after it, and the pairs chosen on a small thin box.
+// steps after it, the trials of several steps that drew the noise of a step drawn
+// before, and the pairs chosen on a small thin box.
 
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 
 #include "../include/flb.h"
@@ -19,7 +21,8 @@ static std::map<const void*, std::string>& kernels() {
     return m;
 }
 static double now_us = 0.0;
-static long several = 0;
+static long several = 0, drawn_before = 0;
+static std::set<unsigned long long> drawn;
 static bool thin = false;
 static const int T = 4;   // steps per launch of this box
 static std::map<hipEvent_t, double> stamp;
@@ -42,9 +45,17 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     *st = nullptr;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
     const bool multi = kernels()[f].find("k_multi") != std::string::npos;
     several += multi;
+    if (multi) {   // the fifth argument: the device counter (null here) and the host's index
+        struct StepIndex {
+            const unsigned long long* dev;
+            unsigned long long host;
+        } at;
+        std::memcpy(&at, args[4], sizeof at);
+        drawn_before += !drawn.insert(at.host).second;
+    }
     const bool row_pair = thin && kernels()[f].find("k_step_ip") != std::string::npos;
     now_us += multi ? 3.6 * T : row_pair ? 3.0 : 3.8;
     return hipSuccess;
@@ -96,11 +107,16 @@ int main() {
             return 2;
         }
         several = 0;
+        const long trials_before = drawn_before;
+        drawn.clear();
         if (flb_step(h, 24, stats, nullptr) != FLB_OK) return 2;
         std::printf("stride %d: %ld launches of several steps\n", stats, several);
         flb_destroy(h);
+        drawn.clear();
+        drawn_before = trials_before;
         if (several != 24 / T) return 1;
     }
+    std::printf("%ld trials under noise drawn before\n", drawn_before);
     // a small box whose row tiles are three quarters empty: they are timed too
     thin = true;
     p.lattice = FLB_D3Q19;
