@@ -485,7 +485,7 @@ flb_status flb_batch_destroy(flb_batch* b);
  * steps alternate the two buffers over `repeats` steps; in-place pairs and the
  * fastest ordinary step with statistics are timed after about 4 ms of settling
  * steps, round-robin over at least three rounds of about 2 ms each, best round
- * kept) and afterwards
+ * kept; every trial step draws the noise of a step of its own) and afterwards
  * restores the state and the accumulated statistics from a host copy (host
  * memory of one population buffer plus the statistics slots); it writes
  * best[4]: the fastest shape for plain steps, for steps with statistics, the
@@ -503,8 +503,9 @@ flb_status flb_batch_destroy(flb_batch* b);
  * Small D2Q9 lattices (at most 2^18 sites in FP32, less in FP64 and with
  * statistics) take two to four steps per launch, with the bits of as many
  * ordinary steps in populations and noise (statistics are summed in another
- * order); flb_autotune times that too and keeps it where it is the fastest,
- * and the shapes above then serve the steps left over.  flb_set_launch turns
+ * order, over the steps of a launch in FP64); flb_autotune times that too, in
+ * turn with the steps a call would take otherwise, and keeps it unless those are
+ * faster by 3 %, and the shapes above then serve the steps left over.  flb_set_launch turns
  * it off.
  * flb_set_launch sets every shape to `config` (an in-place shape then serves
  * pairs and, as an ordinary kernel of its tile, lone steps);
