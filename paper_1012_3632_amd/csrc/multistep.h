@@ -211,8 +211,8 @@ __global__ __launch_bounds__((MultiTile<FORCE, T, TX, TY>::NT)) void k_multi(
     // Statistics: a thread adds its steps in FP64, as steps of a launch of their
     // own are (an FP32 sum over the steps dropped what is below 2^-24 of it), with
     // one reduction for all of them: 200 x 200 FP32, ideal gas, 2.36 -> 2.44 us a
-    // step, Landau 3.97 -> 4.05; the rows of every step reduced to FP64 by
-    // themselves took 2.54 and 4.06.
+    // step, Landau 3.97 -> 4.05 (one step per launch 3.9 and 5.4); the rows of
+    // every step reduced to FP64 by themselves took 2.54 and 4.06.
     double v[STATS ? 2 * Q : 1];
 #pragma unroll
     for (int k = 0; k < (STATS ? 2 * Q : 1); ++k) v[k] = 0.0;
